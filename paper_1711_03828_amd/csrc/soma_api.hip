@@ -1433,6 +1433,57 @@ uint64_t soma_sq_workspace_bytes(const soma_system *sys) {
   return align_up(16 * n) * 2 + align_up(16ull * (sys->cfg.nx + sys->cfg.ny + sys->cfg.nz));
 }
 
+}  // extern "C"
+
+namespace {
+// Radices of the steps of a line of n: eights, a four or a two, then the odd
+// prime factors; false if there are more than the kernel takes (never for n <=
+// kSqMaxLine).
+bool sq_plan(uint32_t n, soma::SqPass &p) {
+  p.n = n;
+  p.n_steps = 0;
+  uint32_t rest = n;
+  auto take = [&](uint32_t r) {
+    while (rest % r == 0 && p.n_steps < soma::kSqMaxSteps) {
+      p.radix[p.n_steps++] = (uint16_t)r;
+      rest /= r;
+    }
+  };
+  take(8);
+  take(4);
+  take(2);
+  for (uint32_t r = 3; rest > 1 && r * r <= rest; r += 2) take(r);
+  if (rest > 1 && p.n_steps < soma::kSqMaxSteps) {
+    p.radix[p.n_steps++] = (uint16_t)rest;
+    rest = 1;
+  }
+  return rest == 1;
+}
+
+// Lines per block: about 1024 elements, at least 8 lines (128 B of consecutive
+// half-spectrum values) where LDS holds them.
+void sq_tile(soma::SqPass &p) {
+  auto fits = [&](uint32_t t) { return (2ull * t + 1u) * p.n * 16u <= soma::kSqLdsBytes; };
+  p.t = 1;
+  p.t_shift = 0;
+  while (p.t < 64u && fits(2u * p.t) && (2u * p.t * p.n <= 1024u || p.t < 8u)) {
+    p.t *= 2u;
+    ++p.t_shift;
+  }
+}
+
+template <int PASS>
+int32_t launch_sq_pass(const soma::SqPass &p, hipStream_t s) {
+  const uint32_t blocks = (p.n_lines + p.t - 1u) / p.t;
+  const size_t lds = (size_t)(2u * p.t + 1u) * p.n * 16u;
+  hipLaunchKernelGGL(soma::sq_fft_kernel<PASS>, dim3(blocks), dim3(soma::kSqThreads), lds, s, p);
+  LAUNCH_TRY();
+  return SOMA_OK;
+}
+}  // namespace
+
+extern "C" {
+
 int32_t soma_structure_factor(soma_system *sys, void *workspace, uint64_t workspace_bytes,
                               double *sq, void *stream) {
   if (!sys || !workspace || !sq) return fail(SOMA_E_INVAL, "NULL argument");
@@ -1445,6 +1496,33 @@ int32_t soma_structure_factor(soma_system *sys, void *workspace, uint64_t worksp
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const uint64_t n = sys->d.n_cells;
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
+  const double nn = (double)sys->cfg.n_ref;
+  const double scale = nn * nn / (4.0 * (double)sys->d.n_beads);
+  const uint32_t axis[3] = {sys->cfg.nx, sys->cfg.ny, sys->cfg.nz};
+  if (std::max(axis[0], std::max(axis[1], axis[2])) <= soma::kSqMaxLine) {
+    soma::SqPass p;
+    p.nx = axis[0];
+    p.ny = axis[1];
+    p.nz = axis[2];
+    p.hx = p.nx / 2u + 1u;
+    p.counts = sys->buf.counts;
+    p.count64 = sys->cfg.count_width == 32;
+    p.a = reinterpret_cast<double2 *>(ws);
+    p.tw_y = reinterpret_cast<double2 *>(ws + 2 * align_up(16 * n)) + p.nx;
+    p.tw_z = p.tw_y + p.ny;
+    p.sq = sq;
+    p.scale = scale;
+    const uint32_t lines[3] = {p.ny * p.nz, p.hx * p.nz, p.hx * p.ny};
+    for (int k = 0; k < 3; ++k) {
+      p.n_lines = lines[k];
+      if (!sq_plan(axis[k], p)) return fail(SOMA_E_UNSUPPORTED, "axis of %u cells", axis[k]);
+      sq_tile(p);
+      const int32_t rc = k == 0 ? launch_sq_pass<0>(p, s)
+                         : k == 1 ? launch_sq_pass<1>(p, s) : launch_sq_pass<2>(p, s);
+      if (rc) return rc;
+    }
+    return SOMA_OK;
+  }
   soma::SqArgs a;
   a.counts = sys->buf.counts;
   a.count64 = sys->cfg.count_width == 32;
@@ -1472,9 +1550,7 @@ int32_t soma_structure_factor(soma_system *sys, void *workspace, uint64_t worksp
   hipLaunchKernelGGL(soma::sq_dft_axis_kernel, grid, dim3(256), 0, s, a.b, a.a, a.tw[2], a.nx,
                      a.ny, a.nz, 2);
   LAUNCH_TRY();
-  const double nn = (double)sys->cfg.n_ref;
-  hipLaunchKernelGGL(soma::sq_power_kernel, grid, dim3(256), 0, s, a.a, sq, n,
-                     nn * nn / (4.0 * (double)sys->d.n_beads));
+  hipLaunchKernelGGL(soma::sq_power_kernel, grid, dim3(256), 0, s, a.a, sq, n, scale);
   LAUNCH_TRY();
   return SOMA_OK;
 }

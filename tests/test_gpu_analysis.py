@@ -55,6 +55,27 @@ def test_structure_factor_matches_oracle(orc, wname):
     np.testing.assert_allclose(m1, m2, rtol=1e-9)
 
 
+@pytest.mark.parametrize("grid,width", [
+    ((1, 1, 5), 16), ((2, 3, 1), 32), ((64, 1, 27), 16), ((7, 49, 11), 32), ((125, 6, 2), 16),
+    ((96, 40, 9), 16), ((33, 16, 128), 32), ((1361, 2, 3), 16), ((3, 2, 1365), 32),
+    ((4, 1366, 1), 16)])
+def test_structure_factor_axis_lengths(orc, grid, width):
+    """Every kind of line: lengths 1 and 2, powers of two, each small radix, primes, the longest
+    line of the LDS passes and a longer one (direct sums).  Bar 1e-12 of the largest value: a sum
+    of at most 1366 rounded FP64 terms per axis, 3 * 1366 * 2^-53 = 4.5e-13 of sum |psi|."""
+    from paper_1711_03828_amd.melt import Melt
+    w = synth.Workload("axis", grid, (synth.SpeciesSpec(150, 17, 9),), 6.0, 17, 20.0, 50.0, width)
+    pos = walks_for(w, 63)
+    m = Melt(device_config(w), positions=torch.from_numpy(pos))
+    counts = orc.density_hist(pos, [Species(150, 17, 9)], grid)
+    exp = A.structure_factor(counts, grid, w.n_ref, w.n_beads)
+    flush(grid, width)
+    got = _device_sq(m)
+    err = np.abs(got - exp).max() / max(exp.max(), np.abs(counts.astype(float)).sum())
+    flush(grid, "max rel err", err)
+    assert err <= 1e-12
+
+
 def test_slab_pattern_peak():
     """A beads in two slabs along z (period L/2): peak shell 2."""
     from paper_1711_03828_amd import soma as C
