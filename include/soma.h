@@ -630,8 +630,7 @@ int32_t soma_train_step(const float *features, const float *targets, uint32_t n,
 /* soma_train_step for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same step, arguments and results, without a workspace argument.  Its
- * scratch (the prepared network and up to SOMA_NOALLOC_TRAIN_WAVES partial
- * gradients, about 4.4 MB) is a fixed device array of the library, one per
+ * scratch (up to SOMA_NOALLOC_TRAIN_WAVES partial gradients, about 4.4 MB) is a fixed device array of the library, one per
  * GPU, held until the process ends; the call allocates nothing.  The number
  * of partial gradients is that of soma_train_step (opts->max_waves, or one
  * per 64 samples if 0); SOMA_E_SIZE if it exceeds SOMA_NOALLOC_TRAIN_WAVES

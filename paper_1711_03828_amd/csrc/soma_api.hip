@@ -1618,8 +1618,7 @@ int32_t soma_sq_shells(const double *sq, uint32_t nx, uint32_t ny, uint32_t nz,
 
 uint64_t soma_train_workspace_bytes(uint32_t max_waves) {
   if (max_waves == 0) max_waves = 1;
-  return align_up(sizeof(soma::NetDev)) + align_up((uint64_t)max_waves * soma::kPSize * 4ull) +
-         align_up((uint64_t)max_waves * 4ull);
+  return align_up((uint64_t)max_waves * soma::kPSize * 4ull) + align_up((uint64_t)max_waves * 4ull);
 }
 
 }  // extern "C"
@@ -1627,7 +1626,7 @@ uint64_t soma_train_workspace_bytes(uint32_t max_waves) {
 namespace {
 
 // The training step on a scratch buffer `workspace` of workspace_bytes bytes
-// (the prepared network, per-wave partial gradients and loss partials; every
+// (the partial gradients and loss partials of the grad kernel's blocks; every
 // byte the step reads is written by the step first).
 int32_t train_step_impl(const float *features, const float *targets, uint32_t n, float *params,
                         float *adam_m, float *adam_v, uint32_t step, const soma_train_opts *o,
@@ -1649,14 +1648,11 @@ int32_t train_step_impl(const float *features, const float *targets, uint32_t n,
                 (unsigned long long)soma_train_workspace_bytes(waves));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
-  soma::NetDev *net = reinterpret_cast<soma::NetDev *>(ws);
-  float *partials = reinterpret_cast<float *>(ws + align_up(sizeof(soma::NetDev)));
-  float *lossp = reinterpret_cast<float *>(ws + align_up(sizeof(soma::NetDev)) +
-                                           align_up((uint64_t)waves * soma::kPSize * 4ull));
-  hipLaunchKernelGGL(soma::net_prepare_kernel, dim3(soma::kNetPrepareBlocks), dim3(256), 0, s, params, net);
-  LAUNCH_TRY();
+  float *partials = reinterpret_cast<float *>(ws);
+  float *lossp = reinterpret_cast<float *>(ws + align_up((uint64_t)waves * soma::kPSize * 4ull));
   soma::TrainArgs ta;
-  ta.net = net;
+  ta.params = params;
+  ta.vec4 = aligned(params, 16) && aligned(features, 16) ? 1u : 0u;
   ta.feat = features;
   ta.target = targets;
   ta.n = n;
@@ -1665,7 +1661,7 @@ int32_t train_step_impl(const float *features, const float *targets, uint32_t n,
   ta.head.hi = o->log_sigma_max;
   ta.partials = partials;
   ta.loss_partials = lossp;
-  hipLaunchKernelGGL(soma::mlp_grad_kernel, dim3(waves), dim3(64), 0, s, ta);
+  hipLaunchKernelGGL(soma::mlp_grad_kernel, dim3(waves), dim3(256), 0, s, ta);
   LAUNCH_TRY();
   soma::AdamArgs aa;
   aa.partials = partials;
@@ -1686,18 +1682,16 @@ int32_t train_step_impl(const float *features, const float *targets, uint32_t n,
   aa.loss_out = loss_out;
   hipLaunchKernelGGL(soma::mlp_adam_kernel,
                      dim3((soma::kPSize + soma::kAdamParamsPerBlock - 1) / soma::kAdamParamsPerBlock),
-                     dim3(256), 0, s, aa);
+                     dim3(64 * soma::kAdamWaves), 0, s, aa);
   LAUNCH_TRY();
   return SOMA_OK;
 }
 
-// Scratch of soma_train_step_noalloc: the prepared network, up to
-// kNoAllocWaves partial gradients and their loss partials, in a device array
-// of the library (one copy per GPU, held until the process ends).
+// Scratch of soma_train_step_noalloc: up to kNoAllocWaves partial gradients and
+// their loss partials, in a device array of the library (one copy per GPU, held until the process ends).
 constexpr uint64_t align256(uint64_t x) { return (x + 255u) / 256u * 256u; }
 constexpr uint32_t kNoAllocWaves = SOMA_NOALLOC_TRAIN_WAVES;
-constexpr uint64_t kNoAllocBytes = align256(sizeof(soma::NetDev)) +
-                                   align256((uint64_t)kNoAllocWaves * soma::kPSize * 4u) +
+constexpr uint64_t kNoAllocBytes = align256((uint64_t)kNoAllocWaves * soma::kPSize * 4u) +
                                    align256((uint64_t)kNoAllocWaves * 4u);
 
 }  // namespace

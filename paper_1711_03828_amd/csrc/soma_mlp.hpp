@@ -31,21 +31,16 @@ constexpr int kActStride = 72;  // bf16 per LDS row: 64 units + 8 padding
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Device copy of the network, ready for the MFMA tiles.  The learned move
-// evaluates the first layer with the input standardisation folded in (w1f,
-// b1f: W1'[o][k] = W1[o][k] scale[k], b1'[o] = b1[o] - sum_k W1'[o][k] shift[k]
-// in FP32, k ascending), so raw features go straight to BF16; training uses
-// the standardised form (shift, scale, w1, b1).
+// Device copy of the network, ready for the MFMA tiles of the learned move,
+// with the input standardisation folded into the first layer (w1f, b1f:
+// W1'[o][k] = W1[o][k] scale[k], b1'[o] = b1[o] - sum_k W1'[o][k] shift[k] in
+// FP32, k ascending), so raw features go straight to BF16.  Training works on
+// the standardised form, converted from the parameter blob by its own kernel.
 struct NetDev {
-  float shift[64], scale[64];  // entries 60..63: shift 0, scale 0 (feature 0)
-  float b1[64], b2[64], b3[16];
-  __bf16 w1[64 * 64];          // [out][in], in >= 60 zero
-  __bf16 w2[64 * 64];          // [out][in]
-  __bf16 w3[16 * 64];          // rows >= 6 zero
-  __bf16 w2t[64 * 64];         // W2 transposed: [in][out]
-  __bf16 w3t[64 * 32];         // [hidden][k]: W3[k][hidden] for k < 6, else 0
-  float b1f[64];               // folded first-layer bias
-  __bf16 w1f[64 * 64];         // folded first-layer weights [out][in], in >= 60 zero
+  float b1f[64], b2[64], b3[16];   // folded first-layer bias, the other biases
+  __bf16 w1f[64 * 64];             // folded first-layer weights [out][in], in >= 60 zero
+  __bf16 w2[64 * 64];              // [out][in]
+  __bf16 w3[16 * 64];              // rows >= 6 zero
 };
 
 struct HeadArgs {
@@ -61,9 +56,6 @@ __global__ __launch_bounds__(256) void net_prepare_kernel(const float *__restric
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= 64 * 64) return;
   if (i < 64) {
-    net->shift[i] = i < kNF ? p[kPShift + i] : 0.0f;
-    net->scale[i] = i < kNF ? p[kPScale + i] : 0.0f;
-    net->b1[i] = p[kPB1 + i];
     net->b2[i] = p[kPB2 + i];
     if (i < 16) net->b3[i] = i < kNO ? p[kPB3 + i] : 0.0f;
     float b = p[kPB1 + i];   // folded bias of unit i (built without FP contraction)
@@ -75,15 +67,9 @@ __global__ __launch_bounds__(256) void net_prepare_kernel(const float *__restric
     net->b1f[i] = b;
   }
   const int o = i >> 6, k = i & 63;
-  net->w1[i] = (__bf16)(k < kNF ? p[kPW1 + o * kNF + k] : 0.0f);
   net->w1f[i] = (__bf16)(k < kNF ? p[kPW1 + o * kNF + k] * p[kPScale + k] : 0.0f);
   net->w2[i] = (__bf16)p[kPW2 + o * kNH + k];
-  net->w2t[i] = (__bf16)p[kPW2 + k * kNH + o];
   if (o < 16) net->w3[i] = (__bf16)(o < kNO ? p[kPW3 + o * kNH + k] : 0.0f);
-  if (i < 64 * 32) {
-    const int h = i >> 5, kk = i & 31;
-    net->w3t[i] = (__bf16)(kk < kNO ? p[kPW3 + kk * kNH + h] : 0.0f);
-  }
 }
 
 // Hardware reciprocal (1 ulp): ample where the result feeds a bfloat16 tile

@@ -2,14 +2,15 @@
 // cores: forward, Gaussian negative log-likelihood of observed displacements,
 // back-propagation and Adam, all with BF16 MFMA inputs and FP32 accumulation.
 //
-// One wavefront (a 64-thread block) handles chunks of 64 samples (lane =
-// sample).  Every matrix product is a v_mfma_f32_16x16x32_bf16 tile: the
-// forward and the error propagation contract over units (activations and
-// errors in sample-major LDS tiles are the B operand), the weight gradients
-// contract over the 64 samples of a chunk (unit-major, transposed LDS tiles).
-// Gradients accumulate in registers over all chunks of the wave and are
-// written once as a per-wave partial; a second kernel sums the partials in a
-// fixed order and applies Adam to the FP32 master parameters.
+// A block of four waves takes chunks of 64 samples, 16 per wave.  Every matrix
+// product is a v_mfma_f32_16x16x32_bf16 tile: the forward and the error
+// propagation contract over units (a wave's samples stay in its own rows of a
+// sample-major LDS tile, so the layers need no block barrier), the weight
+// gradients contract over the 64 samples of the chunk (unit-major, transposed
+// LDS tiles; wave w owns the 16 input units 16 w .. of every gradient).
+// Gradients accumulate in registers over all chunks of the block and are
+// written once as a partial; a second kernel sums the partials in a fixed
+// order and applies Adam to the FP32 master parameters.
 #pragma once
 
 #include "soma_mlp.hpp"
@@ -19,226 +20,257 @@ namespace soma {
 constexpr int kTStride = 72;  // bf16 per row of a transposed (unit-major) tile
 
 struct TrainArgs {
-  const NetDev *net;
+  const float *params;   // FP32 blob
   const float *feat;     // [n][60] raw features
   const float *target;   // [n][3] displacements
   uint32_t n;
+  uint32_t vec4;         // params and feat are 16-byte aligned
   HeadArgs head;
-  float *partials;       // [waves][kPSize] gradient partials (sums over samples)
-  float *loss_partials;  // [waves]
+  float *partials;       // [blocks][kPSize] gradient partials (sums over samples)
+  float *loss_partials;  // [blocks]
 };
 
 __device__ __forceinline__ bf16x8 lds8(const __bf16 *p) { return *reinterpret_cast<const bf16x8 *>(p); }
 
-__device__ __forceinline__ float drelu(float a) { return a > 0.0f ? 1.0f : 0.0f; }
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// out[mt][t] += W[16 mt + row][k] * act[sample][k] over K = 64 (two blocks):
-// rows of W (global, [64][64] bf16), act sample-major LDS [64][72].
-__device__ __forceinline__ void mm_units(const __bf16 *__restrict__ w, int w_stride, int m_tiles,
-                                         int k_blocks, const __bf16 *act, f32x4 (&acc)[4][4]) {
-  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-  for (int kb = 0; kb < k_blocks; ++kb) {
-    bf16x8 b[4];
+// Four consecutive floats, as one 16-byte load where the base is aligned (the
+// offsets used are multiples of four).
+__device__ __forceinline__ f32x4 load_f4(const float *p, uint32_t vec4) {
+  if (vec4) return *reinterpret_cast<const f32x4 *>(p);
+  return f32x4{p[0], p[1], p[2], p[3]};
+}
+
+// Orders the LDS accesses of one wave's lanes (a wave's LDS operations execute
+// in issue order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The weights of a block as BF16 tiles: W1 (inputs 60..63 zero), W2, W2
+// transposed, W3 (rows >= 6 zero) and W3 transposed ([hidden][8], outputs >= 6
+// zero), with the FP32 standardisation and biases.
+struct alignas(16) TrainLds {
+  __bf16 w1[64 * kTStride], w2[64 * kTStride], w2t[64 * kTStride], w3[16 * kTStride], w3t[64 * 8];
+  __bf16 act[64 * kActStride];   // sample-major: the input, then each layer's activations and errors
+  __bf16 x_t[64 * kTStride], h1_t[64 * kTStride], h2_t[64 * kTStride];
+  __bf16 d1_t[64 * kTStride], d2_t[64 * kTStride], dz_t[16 * kTStride];
+  __bf16 dz_s[64 * 8];
+  float z[64 * 8];
+  float shift[64], scale[64], b1[64], b2[64], b3[8];
+  float red1[4][64], red2[4][64], red3[4][8], red_loss[4];
+};
+
+__device__ __forceinline__ void stage_weights(const TrainArgs &a, TrainLds &s) {
+  const uint32_t tid = threadIdx.x;
+  for (uint32_t q = tid; q < 64u * 16u; q += 256u) {   // four inputs of one output row
+    const uint32_t o = q >> 4, k = 4u * (q & 15u);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 v1 = k < (uint32_t)kNF ? load_f4(a.params + kPW1 + o * kNF + k, a.vec4) : zero;
+    const f32x4 v2 = load_f4(a.params + kPW2 + o * kNH + k, a.vec4);
+    *reinterpret_cast<bf16x4 *>(s.w1 + o * kTStride + k) = __builtin_convertvector(v1, bf16x4);
+    const bf16x4 b2 = __builtin_convertvector(v2, bf16x4);
+    *reinterpret_cast<bf16x4 *>(s.w2 + o * kTStride + k) = b2;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) b[t] = lds8(act + (16 * t + col) * kActStride + 32 * kb + 8 * g);
-    for (int mt = 0; mt < m_tiles; ++mt) {
-      const bf16x8 av = *reinterpret_cast<const bf16x8 *>(w + (16 * mt + col) * w_stride + 32 * kb + 8 * g);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[t], acc[mt][t], 0, 0, 0);
-    }
+    for (int j = 0; j < 4; ++j) s.w2t[(k + j) * kTStride + o] = b2[j];
   }
-}
-
-// acc[mt][nt] += A[16 mt + row][s] * B[16 nt + col][s] over the 64 samples s,
-// both unit-major LDS tiles [units][kTStride].
-__device__ __forceinline__ void mm_samples(const __bf16 *a_t, int m_tiles, const __bf16 *b_t,
-                                           int n_tiles, f32x4 (&acc)[4][4]) {
-  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+  {
+    const uint32_t o = tid >> 4, k = 4u * (tid & 15u);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (o < (uint32_t)kNO) v = load_f4(a.params + kPW3 + o * kNH + k, a.vec4);
+    const bf16x4 b = __builtin_convertvector(v, bf16x4);
+    *reinterpret_cast<bf16x4 *>(s.w3 + o * kTStride + k) = b;
+    if (o < 8u)
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    bf16x8 b[4];
-    for (int nt = 0; nt < n_tiles; ++nt) b[nt] = lds8(b_t + (16 * nt + col) * kTStride + 32 * kb + 8 * g);
-    for (int mt = 0; mt < m_tiles; ++mt) {
-      const bf16x8 av = lds8(a_t + (16 * mt + col) * kTStride + 32 * kb + 8 * g);
-      for (int nt = 0; nt < n_tiles; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[nt], acc[mt][nt], 0, 0, 0);
-    }
+      for (int j = 0; j < 4; ++j) s.w3t[(k + j) * 8 + o] = b[j];
   }
+  if (tid < 64u) {
+    s.shift[tid] = tid < (uint32_t)kNF ? a.params[kPShift + tid] : 0.0f;
+    s.scale[tid] = tid < (uint32_t)kNF ? a.params[kPScale + tid] : 0.0f;
+    s.b1[tid] = a.params[kPB1 + tid];
+    s.b2[tid] = a.params[kPB2 + tid];
+    if (tid < 8u) s.b3[tid] = tid < (uint32_t)kNO ? a.params[kPB3 + tid] : 0.0f;
+  }
+  // error rows 6..15 stay zero
+  for (uint32_t q = tid; q < 16u * kTStride; q += 256u) s.dz_t[q] = (__bf16)0.0f;
 }
 
-__device__ __forceinline__ void zero_acc(f32x4 (&acc)[4][4]) {
+// One hidden layer of the wave's 16 samples (row = 16 wv + col of `act`): ReLU
+// of the BF16 product plus bias, to the sample's own row and transposed to
+// `h_t`; returns the units with a positive input, bit 4 mt + r.
+__device__ __forceinline__ uint32_t train_layer(const __bf16 *w, const float *bias, __bf16 *act,
+                                                __bf16 *h_t, uint32_t wv) {
+  const uint32_t lane = threadIdx.x & 63u, col = lane & 15u, g = lane >> 4, sm = 16u * wv + col;
+  bf16x8 b[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int kb = 0; kb < 2; ++kb) b[kb] = lds8(act + sm * kActStride + 32 * kb + 8 * g);
+  wave_lds_fence();
+  uint32_t on = 0u;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int mt = 0; mt < 4; ++mt) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds8(w + (16 * mt + col) * kTStride + 32 * kb + 8 * g),
+                                                    b[kb], acc, 0, 0, 0);
+    const uint32_t u = 16u * mt + 4u * g;
+    const f32x4 pre = acc + *reinterpret_cast<const f32x4 *>(bias + u);
+    bf16x4 h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h[r] = (__bf16)relu(pre[r]);
+      on |= pre[r] > 0.0f ? 1u << (4 * mt + r) : 0u;
+    }
+    *reinterpret_cast<bf16x4 *>(act + sm * kActStride + u) = h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h_t[(u + r) * kTStride + sm] = h[r];
+  }
+  wave_lds_fence();
+  return on;
 }
 
-__global__ __launch_bounds__(64) void mlp_grad_kernel(const TrainArgs a) {
-  __shared__ __bf16 x_s[64 * kActStride], h1_s[64 * kActStride], h2_s[64 * kActStride];
-  __shared__ __bf16 d2_s[64 * kActStride];
-  __shared__ __bf16 x_t[64 * kTStride], h1_t[64 * kTStride], h2_t[64 * kTStride];
-  __shared__ __bf16 d1_t[64 * kTStride], d2_t[64 * kTStride], dz_t[16 * kTStride];
-  __shared__ __bf16 dz_s[64 * 32];
-  __shared__ float a1_f[64 * 64], a2_f[64 * 64], z_f[64 * 8];
-  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-  const NetDev *net = a.net;
-
-  f32x4 gw1[4][4], gw2[4][4], gw3[4][4];
-  zero_acc(gw1);
-  zero_acc(gw2);
-  zero_acc(gw3);
-  float gb1[4][4], gb2[4][4], gb3[kNO] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, loss = 0.0f;
+// One block per partial gradient, four waves.  Bound by latency (a chain of six
+// small products per chunk and the traffic through LDS between them), which is
+// why a chunk is spread over four waves and the weights are converted here
+// instead of by a kernel before it.  Batch 8192 (128 chunks), whole step: 46.9 us
+// with one wave per chunk, per-sample strided feature loads and three launches.
+__global__ __launch_bounds__(256) void mlp_grad_kernel(const TrainArgs a) {
+  __shared__ TrainLds s;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6, col = lane & 15u, g = lane >> 4;
+  const uint32_t sm = 16u * wv + col;   // the lane's sample within the chunk
+  stage_weights(a, s);
+  f32x4 gw1[4], gw2[4], gw3 = {0.f, 0.f, 0.f, 0.f}, gb1[4], gb2[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) gb1[i][j] = gb2[i][j] = 0.0f;
+  for (int i = 0; i < 4; ++i) gw1[i] = gw2[i] = gb1[i] = gb2[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gmu = 0.0f, gls = 0.0f, loss = 0.0f;   // output-bias gradients of dimension g
 
   const uint32_t n_chunks = (a.n + 63u) / 64u;
   for (uint32_t chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
-    const uint32_t s = chunk * 64u + (uint32_t)lane;
-    const bool valid = s < a.n;
-    // standardised inputs, sample-major and unit-major
-    for (int k = 0; k < 64; ++k) {
-      const float raw = (valid && k < kNF) ? a.feat[(size_t)s * kNF + k] : 0.0f;
-      const __bf16 v = k < kNF ? (__bf16)((raw - net->shift[k]) * net->scale[k]) : (__bf16)0.0f;
-      x_s[lane * kActStride + k] = v;
-      x_t[k * kTStride + lane] = v;
+    const uint32_t s0 = chunk * 64u;
+    __syncthreads();   // the tiles of the chunk before are read; the weights are staged
+    // standardised inputs, sample-major and unit-major; quad q = features 4 (q mod 16) ..
+    for (uint32_t q = tid; q < 64u * 16u; q += 256u) {
+      const uint32_t sr = q >> 4, k = 4u * (q & 15u);
+      f32x4 raw = {0.f, 0.f, 0.f, 0.f};
+      if (s0 + sr < a.n && k < (uint32_t)kNF) raw = load_f4(a.feat + (size_t)(s0 + sr) * kNF + k, a.vec4);
+      const f32x4 v = (raw - *reinterpret_cast<const f32x4 *>(s.shift + k)) *
+                      *reinterpret_cast<const f32x4 *>(s.scale + k);
+      const bf16x4 h = __builtin_convertvector(v, bf16x4);
+      *reinterpret_cast<bf16x4 *>(s.act + sr * kActStride + k) = h;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s.x_t[(k + j) * kTStride + sr] = h[j];
     }
-    // layer 1
-    f32x4 acc[4][4];
-    zero_acc(acc);
-    mm_units(net->w1, 64, 4, 2, x_s, acc);
+    __syncthreads();
+    const uint32_t on1 = train_layer(s.w1, s.b1, s.act, s.h1_t, wv);
+    const uint32_t on2 = train_layer(s.w2, s.b2, s.act, s.h2_t, wv);
+    {   // output layer: rows 0..5 of one tile
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int u = 16 * mt + 4 * g + r, sm = 16 * t + col;
-          const float pre = acc[mt][t][r] + net->b1[u];
-          const __bf16 h = (__bf16)relu(pre);
-          a1_f[sm * 64 + u] = pre;
-          h1_s[sm * kActStride + u] = h;
-          h1_t[u * kTStride + sm] = h;
-        }
-    // layer 2
-    zero_acc(acc);
-    mm_units(net->w2, 64, 4, 2, h1_s, acc);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int u = 16 * mt + 4 * g + r, sm = 16 * t + col;
-          const float pre = acc[mt][t][r] + net->b2[u];
-          const __bf16 h = (__bf16)relu(pre);
-          a2_f[sm * 64 + u] = pre;
-          h2_s[sm * kActStride + u] = h;
-          h2_t[u * kTStride + sm] = h;
-        }
-    // layer 3 -> z (rows 0..5 of one M tile)
-    zero_acc(acc);
-    mm_units(net->w3, 64, 1, 2, h2_s, acc);
-    if (g < 2)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) z_f[(16 * t + col) * 8 + 4 * g + r] = acc[0][t][r] + net->b3[4 * g + r];
-    // loss and dL/dz of this lane's sample
-    float dz[kNO];
+      for (int kb = 0; kb < 2; ++kb)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds8(s.w3 + col * kTStride + 32 * kb + 8 * g),
+                                                      lds8(s.act + sm * kActStride + 32 * kb + 8 * g),
+                                                      acc, 0, 0, 0);
+      if (g < 2u) *reinterpret_cast<f32x4 *>(s.z + sm * 8 + 4 * g) =
+          acc + *reinterpret_cast<const f32x4 *>(s.b3 + 4 * g);
+    }
+    wave_lds_fence();
+    // loss and dL/dz: lane row g takes dimension g of the lane's sample
     {
-      const float *z = z_f + lane * 8;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const float tgt = valid ? a.target[(size_t)s * 3 + d] : 0.0f;
-        const float mu = a.head.m_max * tanhf(z[d] / a.head.m_max);
-        const float sg = fast_rcp(1.0f + __expf(-z[3 + d]));
-        const float ls = a.head.lo + (a.head.hi - a.head.lo) * sg;
-        const float inv_var = __expf(-2.0f * ls);
-        const float e = tgt - mu;
-        if (valid) loss += 0.5f * e * e * inv_var + ls;
-        const float dmu = -e * inv_var, dls = 1.0f - e * e * inv_var;
-        dz[d] = valid ? dmu * (1.0f - (mu / a.head.m_max) * (mu / a.head.m_max)) : 0.0f;
-        dz[3 + d] = valid ? dls * (a.head.hi - a.head.lo) * sg * (1.0f - sg) : 0.0f;
+      const uint32_t d = g < 3u ? g : 0u;
+      const bool valid = g < 3u && s0 + sm < a.n;
+      const float tgt = valid ? a.target[(size_t)(s0 + sm) * 3u + d] : 0.0f;
+      const float mu = a.head.m_max * tanhf(s.z[sm * 8 + d] / a.head.m_max);
+      const float sg = fast_rcp(1.0f + __expf(-s.z[sm * 8 + 3 + d]));
+      const float ls = a.head.lo + (a.head.hi - a.head.lo) * sg;
+      const float inv_var = __expf(-2.0f * ls);
+      const float e = tgt - mu;
+      if (valid) loss += 0.5f * e * e * inv_var + ls;
+      const float dmu = -e * inv_var, dls = 1.0f - e * e * inv_var;
+      const float zm = valid ? dmu * (1.0f - (mu / a.head.m_max) * (mu / a.head.m_max)) : 0.0f;
+      const float zl = valid ? dls * (a.head.hi - a.head.lo) * sg * (1.0f - sg) : 0.0f;
+      gmu += zm;
+      gls += zl;
+      if (g < 3u) {
+        const __bf16 bm = (__bf16)zm, bl = (__bf16)zl;
+        s.dz_s[sm * 8 + d] = bm;
+        s.dz_s[sm * 8 + 3 + d] = bl;
+        s.dz_t[d * kTStride + sm] = bm;
+        s.dz_t[(3 + d) * kTStride + sm] = bl;
+      } else {
+        s.dz_s[sm * 8 + 6] = s.dz_s[sm * 8 + 7] = (__bf16)0.0f;
       }
     }
-    for (int k = 0; k < 32; ++k) {
-      const __bf16 v = k < kNO ? (__bf16)dz[k < kNO ? k : 0] : (__bf16)0.0f;
-      dz_s[lane * 32 + k] = v;
-      if (k < 16) dz_t[k * kTStride + lane] = v;
+    wave_lds_fence();
+    // delta2 = (W3^T dz) * relu'(a2): K = 32 with outputs 0..7 in lane row 0
+    const bf16x8 zero8 = {};
+    const bf16x8 bz = g == 0u ? lds8(s.dz_s + sm * 8) : zero8;
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const bf16x8 av = g == 0u ? lds8(s.w3t + (16 * mt + col) * 8) : zero8;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bz, acc, 0, 0, 0);
+      const uint32_t u = 16u * mt + 4u * g;
+      f32x4 d;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d[r] = acc[r] * ((on2 >> (4 * mt + r)) & 1u ? 1.0f : 0.0f);
+      gb2[mt] += d;
+      const bf16x4 db = __builtin_convertvector(d, bf16x4);
+      *reinterpret_cast<bf16x4 *>(s.act + sm * kActStride + u) = db;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s.d2_t[(u + r) * kTStride + sm] = db[r];
     }
-    // output-bias gradient: FP32 sum of dz over the chunk's samples
+    wave_lds_fence();
+    // delta1 = (W2^T delta2) * relu'(a1)
+    bf16x8 b2[2];
 #pragma unroll
-    for (int o = 0; o < kNO; ++o) {
-      float v = dz[o];
+    for (int kb = 0; kb < 2; ++kb) b2[kb] = lds8(s.act + sm * kActStride + 32 * kb + 8 * g);
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      gb3[o] += v;
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            lds8(s.w2t + (16 * mt + col) * kTStride + 32 * kb + 8 * g), b2[kb], acc, 0, 0, 0);
+      const uint32_t u = 16u * mt + 4u * g;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float d = acc[r] * ((on1 >> (4 * mt + r)) & 1u ? 1.0f : 0.0f);
+        gb1[mt][r] += d;
+        s.d1_t[(u + r) * kTStride + sm] = (__bf16)d;
+      }
     }
-    // delta2 = (W3^T dz) * relu'(a2)
-    zero_acc(acc);
-    {
-      // K = 32 (6 used): one block; B operand from dz_s rows
-      bf16x8 b[4];
+    __syncthreads();
+    // weight gradients, contracted over the chunk's samples: input units 16 wv + col
 #pragma unroll
-      for (int t = 0; t < 4; ++t) b[t] = lds8(dz_s + (16 * t + col) * 32 + 8 * g);
+    for (int kb = 0; kb < 2; ++kb) {
+      const uint32_t at = 32u * kb + 8u * g;
+      const bf16x8 bx = lds8(s.x_t + sm * kTStride + at), bh1 = lds8(s.h1_t + sm * kTStride + at),
+                   bh2 = lds8(s.h2_t + sm * kTStride + at);
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        const bf16x8 av = *reinterpret_cast<const bf16x8 *>(net->w3t + (16 * mt + col) * 32 + 8 * g);
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[t], acc[mt][t], 0, 0, 0);
+        gw1[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds8(s.d1_t + (16 * mt + col) * kTStride + at),
+                                                          bx, gw1[mt], 0, 0, 0);
+        gw2[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds8(s.d2_t + (16 * mt + col) * kTStride + at),
+                                                          bh1, gw2[mt], 0, 0, 0);
       }
+      gw3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds8(s.dz_t + col * kTStride + at), bh2, gw3, 0, 0, 0);
     }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int u = 16 * mt + 4 * g + r, sm = 16 * t + col;
-          const float d = acc[mt][t][r] * drelu(a2_f[sm * 64 + u]);
-          gb2[mt][r] += d;
-          const __bf16 db = (__bf16)d;
-          d2_s[sm * kActStride + u] = db;
-          d2_t[u * kTStride + sm] = db;
-        }
-    // delta1 = (W2^T delta2) * relu'(a1)
-    zero_acc(acc);
-    mm_units(net->w2t, 64, 4, 2, d2_s, acc);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int u = 16 * mt + 4 * g + r, sm = 16 * t + col;
-          const float d = acc[mt][t][r] * drelu(a1_f[sm * 64 + u]);
-          gb1[mt][r] += d;
-          d1_t[u * kTStride + sm] = (__bf16)d;
-        }
-    // weight gradients, contracted over the chunk's samples
-    mm_samples(d1_t, 4, x_t, 4, gw1);
-    mm_samples(d2_t, 4, h1_t, 4, gw2);
-    mm_samples(dz_t, 1, h2_t, 4, gw3);
   }
 
-  // write this wave's partial gradient in the parameter layout
+  // the block's partial gradient in the parameter layout
   float *out = a.partials + (size_t)blockIdx.x * kPSize;
+  const uint32_t i = 16u * wv + col;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = 16 * mt + 4 * g + r, i = 16 * nt + col;
-        if (i < kNF) out[kPW1 + o * kNF + i] = gw1[mt][nt][r];
-        out[kPW2 + o * kNH + i] = gw2[mt][nt][r];
-        if (mt == 0 && o < kNO) out[kPW3 + o * kNH + i] = gw3[0][nt][r];
-      }
-  // bias partials: sum the per-lane values over the 16 lanes sharing g
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t o = 16u * mt + 4u * g + r;
+      if (i < (uint32_t)kNF) out[kPW1 + o * kNF + i] = gw1[mt][r];
+      out[kPW2 + o * kNH + i] = gw2[mt][r];
+      if (mt == 0 && o < (uint32_t)kNO) out[kPW3 + o * kNH + i] = gw3[r];
+    }
+  // bias and loss partials: over the 16 samples of a wave, then over the waves in order
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -249,20 +281,34 @@ __global__ __launch_bounds__(64) void mlp_grad_kernel(const TrainArgs a) {
         v1 += __shfl_xor(v1, off, 16);
         v2 += __shfl_xor(v2, off, 16);
       }
-      if (col == 0) {
-        out[kPB1 + 16 * mt + 4 * g + r] = v1;
-        out[kPB2 + 16 * mt + 4 * g + r] = v2;
+      if (col == 0u) {
+        s.red1[wv][16 * mt + 4 * g + r] = v1;
+        s.red2[wv][16 * mt + 4 * g + r] = v2;
       }
     }
 #pragma unroll
-  for (int o = 0; o < kNO; ++o)
-    if (lane == o) out[kPB3 + o] = gb3[o];
-  if (lane < kPW1) out[lane] = 0.0f;       // no gradient for the standardisation
-  if (lane + 64 < kPW1) out[lane + 64] = 0.0f;
-  if (lane < kPSize - kPB3 - kNO) out[kPB3 + kNO + lane] = 0.0f;
-  // loss partial
-  for (int off = 32; off > 0; off >>= 1) loss += __shfl_down(loss, off, 64);
-  if (lane == 0) a.loss_partials[blockIdx.x] = loss;
+  for (int off = 8; off > 0; off >>= 1) {
+    gmu += __shfl_xor(gmu, off, 16);
+    gls += __shfl_xor(gls, off, 16);
+  }
+  if (col == 0u && g < 3u) {
+    s.red3[wv][g] = gmu;
+    s.red3[wv][3 + g] = gls;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+  if (lane == 0u) s.red_loss[wv] = loss;
+  __syncthreads();
+  if (tid < 64u) {
+    out[kPB1 + tid] = (s.red1[0][tid] + s.red1[1][tid]) + (s.red1[2][tid] + s.red1[3][tid]);
+    out[kPB2 + tid] = (s.red2[0][tid] + s.red2[1][tid]) + (s.red2[2][tid] + s.red2[3][tid]);
+    if (tid < (uint32_t)kNO)
+      out[kPB3 + tid] = (s.red3[0][tid] + s.red3[1][tid]) + (s.red3[2][tid] + s.red3[3][tid]);
+    if (tid == 0u)
+      a.loss_partials[blockIdx.x] = (s.red_loss[0] + s.red_loss[1]) + (s.red_loss[2] + s.red_loss[3]);
+  }
+  if (tid < (uint32_t)kPW1) out[tid] = 0.0f;   // no gradient for the standardisation
+  if (tid < (uint32_t)(kPSize - kPB3 - kNO)) out[kPB3 + kNO + tid] = 0.0f;
 }
 
 struct AdamArgs {
@@ -279,36 +325,48 @@ struct AdamArgs {
 
 // Mean gradient over the batch and the Adam step on the FP32 master
 // parameters (standardisation constants untouched).  A block covers 64
-// parameters; its four waves sum the partials of waves q, q+4, q+8, ... (q the
-// wave in the block), eight loads in flight, and the four sums are combined
-// in a fixed order: the result does not depend on timing.
+// parameters; its 16 waves sum the partials of blocks q, q+16, q+32, ... (q the
+// wave in the block), eight loads in flight, and the 16 sums are combined in a
+// fixed order: the result does not depend on timing.  Bound by the latency of
+// its loads: 128 partials are one round of eight loads per wave (four rounds
+// with four waves, and a serial sum of the losses, took 9.2 us).
 constexpr uint32_t kAdamParamsPerBlock = 64;
+constexpr uint32_t kAdamWaves = 16;
 
-__global__ __launch_bounds__(256) void mlp_adam_kernel(const AdamArgs a) {
-  __shared__ float s_part[4][kAdamParamsPerBlock];
+__global__ __launch_bounds__(64 * kAdamWaves) void mlp_adam_kernel(const AdamArgs a) {
+  __shared__ float s_part[kAdamWaves][kAdamParamsPerBlock];
   const uint32_t lane = threadIdx.x & 63u, q = threadIdx.x >> 6;
   const uint32_t p = blockIdx.x * kAdamParamsPerBlock + lane;
   float gsum = 0.0f;
   if (p < (uint32_t)kPSize) {
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    uint32_t w = q;
-    for (; w + 28u < a.waves; w += 32u) {
+    for (uint32_t w = q; w < a.waves; w += 8u * kAdamWaves) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc[u] += a.partials[(size_t)(w + 4u * u) * kPSize + p];
+      for (uint32_t u = 0; u < 8u; ++u) {
+        const uint32_t ww = w + kAdamWaves * u;
+        if (ww < a.waves) acc[u] += a.partials[(size_t)ww * kPSize + p];
+      }
     }
-    for (; w < a.waves; w += 4u) acc[0] += a.partials[(size_t)w * kPSize + p];
     gsum = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   }
   s_part[q][lane] = gsum;
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 64 && a.loss_out) {
+  if (blockIdx.x == 0 && q == 1u && a.loss_out) {
     float l = 0.0f;
-    for (uint32_t w = 0; w < a.waves; ++w) l += a.loss_partials[w];
-    *a.loss_out = l / (float)a.n;
+    for (uint32_t w = lane; w < a.waves; w += 64u) l += a.loss_partials[w];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (lane == 0u) *a.loss_out = l / (float)a.n;
   }
   if (q != 0 || p >= (uint32_t)kPSize) return;
-  const float grad = ((s_part[0][lane] + s_part[1][lane]) + (s_part[2][lane] + s_part[3][lane])) /
-                     (float)a.n;
+  float part[kAdamWaves];
+#pragma unroll
+  for (uint32_t w = 0; w < kAdamWaves; ++w) part[w] = s_part[w][lane];
+#pragma unroll
+  for (uint32_t half = kAdamWaves / 2u; half > 0u; half >>= 1)
+#pragma unroll
+    for (uint32_t w = 0; w < half; ++w) part[w] += part[w + half];
+  const float grad = part[0] / (float)a.n;
   if (a.grad_out) a.grad_out[p] = grad;
   if (!a.apply || p < (uint32_t)kPW1 || p >= (uint32_t)(kPB3 + kNO)) return;
   const float m = a.beta1 * a.m[p] + (1.0f - a.beta1) * grad;

@@ -71,6 +71,32 @@ def test_gradient_matches_bf16_oracle(orc, n, max_waves):
     assert np.all(grad[:120] == 0.0) and np.all(grad[8574:] == 0.0)
 
 
+@pytest.mark.parametrize("n,max_waves,offset", [(1, 0, 0), (63, 0, 1), (64, 0, 0), (129, 1, 1),
+                                                (200, 3, 2)])
+def test_gradient_chunk_edges_and_unaligned_input(orc, n, max_waves, offset):
+    """Chunks of 64 that are full, ragged or shared by one block, with features and parameters on a
+    16-byte boundary and `offset` floats past one (vector and scalar loads): the oracle's envelope."""
+    from paper_1711_03828_amd import soma as C
+    g = np.random.default_rng(100 + n)
+    params = synth.mlp_params(33, weight_gain=1.2, out_gain=0.5,
+                              shift=g.standard_normal(60) * 0.1, scale=1 + 0.2 * g.random(60))
+    f = (g.standard_normal((n, 60)) * 1.5).astype(np.float32)
+    t = (g.standard_normal((n, 3)) * 0.3).astype(np.float32)
+    fd = torch.empty(n * 60 + offset, device="cuda")[offset:].view(n, 60)
+    fd.copy_(torch.from_numpy(f))
+    p = torch.empty(8576 + offset, device="cuda")[offset:]
+    p.copy_(torch.from_numpy(params))
+    flush(n, max_waves, offset)
+    grad, loss = _step(C, p, fd, torch.from_numpy(t).cuda(), max_waves=max_waves)
+    loss_o, grad_o, bound, _, _ = orc.nll_batch_envelope(params, f, t, **HEAD)
+    assert abs(loss - loss_o) <= 2e-3 * abs(loss_o)
+    for name, size in GROUPS:
+        sl = slice(synth.MLP_LAYOUT[name], synth.MLP_LAYOUT[name] + size)
+        d = np.abs(grad[sl] - grad_o[sl])
+        flush(name, "max |dg|/bound", (d / np.maximum(bound[sl], 1e-300)).max())
+        assert (d <= bound[sl]).all(), (name, int(np.argmax(d - bound[sl])))
+
+
 def test_adam_step_formula():
     from paper_1711_03828_amd import soma as C
     g = np.random.default_rng(3)
