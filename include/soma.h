@@ -302,8 +302,8 @@ int32_t soma_type_counts(soma_system *sys, uint64_t *out, uint32_t n_out, void *
 /* Launch shape of the SET sweeps (local, smart-MC, bond-Gibbs and mixed
  * moves): 0 (default) runs one wave per tile of chains; blocks > 0, when
  * fewer than the tile groups, runs that many persistent blocks whose waves
- * draw their tiles from per-XCD counters in the workspace (zeroed by a small
- * kernel before each launch, a graph node).  Results are identical for every
+ * draw their tiles from per-XCD counters in the workspace (zero between
+ * launches: the last block of a launch clears them).  Results are identical for every
  * value (they depend only on seed, sweep and chain).  A multiple of 8 keeps
  * each XCD on one contiguous range of chains.  Capture graphs again after a
  * change. */

@@ -105,7 +105,7 @@ int32_t derive(const soma_config *c, Derived *d) {
   d->n_cells = n_cells;
   d->n_free = n_cells;
   {
-    const uint64_t fb = (n_cells + 4095) / 4096;
+    const uint64_t fb = (n_cells + soma::kFieldBlockCells - 1) / soma::kFieldBlockCells;
     d->field_blocks = (uint32_t)(fb < soma::kFieldBlocks ? fb : soma::kFieldBlocks);
   }
   d->n_beads = d->n_chains = d->n_a_total = d->obs_blocks = 0;
@@ -266,11 +266,15 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.ext = d.ext;
   a.forbid = d.forbid;
   a.form = d.form;
+  a.ctr = nullptr;
+  a.ctr_by = 0;
   return a;
 }
 
+// ctr, ctr_by: sweep counter that this refresh advances (the last one of a call).
 int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float *omega,
-                     soma::FieldPartial *partials, hipStream_t s, float *halo = nullptr) {
+                     soma::FieldPartial *partials, hipStream_t s, float *halo = nullptr,
+                     uint32_t *ctr = nullptr, uint32_t ctr_by = 0) {
   const uint32_t blocks = d.field_blocks;
   if (d.n_types > 2) {   // no halo copy, external fields or walls with more than two types
     soma::MultiFieldArgs m;
@@ -286,6 +290,8 @@ int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float
     m.kappa_n_d = (double)c->kappa_n;
     std::memcpy(m.chi, d.chi_m, sizeof m.chi);
     m.partials = partials;
+    m.ctr = ctr;
+    m.ctr_by = ctr_by;
     const bool c64 = c->count_width == 32;
     switch (d.n_types) {
 #define SOMA_MULTI_CASE(NT)                                                                       \
@@ -306,7 +312,9 @@ int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float
     LAUNCH_TRY();
     return SOMA_OK;
   }
-  const soma::FieldArgs a = field_args(c, d, counts, omega, partials, halo);
+  soma::FieldArgs a = field_args(c, d, counts, omega, partials, halo);
+  a.ctr = ctr;
+  a.ctr_by = ctr_by;
   // counts of 64 MiB and more are read with the non-temporal hint (measured on
   // the 134M-bead melt: 3.7% off the SCMF cycle, the next sweep's field
   // gathers hitting the last-level cache more often)
@@ -637,10 +645,8 @@ int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t of
     const uint64_t chains_per_block = (uint64_t)(threads / 64u) * a.chains_per_wave;
     uint64_t blocks = (a.n_sub + chains_per_block - 1) / chains_per_block;
     if (sys->sweep_blocks && sys->sweep_blocks < blocks) {
-      blocks = sys->sweep_blocks;   // persistent: tiles from counters zeroed here
+      blocks = sys->sweep_blocks;   // persistent: tiles from counters, zero between launches
       a.queue = reinterpret_cast<uint32_t *>(sys->ws + sys->d.off_queue);
-      hipLaunchKernelGGL(soma::queue_reset_kernel, dim3(1), dim3(256), 0, s, a.queue);
-      LAUNCH_TRY();
     }
     const bool v2 = species_vec2(sys, sp);
     const dim3 grid((uint32_t)blocks), block(threads);
@@ -694,22 +700,26 @@ int32_t launch_grad(soma_system *sys, hipStream_t s) {
 }
 
 // Stage 1 of the cycle: fields from the counts, then the gradient field if kept.
-int32_t refresh_fields(soma_system *sys, hipStream_t s) {
+// advance > 0: the sweep counter moves on by that many sweeps.
+int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0) {
   int32_t r = launch_field(&sys->cfg, sys->d, sys->buf.counts, sys->buf.omega, sys->fpart(), s,
-                           sys->halo());
+                           sys->halo(), advance ? sys->sweep_ctr() : nullptr, advance);
   if (!r && sys->grad) r = launch_grad(sys, s);
   return r;
 }
 
-// One SCMF cycle with sweep offset `off`: for each of the system's k chain
-// subsets, its sweep and then the field refresh (k = 1: sweep, refresh).
-int32_t enqueue_cycle(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t off) {
+// n SCMF cycles: for each of the system's k chain subsets, its sweep and then
+// the field refresh (k = 1: sweep, refresh).  The last refresh advances the
+// device sweep counter by n (a launch of its own took 1.4 us of a small melt's
+// 12 us cycle, and the gap before it).
+int32_t enqueue_cycles(soma_system *sys, uint32_t n, uint32_t kind, hipStream_t s) {
   const uint32_t k = sys->substeps;
-  for (uint32_t j = 0; j < k; ++j) {
-    int32_t r = launch_sweep(sys, kind, s, off, k, j);
-    if (!r) r = refresh_fields(sys, s);
-    if (r) return r;
-  }
+  for (uint32_t i = 0; i < n; ++i)
+    for (uint32_t j = 0; j < k; ++j) {
+      int32_t r = launch_sweep(sys, kind, s, i, k, j);
+      if (!r) r = refresh_fields(sys, s, i + 1u == n && j + 1u == k ? n : 0u);
+      if (r) return r;
+    }
   return SOMA_OK;
 }
 
@@ -839,11 +849,7 @@ int32_t soma_capture_cycle(soma_system *sys, uint32_t cycles, uint32_t move_kind
   int32_t rc = check_kind(sys, move_kind);
   if (rc) return rc;
   return capture_graph(sys->graph, cycles, move_kind, [&](hipStream_t cs) -> int32_t {
-    for (uint32_t i = 0; i < cycles; ++i) {
-      const int32_t r = enqueue_cycle(sys, move_kind, cs, i);
-      if (r) return r;
-    }
-    return launch_counter(sys->sweep_ctr(), cycles, 0, 0, cs);
+    return enqueue_cycles(sys, cycles, move_kind, cs);
   });
 }
 
@@ -859,11 +865,7 @@ int32_t soma_cycle(soma_system *sys, uint32_t n_cycles, uint32_t move_kind, void
   int32_t rc = check_kind(sys, move_kind);
   if (rc || n_cycles == 0) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  for (uint32_t i = 0; i < n_cycles; ++i) {
-    rc = enqueue_cycle(sys, move_kind, s, i);
-    if (rc) return rc;
-  }
-  rc = launch_counter(sys->sweep_ctr(), n_cycles, 0, 0, s);
+  rc = enqueue_cycles(sys, n_cycles, move_kind, s);
   if (rc) return rc;
   sys->count_sweeps(move_kind, n_cycles);
   return SOMA_OK;
@@ -1914,15 +1916,16 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   return SOMA_OK;
 }
 
-int32_t launch_batch_field(soma_batch *b, hipStream_t s) {
+// advance > 0: every system's sweep counter moves on by that many sweeps.
+int32_t launch_batch_field(soma_batch *b, hipStream_t s, uint32_t advance = 0) {
   const uint32_t n_sys = (uint32_t)b->sys.size();
   const dim3 grid(b->fb_first[n_sys]);
   if (b->c64)
     hipLaunchKernelGGL(soma::batched_field_kernel<true>, grid, dim3(256), 0, s, b->d_fargs,
-                       b->d_fb_first, n_sys);
+                       b->d_fb_first, n_sys, b->d_ctrs, advance);
   else
     hipLaunchKernelGGL(soma::batched_field_kernel<false>, grid, dim3(256), 0, s, b->d_fargs,
-                       b->d_fb_first, n_sys);
+                       b->d_fb_first, n_sys, b->d_ctrs, advance);
   LAUNCH_TRY();
   for (soma_system *x : b->sys)   // gradient fields of the systems that keep one
     if (x->grad) {
@@ -1937,6 +1940,17 @@ int32_t launch_batch_counter(soma_batch *b, uint32_t by, hipStream_t s) {
   hipLaunchKernelGGL(soma::sweep_counter_kernel, dim3((n_sys + 63) / 64), dim3(64), 0, s,
                      b->d_ctrs, n_sys, by, 0u, 0u);
   LAUNCH_TRY();
+  return SOMA_OK;
+}
+
+// n cycles of the whole batch; the last refresh advances the sweep counters.
+int32_t enqueue_batch_cycles(soma_batch *b, uint32_t n, uint32_t kind, hipStream_t s) {
+  for (uint32_t i = 0; i < n; ++i)
+    for (uint32_t j = 0; j < b->substeps; ++j) {
+      int32_t r = launch_batch_sweep(b, kind, s, i, j);
+      if (!r) r = launch_batch_field(b, s, i + 1u == n && j + 1u == b->substeps ? n : 0u);
+      if (r) return r;
+    }
   return SOMA_OK;
 }
 
@@ -2108,13 +2122,7 @@ int32_t soma_batch_capture_cycle(soma_batch *b, uint32_t cycles, uint32_t move_k
   const int32_t rc = batch_check_kind(b, move_kind);
   if (rc) return rc;
   return capture_graph(b->graph, cycles, move_kind, [&](hipStream_t cs) -> int32_t {
-    for (uint32_t i = 0; i < cycles; ++i)
-      for (uint32_t j = 0; j < b->substeps; ++j) {
-        int32_t r = launch_batch_sweep(b, move_kind, cs, i, j);
-        if (!r) r = launch_batch_field(b, cs);
-        if (r) return r;
-      }
-    return launch_batch_counter(b, cycles, cs);
+    return enqueue_batch_cycles(b, cycles, move_kind, cs);
   });
 }
 
@@ -2136,13 +2144,7 @@ int32_t soma_batch_cycle(soma_batch *b, uint32_t n_cycles, uint32_t move_kind, v
   int32_t rc = batch_check_kind(b, move_kind);
   if (rc || n_cycles == 0) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  for (uint32_t i = 0; i < n_cycles; ++i)
-    for (uint32_t j = 0; j < b->substeps; ++j) {
-      rc = launch_batch_sweep(b, move_kind, s, i, j);
-      if (!rc) rc = launch_batch_field(b, s);
-      if (rc) return rc;
-    }
-  rc = launch_batch_counter(b, n_cycles, s);
+  rc = enqueue_batch_cycles(b, n_cycles, move_kind, s);
   if (rc) return rc;
   batch_count(b, move_kind, n_cycles);
   return SOMA_OK;

@@ -61,8 +61,8 @@ struct SweepArgs {
   // energy added to every move that changes cell (0: the quasi-instantaneous
   // field alone); see soma_set_self_term
   float self_term;
-  // persistent local sweeps: kQueueParts x kQueueSub tile counters, kQueueStride
-  // words apart, zeroed before the launch (null: the static tile order)
+  // persistent sweeps: kQueueParts x kQueueSub tile counters, kQueueStride words
+  // apart, zero at every launch (null: the static tile order)
   uint32_t *queue;
   // waves per block of the launch (blockDim.x / 64), as a kernel argument: it
   // loads with the other arguments, while the block size itself is a 16-bit
@@ -79,11 +79,21 @@ struct SweepArgs {
 
 constexpr uint32_t kQueueParts = 8u, kQueueSub = 16u, kQueueStride = 32u;
 
-// Zeroes the tile counters of a persistent sweep (a kernel, not a memset, so
-// that it can sit in a captured graph).
-__global__ __launch_bounds__(256) void queue_reset_kernel(uint32_t *q) {
+// End of a persistent sweep's block, after its waves have drawn their last tile:
+// the last block to arrive zeroes the tile counters for the next launch (the
+// workspace starts zeroed), where a kernel before every sweep would cost a launch
+// (4.7 us before each 113 us sweep of an eighth of a 262,144-chain melt).  Every
+// draw of a block has returned before its arrival, so none can follow the zeroing.
+// The arrivals are counted in the second word of the first counter's line.
+__device__ __forceinline__ void queue_finish(uint32_t *q) {
+  __shared__ uint32_t s_last;
+  __syncthreads();
+  if (threadIdx.x == 0u) s_last = atomicAdd(q + 1, 1u) + 1u == gridDim.x ? 1u : 0u;
+  __syncthreads();
+  if (s_last == 0u) return;
   for (uint32_t i = threadIdx.x; i < kQueueParts * kQueueSub; i += blockDim.x)
     q[i * kQueueStride] = 0u;
+  if (threadIdx.x == 0u) q[1] = 0u;
 }
 
 // Tiles of a persistent SET sweep (PERSIST instances; SweepArgs::queue set).  The tiles (one
@@ -445,6 +455,7 @@ void mc_sweep_local_kernel(const SweepArgs a_in) {
     t = tile_of(it, vn);
   }
   finish_block(a, n_acc);
+  queue_finish(a.queue);
 }
 
 // Central-difference gradient of one field plane at cell (cx,cy,cz); the
@@ -654,6 +665,7 @@ __device__ __forceinline__ void smc_tiles(const SweepArgs &a) {
     t = tile_of(it, vn);
   }
   finish_block(a, n_acc);
+  queue_finish(a.queue);
 }
 
 // PERSIST: the persistent-grid instance (SweepArgs::queue set); its loop over
@@ -880,6 +892,7 @@ __global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_i
     t = tile_of(it, vn);
   }
   mixed_finish(a, mx, cnt);
+  queue_finish(a.queue);
 }
 
 }  // namespace soma
