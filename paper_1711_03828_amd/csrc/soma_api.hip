@@ -80,6 +80,14 @@ struct Derived {
   uint64_t off_queue = 0;   // tile counters of persistent local sweeps
 };
 
+// Blocks of the observables kernel for a species: four waves of 64 / lanes-per-chain
+// chains each, at most kObsMaxBlocks (which then loop).
+uint32_t obs_lanes(const soma_species &sp) { return (sp.n + soma::kObsBeads - 1u) / soma::kObsBeads; }
+uint32_t obs_blocks(const soma_species &sp) {
+  const uint32_t per = 4u * (64u / obs_lanes(sp));
+  return std::min((sp.n_chains + per - 1u) / per, soma::kObsMaxBlocks);
+}
+
 int32_t derive(const soma_config *c, Derived *d) {
   if (!c) return fail(SOMA_E_INVAL, "config is NULL");
   if (c->nx == 0 || c->ny == 0 || c->nz == 0)
@@ -123,7 +131,7 @@ int32_t derive(const soma_config *c, Derived *d) {
     d->n_beads += (uint64_t)sp.n_chains * sp.n;
     d->n_chains += sp.n_chains;
     d->n_a_total += (uint64_t)sp.n_chains * sp.n_a;
-    d->obs_blocks += (sp.n_chains + 255u) / 256u;
+    d->obs_blocks += obs_blocks(sp);
   }
   if (d->n_chains >= (1ull << 32)) return fail(SOMA_E_UNSUPPORTED, "2^32 or more chains");
   if (d->n_beads == 0) return fail(SOMA_E_INVAL, "no beads");
@@ -135,9 +143,9 @@ int32_t derive(const soma_config *c, Derived *d) {
   d->off_att = align_up(d->off_acc + 4ull * soma::kAccSlots * 8ull);
   d->off_net = align_up(d->off_att + soma::kAccSlots * 8ull);
   d->off_fpart = align_up(d->off_net + SOMA_MAX_SPECIES * align_up(sizeof(soma::NetDev)));
-  d->off_totals = align_up(d->off_fpart + soma::kFieldBlocks * sizeof(soma::FieldPartial));
+  d->off_totals = align_up(d->off_fpart + sizeof(soma::FieldPartials));
   d->off_opart = align_up(d->off_totals + sizeof(soma::Totals));
-  d->off_arch = align_up(d->off_opart + (d->obs_blocks ? d->obs_blocks : 1) * sizeof(soma::ObsPartial));
+  d->off_arch = align_up(d->off_opart + d->obs_blocks * soma::kObsSums * 8ull);
   d->off_tcount = align_up(d->off_arch + SOMA_MAX_SPECIES * align_up(sizeof(soma::ArchDev)));
   d->off_halo = align_up(d->off_tcount + 8ull * soma::kFieldBlocks * soma::kMaxTypes);
   // the learned proposal reads its 27-cell neighbourhoods from a copy of the
@@ -247,7 +255,7 @@ int32_t launch_hist(const soma_config *c, const Derived &d, const float *pos, vo
 }
 
 soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts, float *omega,
-                           soma::FieldPartial *partials, float *halo = nullptr) {
+                           soma::FieldPartials *partials, float *halo = nullptr) {
   soma::FieldArgs a;
   a.counts = counts;
   a.omega = omega;
@@ -273,7 +281,7 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
 
 // ctr, ctr_by: sweep counter that this refresh advances (the last one of a call).
 int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float *omega,
-                     soma::FieldPartial *partials, hipStream_t s, float *halo = nullptr,
+                     soma::FieldPartials *partials, hipStream_t s, float *halo = nullptr,
                      uint32_t *ctr = nullptr, uint32_t ctr_by = 0) {
   const uint32_t blocks = d.field_blocks;
   if (d.n_types > 2) {   // no halo copy, external fields or walls with more than two types
@@ -375,7 +383,59 @@ struct CycleGraph {
   }
 };
 
+// Pinned host memory that the observables' totals are written to directly: a copy
+// to pageable memory costs a kernel and its own wait (20 us of a 73 us call).
+// kHostSlots records shared by all systems, allocated with the first call that
+// wants one and freed with the last system; a call takes a free slot for its own
+// duration, so calls on several threads and streams never share one.
+namespace {
+constexpr uint32_t kHostSlots = 32u;
+struct HostPool {
+  std::mutex mu;
+  soma::Totals *base = nullptr;
+  uint32_t used = 0, systems = 0;
+} g_host;
+
+struct HostSlot {
+  soma::Totals *ptr = nullptr;
+  uint32_t index = 0;
+  HostSlot() {
+    std::lock_guard<std::mutex> lock(g_host.mu);
+    if (!g_host.base) {
+      void *p = nullptr;
+      if (hipHostMalloc(&p, kHostSlots * sizeof(soma::Totals), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+      }
+      g_host.base = reinterpret_cast<soma::Totals *>(p);
+    }
+    if (g_host.used == 0xFFFFFFFFu) return;
+    index = (uint32_t)__builtin_ctz(~g_host.used);
+    g_host.used |= 1u << index;
+    ptr = g_host.base + index;
+  }
+  ~HostSlot() {
+    if (!ptr) return;
+    std::lock_guard<std::mutex> lock(g_host.mu);
+    g_host.used &= ~(1u << index);
+  }
+  HostSlot(const HostSlot &) = delete;
+  HostSlot &operator=(const HostSlot &) = delete;
+};
+
+void host_pool_system(bool created) {
+  std::lock_guard<std::mutex> lock(g_host.mu);
+  if (created) {
+    ++g_host.systems;
+  } else if (--g_host.systems == 0 && g_host.base) {
+    (void)hipHostFree(g_host.base);
+    g_host.base = nullptr;
+  }
+}
+}  // namespace
+
 struct soma_system {
+  soma_system() { host_pool_system(true); }
   soma_config cfg;
   soma_buffers buf;
   Derived d;
@@ -397,7 +457,10 @@ struct soma_system {
   float4 *grad = nullptr;     // optional gradient field (caller-owned), see soma_set_grad_field
   unsigned char *ws = nullptr;
   CycleGraph graph;
-  ~soma_system() { graph.release(); }
+  ~soma_system() {
+    graph.release();
+    host_pool_system(false);
+  }
   uint32_t *err() { return reinterpret_cast<uint32_t *>(ws + d.off_err); }
   uint32_t *sweep_ctr() { return reinterpret_cast<uint32_t *>(ws + d.off_err) + 1; }
   void count_sweeps(uint32_t kind, uint64_t n) {
@@ -406,9 +469,9 @@ struct soma_system {
     else attempted[kind] += n * d.n_beads;
   }
   unsigned long long *acc() { return reinterpret_cast<unsigned long long *>(ws + d.off_acc); }
-  soma::FieldPartial *fpart() { return reinterpret_cast<soma::FieldPartial *>(ws + d.off_fpart); }
+  soma::FieldPartials *fpart() { return reinterpret_cast<soma::FieldPartials *>(ws + d.off_fpart); }
   soma::Totals *totals() { return reinterpret_cast<soma::Totals *>(ws + d.off_totals); }
-  soma::ObsPartial *opart() { return reinterpret_cast<soma::ObsPartial *>(ws + d.off_opart); }
+  double *opart() { return reinterpret_cast<double *>(ws + d.off_opart); }
   float *halo() { return d.halo_plane ? reinterpret_cast<float *>(ws + d.off_halo) : nullptr; }
   unsigned long long *att() { return reinterpret_cast<unsigned long long *>(ws + d.off_att); }
   soma::ArchDev *arch(uint32_t sp) {
@@ -1220,6 +1283,9 @@ int32_t soma_observables(soma_system *sys, soma_obs *out, void *stream) {
   if (!sys || !out) return fail(SOMA_E_INVAL, "system or out is NULL");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const soma_config *c = &sys->cfg;
+  soma::Totals t;
+  HostSlot slot;   // the totals arrive in pinned memory, or by a copy where there is no slot
+  soma::Totals *const dst = slot.ptr ? slot.ptr : sys->totals();
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
     const soma_species &S = c->species[sp];
     if (!S.n_chains) continue;
@@ -1229,25 +1295,27 @@ int32_t soma_observables(soma_system *sys, soma_obs *out, void *stream) {
     a.n_chains = S.n_chains;
     a.n = S.n;
     a.n_a = S.n_a;
-    a.seg = 1;
-    while (a.seg < S.n && a.seg < 64) a.seg <<= 1;
+    a.lpc = obs_lanes(S);
     a.inv_n = 1.0 / (double)S.n;
     a.half_k0 = 0.5 * (double)S.k0;
     a.inv_nref = 1.0 / (double)c->n_ref;
     a.grid = sys->grid;
     a.partials = sys->opart() + sys->d.obs_block_off[sp];
+    a.plane = (uint32_t)sys->d.obs_blocks;
     a.arch = sys->d.arch[sp];
     a.err = sys->err();
-    hipLaunchKernelGGL(soma::chain_obs_kernel, dim3((S.n_chains + 255) / 256), dim3(256), 0, s, a);
+    const dim3 grid(obs_blocks(S));
+    if (a.arch) hipLaunchKernelGGL(soma::chain_obs_kernel<true>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(soma::chain_obs_kernel<false>, grid, dim3(256), 0, s, a);
     LAUNCH_TRY();
   }
-  hipLaunchKernelGGL(soma::reduce_totals_kernel, dim3(1), dim3(256), 0, s, sys->opart(),
+  hipLaunchKernelGGL(soma::reduce_totals_kernel, dim3(1), dim3(64 * soma::kTotalsWaves), 0, s, sys->opart(),
                      (uint32_t)sys->d.obs_blocks, sys->fpart(), sys->d.field_blocks, sys->acc(),
-                     sys->att(), sys->err(), sys->totals());
+                     sys->att(), sys->err(), dst);
   LAUNCH_TRY();
-  soma::Totals t;
-  HIP_TRY(hipMemcpyAsync(&t, sys->totals(), sizeof t, hipMemcpyDeviceToHost, s));
+  if (!slot.ptr) HIP_TRY(hipMemcpyAsync(&t, dst, sizeof t, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  if (slot.ptr) t = *slot.ptr;
   std::memset(out, 0, sizeof *out);
   out->sweeps = sys->sweep;
   out->n_beads = sys->d.n_beads;

@@ -19,6 +19,13 @@ constexpr float kMaxCoord = 4194304.0f;  // 2^22: cell arithmetic stays exact be
 // selects between vectors never go through private memory).
 typedef float F3 __attribute__((ext_vector_type(3)));
 
+// Orders the LDS accesses of one wave's lanes (a wave's LDS operations execute
+// in issue order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 struct Rand4 {
   uint32_t x, y, z, w;
 };

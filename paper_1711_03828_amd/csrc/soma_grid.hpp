@@ -13,10 +13,11 @@ constexpr uint32_t kFieldBlocks = 1024u;  // largest grid of the field kernel
 // (24^3 cells: 14 blocks and 3.1 us, against 4 blocks of four rounds and 5.5 us).
 constexpr uint32_t kFieldBlockCells = 1024u;
 
-struct FieldPartial {
-  unsigned long long sum_a, sum_b;
-  double h_nb;
-  double pad;
+// Per-block sums of the last field refresh, one array per quantity (their
+// reduction then reads whole lines).
+struct FieldPartials {
+  unsigned long long sum_a[kFieldBlocks], sum_b[kFieldBlocks];
+  double h_nb[kFieldBlocks];
 };
 
 // ---------------------------------------------------------------------------
@@ -92,7 +93,7 @@ struct FieldArgs {
   uint32_t n_cells;
   float inv_rho, chi_n, kappa_n;
   double inv_rho_d, chi_n_d, kappa_n_d;
-  FieldPartial *partials;  // may be null
+  FieldPartials *partials;  // may be null
   int clear;
   // optional copy of the fields with one periodic halo cell at each end of every
   // x row: [2][nz*ny][nx + 2] (null: not kept)
@@ -316,12 +317,9 @@ __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uin
   if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    FieldPartial p;
-    p.sum_a = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    p.sum_b = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-    p.h_nb = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
-    p.pad = 0.0;
-    a.partials[blk] = p;
+    a.partials->sum_a[blk] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
+    a.partials->sum_b[blk] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
+    a.partials->h_nb[blk] = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
   }
 }
 
@@ -352,7 +350,7 @@ struct MultiFieldArgs {
   float inv_rho, kappa_n;
   double inv_rho_d, kappa_n_d;
   float chi[kMaxTypes * kMaxTypes];   // chi_ik N at [i * kMaxTypes + k]
-  FieldPartial *partials;              // may be null
+  FieldPartials *partials;             // may be null
   uint32_t *ctr;                       // as in FieldArgs
   uint32_t ctr_by;
 };
@@ -503,12 +501,9 @@ __global__ __launch_bounds__(256) void field_multi_kernel(const MultiFieldArgs a
   if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    FieldPartial p;
-    p.sum_a = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    p.sum_b = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-    p.h_nb = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
-    p.pad = 0.0;
-    a.partials[blockIdx.x] = p;
+    a.partials->sum_a[blockIdx.x] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
+    a.partials->sum_b[blockIdx.x] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
+    a.partials->h_nb[blockIdx.x] = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
   }
 }
 

@@ -41,13 +41,6 @@ __device__ __forceinline__ f32x4 load_f4(const float *p, uint32_t vec4) {
   return f32x4{p[0], p[1], p[2], p[3]};
 }
 
-// Orders the LDS accesses of one wave's lanes (a wave's LDS operations execute
-// in issue order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The weights of a block as BF16 tiles: W1 (inputs 60..63 zero), W2, W2
 // transposed, W3 (rows >= 6 zero) and W3 transposed ([hidden][8], outputs >= 6
 // zero), with the FP32 standardisation and biases.

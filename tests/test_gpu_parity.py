@@ -252,6 +252,57 @@ def test_observables_match_oracle(C, orc):
     assert obs.n_beads == 32768 and obs.n_chains == 1024 and obs.sweeps == 0
 
 
+@pytest.mark.parametrize("lengths,chains", [((1, 2, 3, 4, 5, 8, 31, 128), 70), ((4, 127, 63), 300000)])
+def test_observables_chain_lengths(C, orc, lengths, chains):
+    """Chains that end inside, at and past a lane's beads, species that start at odd beads, and more
+    chains than one pass of the grid takes; FP64 sums within 1e-9 of the oracle's."""
+    from paper_1711_03828_amd.melt import Melt
+    counts = [max(1, chains // n ** 2) if n > 8 else chains for n in lengths]
+    w = synth.Workload("lengths", (14, 9, 11),
+                       tuple(synth.SpeciesSpec(c, n, n // 3) for c, n in zip(counts, lengths)),
+                       6.0, 16, 20.0, 50.0, 32)
+    pos = walks_for(w, 47)
+    m = Melt(device_config(w), positions=torch.from_numpy(pos))
+    omega = m.omega.cpu().numpy()
+    flush(lengths, chains)
+    obs = m.observables()
+    tot, at = np.zeros(4), 0
+    for c, n in zip(counts, lengths):
+        part = pos[at:at + c * n]
+        at += c * n
+        re2, rg2, b2 = orc.chain_observables(part, c, n)
+        tot += (re2.sum(), rg2.sum(), b2.sum(),
+                orc.field_energy(part, Species(c, n, n // 3), omega, w.grid, w.n_ref))
+    got = (obs.re2_sum, obs.rg2_sum, obs.b2_sum, obs.e_field)
+    np.testing.assert_allclose(got, tot, rtol=1e-9)
+    assert obs.counts_conserved == 1
+
+
+def test_observables_from_several_threads(C):
+    """Concurrent calls on systems and streams of their own give what a lone call gives."""
+    import threading
+
+    from paper_1711_03828_amd.melt import Melt
+    melts = [Melt(device_config(synth.scaled(synth.C1_SMALL, 200 + 50 * i, (12, 12, 12)), seed=i))
+             for i in range(4)]
+    torch.cuda.synchronize()
+    key = lambda o: (o.re2_sum, o.rg2_sum, o.b2_sum, o.e_field, o.h_nb, o.count_a)
+    alone = [key(m.observables()) for m in melts]
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        for _ in range(25):
+            if key(melts[i].observables(stream=stream)) != alone[i]:
+                wrong.append(i)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
 def test_resume_is_bit_exact(C):
     from paper_1711_03828_amd.melt import Melt
     w = synth.C1_SMALL
