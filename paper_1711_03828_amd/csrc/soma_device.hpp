@@ -54,14 +54,16 @@ __device__ __forceinline__ Rand4 philox(uint32_t c0, uint32_t c1, uint32_t c2,
 
 // u = (2k+1) 2^-24 from the top 23 bits k: exact in FP32, in (0,1), symmetric.
 // Built from the bit pattern 1 + k 2^-23 of [1,2): (f - 1) + 2^-24, both exact.
+// One v_alignbit_b32 shifts the exponent in on top of the 23 bits.
 __device__ __forceinline__ float uniform01(uint32_t x) {
-  const float f = __uint_as_float((x >> 9) | 0x3F800000u);
+  const float f = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, x, 9u));
   return (f - 1.0f) + 0x1p-24f;
 }
-// v = 2u - 1 = (2f - 3) + 2^-23 in (-1,1), both steps exact.
+// v = 2u - 1 = (g - 3) + 2^-23 in (-1,1) with g = 2 + k 2^-22 of [2,4), both
+// steps exact.
 __device__ __forceinline__ float uniform11(uint32_t x) {
-  const float f = __uint_as_float((x >> 9) | 0x3F800000u);
-  return fmaf(2.0f, f, -3.0f) + 0x1p-23f;
+  const float g = __uint_as_float(__builtin_amdgcn_alignbit(0x80u, x, 9u));
+  return (g - 3.0f) + 0x1p-23f;
 }
 
 // Two standard normals from two words (Box-Muller).
@@ -109,10 +111,16 @@ __device__ __forceinline__ void cell3(const Grid &g, float x, float y, float z,
   cz = wrap_cell(z, g.nz, g.inv_nz);
 }
 
-// (z ny + y) nx + x with 24-bit multiplies (every factor is below 2^24).
+// (z ny + y) nx + x with 24-bit multiplies (every factor is below 2^24).  The
+// empty asm keeps the inner product a 24-bit one: left alone, the compiler drops
+// its masking (the outer product reads 24 bits anyway) and takes the 64-bit
+// multiply-add, whose unused upper addend can be a register that a load in
+// flight will write, and the wave then waits for that load.
 __device__ __forceinline__ uint32_t cell_index(const Grid &g, uint32_t cx,
                                                uint32_t cy, uint32_t cz) {
-  return __umul24(__umul24(cz, (uint32_t)g.ny) + cy, (uint32_t)g.nx) + cx;
+  uint32_t zy = __umul24(cz, (uint32_t)g.ny) + cy;
+  asm("" : "+v"(zy));
+  return __umul24(zy, (uint32_t)g.nx) + cx;
 }
 
 __device__ __forceinline__ uint32_t cell_of(const Grid &g, float x, float y,

@@ -205,32 +205,45 @@ __device__ __forceinline__ LaneMap lane_map(const SweepArgs &a) {
 }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+// 24 bytes of a bead pair as 16 + 8 (8-byte aligned).
+typedef float f32x4_pair __attribute__((ext_vector_type(4), aligned(8)));
 
+// One bead's position, 12 bytes at 4-byte alignment.
+typedef float f32x3_bead __attribute__((ext_vector_type(3), aligned(4)));
+
+// The positions of a lane's beads.  Every lane loads (a lane without beads those
+// of the launch's first chain, a missing second bead the first again; both are
+// ignored later): under a condition the values would have to be merged with a
+// default where the branch ends, and the wave would wait for memory there instead
+// of at their first use.
 // NT: the non-temporal hint (a compile-time choice: loads that differ only in
 // the hint would be merged by the compiler, dropping it).
 template <bool VEC2, bool NT = false>
 __device__ __forceinline__ void load_pair(const float *cp, const LaneMap &m, F3 &r0, F3 &r1) {
-  r0 = F3{0.f, 0.f, 0.f};
-  r1 = F3{0.f, 0.f, 0.f};
   if (VEC2) {
-    if (m.has0) {
-      const f32x2 *q = reinterpret_cast<const f32x2 *>(cp);
-      f32x2 p0, p1, p2;
-      if (NT) {
-        p0 = __builtin_nontemporal_load(q);
-        p1 = __builtin_nontemporal_load(q + 1);
-        p2 = __builtin_nontemporal_load(q + 2);
-      } else {
-        p0 = q[0];
-        p1 = q[1];
-        p2 = q[2];
-      }
-      r0 = F3{p0.x, p0.y, p1.x};
-      r1 = F3{p1.y, p2.x, p2.y};
+    const f32x4_pair *q = reinterpret_cast<const f32x4_pair *>(cp);
+    const f32x2 *q2 = reinterpret_cast<const f32x2 *>(cp + 4);
+    f32x4_pair p;
+    f32x2 p2;
+    if (NT) {
+      p = __builtin_nontemporal_load(q);
+      p2 = __builtin_nontemporal_load(q2);
+    } else {
+      p = *q;
+      p2 = *q2;
     }
+    r0 = F3{p.x, p.y, p.z};
+    r1 = F3{p.w, p2.x, p2.y};
   } else {
-    if (m.has0) r0 = F3{cp[0], cp[1], cp[2]};
-    if (m.has1) r1 = F3{cp[3], cp[4], cp[5]};
+    const f32x3_bead *p0 = reinterpret_cast<const f32x3_bead *>(cp);
+    const f32x3_bead *p1 = reinterpret_cast<const f32x3_bead *>(cp + (m.has1 ? 3u : 0u));
+    if (NT) {
+      r0 = (F3)__builtin_nontemporal_load(p0);
+      r1 = (F3)__builtin_nontemporal_load(p1);
+    } else {
+      r0 = (F3)*p0;
+      r1 = (F3)*p1;
+    }
   }
 }
 
@@ -238,16 +251,16 @@ template <bool VEC2, bool NT = false>
 __device__ __forceinline__ void store_pair(float *cp, const LaneMap &m, F3 r0, F3 r1) {
   if (VEC2) {
     if (m.has0) {
-      f32x2 *q = reinterpret_cast<f32x2 *>(cp);
-      const f32x2 p0 = {r0.x, r0.y}, p1 = {r0.z, r1.x}, p2 = {r1.y, r1.z};
+      f32x4_pair *q = reinterpret_cast<f32x4_pair *>(cp);
+      f32x2 *q2 = reinterpret_cast<f32x2 *>(cp + 4);
+      const f32x4_pair p = {r0.x, r0.y, r0.z, r1.x};
+      const f32x2 p2 = {r1.y, r1.z};
       if (NT) {
-        __builtin_nontemporal_store(p0, q);
-        __builtin_nontemporal_store(p1, q + 1);
-        __builtin_nontemporal_store(p2, q + 2);
+        __builtin_nontemporal_store(p, q);
+        __builtin_nontemporal_store(p2, q2);
       } else {
-        q[0] = p0;
-        q[1] = p1;
-        q[2] = p2;
+        *q = p;
+        *q2 = p2;
       }
     }
   } else {
@@ -298,119 +311,74 @@ __device__ __forceinline__ uint32_t set_order_bit(const SweepArgs &a, const Lane
   return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)(w0x & 1u));
 }
 
-// ---------------------------------------------------------------------------
-// Local moves (Sec. 2.2, move (i)): uniform trial displacement in [-a,a] per
-// Cartesian direction, Metropolis acceptance of
-//   dE = (k0/2) sum_bonds (|r'-r_j|^2 - |r-r_j|^2) + (omega_t(c') - omega_t(c))/N.
-// A trial position depends only on the bead itself, so both trial positions of
-// a lane and the field values they need are fetched before either set moves;
-// only the bond term waits for the other set.  Per lane the two beads are
-// relabelled once by the chain's set order ("a" moves first, "b" second), so
-// the passes need no per-pass selection.  Requires a < 1 cell (host-checked):
-// a trial position is then at most one cell away along each axis.
-// ---------------------------------------------------------------------------
-// One wave's tile of local moves: positions r0/r1 already loaded for lane map m.
-template <bool COUNT64, bool VEC2, bool BINNED, bool NT = false>
-__device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap &m, float *cp,
-                                               F3 r0, F3 r1) {
-  const uint32_t N = a.n;
-  const uint32_t i0 = 2u * m.k, i1 = i0 + 1u;
-  const uint32_t gchain = a.chain_base + m.chain;
-  // old cells and their field values first: they need only the positions
-  uint32_t x0, y0, z0, x1, y1, z1;
-  cell3(a.grid, r0.x, r0.y, r0.z, x0, y0, z0);
-  cell3(a.grid, r1.x, r1.y, r1.z, x1, y1, z1);
-  const uint32_t c0 = cell_index(a.grid, x0, y0, z0);
-  const uint32_t c1 = cell_index(a.grid, x1, y1, z1);
-  const bool b0 = i0 >= a.n_a, b1 = i1 >= a.n_a;
-  const uint32_t pl0 = b0 ? a.grid.n_cells : 0u, pl1 = b1 ? a.grid.n_cells : 0u;
-  const float wo0 = field_at(a.omega, pl0, c0), wo1 = field_at(a.omega, pl1, c1);
+// The gradient-free energy term of a trial displacement d from r (in the FP32
+// order (2 (r - rj) + d), summed over the bonds): doubling is exact, so
+// fma(2, r - rj, d) rounds once, as the written sum does.
+__device__ __forceinline__ F3 bond_term(F3 r, F3 rj, F3 d) {
+  const F3 e = r - rj;
+  return F3{fmaf(2.0f, e.x, d.x), fmaf(2.0f, e.y, d.y), fmaf(2.0f, e.z, d.z)};
+}
 
-  const Rand4 w0 = philox(gchain, i0 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
-  const Rand4 w1 = philox(gchain, i1 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
-  const bool odd_first = set_order_bit(a, m, w0.x) != 0u;
+// s + w t for a weight w that is 0 or 1 (the product is exact: one rounding,
+// that of the sum).
+__device__ __forceinline__ F3 add_weighted(F3 s, float w, F3 t) {
+  return F3{fmaf(w, t.x, s.x), fmaf(w, t.y, s.y), fmaf(w, t.z, s.z)};
+}
 
-  // trial positions r' = fma(a, v, r) and their cells (at most one cell away)
-  const F3 t0 = {fmaf(a.step, uniform11(w0.x), r0.x), fmaf(a.step, uniform11(w0.y), r0.y),
-                 fmaf(a.step, uniform11(w0.z), r0.z)};
-  const F3 t1 = {fmaf(a.step, uniform11(w1.x), r1.x), fmaf(a.step, uniform11(w1.y), r1.y),
-                 fmaf(a.step, uniform11(w1.z), r1.z)};
-  const uint32_t sx0 = shift_cell(x0, r0.x, t0.x, a.grid.nx),
-                 sy0 = shift_cell(y0, r0.y, t0.y, a.grid.ny),
-                 sz0 = shift_cell(z0, r0.z, t0.z, a.grid.nz);
-  const uint32_t sx1 = shift_cell(x1, r1.x, t1.x, a.grid.nx),
-                 sy1 = shift_cell(y1, r1.y, t1.y, a.grid.ny),
-                 sz1 = shift_cell(z1, r1.z, t1.z, a.grid.nz);
-  const uint32_t n0 = cell_index(a.grid, sx0, sy0, sz0);
-  const uint32_t n1 = cell_index(a.grid, sx1, sy1, sz1);
-  // brick keys of the four cells now, so that the coordinates die here
-  const uint32_t kf0 = BINNED ? brick_key(a.bin, x0, y0, z0) : 0u;
-  const uint32_t kt0 = BINNED ? brick_key(a.bin, sx0, sy0, sz0) : 0u;
-  const uint32_t kf1 = BINNED ? brick_key(a.bin, x1, y1, z1) : 0u;
-  const uint32_t kt1 = BINNED ? brick_key(a.bin, sx1, sy1, sz1) : 0u;
-  // trial-cell values only where the trial leaves the cell, chosen afterwards.
-  // With the old-cell value as the default of the load (which the compiler
-  // makes of a plain choice unless the empty asm hides the loaded registers)
-  // every gather waits for the one before it; this way all four are in flight
-  // together.
-  float g0 = 0.0f, g1 = 0.0f;
-  if (n0 != c0) g0 = field_at(a.omega, pl0, n0);
-  if (n1 != c1) g1 = field_at(a.omega, pl1, n1);
-  asm volatile("" : "+v"(g0), "+v"(g1));
-  const float wn0 = n0 != c0 ? g0 : wo0, wn1 = n1 != c1 ? g1 : wo1;
-  const bool ok0 = move_allowed(a, c0, n0), ok1 = move_allowed(a, c1, n1);
+// Metropolis acceptance of an energy change d_e with draw u in (0,1); no branch,
+// both conditions are a compare.
+__device__ __forceinline__ bool metropolis(float d_e, float u) {
+  const bool down = d_e <= 0.0f, up = u < __expf(-d_e);
+  return down | up;
+}
 
-  // relabel by set order: a moves first, b second
-  const F3 ra0 = sel(odd_first, r1, r0), rb0 = sel(odd_first, r0, r1);
-  const F3 ta = sel(odd_first, t1, t0), tb = sel(odd_first, t0, t1);
-  const Rand4 wa = odd_first ? w1 : w0, wb = odd_first ? w0 : w1;
-  const bool has_a = odd_first ? m.has1 : m.has0, has_b = odd_first ? m.has0 : m.has1;
-  const bool ok_a = odd_first ? ok1 : ok0, ok_b = odd_first ? ok0 : ok1;
-  const float sa = (odd_first ? n1 != c1 : n0 != c0) ? a.self_term : 0.0f;
-  const float sb = (odd_first ? n0 != c0 : n1 != c1) ? a.self_term : 0.0f;
-  const float dfa = ((odd_first ? wn1 : wn0) - (odd_first ? wo1 : wo0)) * a.inv_nref + sa;
-  const float dfb = ((odd_first ? wn0 : wn1) - (odd_first ? wo0 : wo1)) * a.inv_nref + sb;
-  // bonded neighbours of a: own b and b of the adjacent lane (lane k-1 if a is
-  // even, lane k+1 if a is odd); of b: own a and a of the other adjacent lane
-  const int up = m.lane < 63 ? m.lane + 1 : m.lane, dn = m.lane > 0 ? m.lane - 1 : m.lane;
-  const int src_a = odd_first ? up : dn, src_b = odd_first ? dn : up;
-  const bool lo_ok = m.k > 0, hi_ok = i1 + 1u < N;   // beads 2k-1 and 2k+2 exist
-  const float wadj_a = (odd_first ? hi_ok : lo_ok) ? 1.0f : 0.0f;
-  const float wadj_b = (odd_first ? lo_ok : hi_ok) ? 1.0f : 0.0f;
-  const float wown_a = has_b ? 1.0f : 0.0f, wown_b = has_a ? 1.0f : 0.0f;
+// One trial of a local move: the bead, where it would go, its cells and the
+// field values it sees there.
+struct Trial {
+  F3 r, t;
+  uint32_t x, y, z, c;     // cell of r
+  uint32_t sx, sy, sz, n;  // cell of t
+  float wo, wn;
+};
 
-  // pass 1: set of a
-  F3 ra = ra0;
-  bool acc_a;
-  {
-    const F3 nb = {shfl_f(rb0.x, src_a), shfl_f(rb0.y, src_a), shfl_f(rb0.z, src_a)};
-    const F3 d = ta - ra;
-    const F3 q = wown_a * (2.0f * (ra - rb0) + d) + wadj_a * (2.0f * (ra - nb) + d);
-    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + dfa;
-    acc_a = has_a && ok_a && (d_e <= 0.0f || uniform01(wa.w) < __expf(-d_e));
-    ra = acc_a ? ta : ra;
-  }
-  // pass 2: set of b, against the updated a beads
-  F3 rb = rb0;
-  bool acc_b;
-  {
-    const F3 nb = {shfl_f(ra.x, src_b), shfl_f(ra.y, src_b), shfl_f(ra.z, src_b)};
-    const F3 d = tb - rb;
-    const F3 q = wown_b * (2.0f * (rb - ra) + d) + wadj_b * (2.0f * (rb - nb) + d);
-    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + dfb;
-    acc_b = has_b && ok_b && (d_e <= 0.0f || uniform01(wb.w) < __expf(-d_e));
-    rb = acc_b ? tb : rb;
-  }
-  store_pair<VEC2, NT>(cp, m, sel(odd_first, rb, ra), sel(odd_first, ra, rb));
-  const bool acc0 = odd_first ? acc_b : acc_a, acc1 = odd_first ? acc_a : acc_b;
-  if (BINNED) {
-    bin_moves<COUNT64>(a.bin, a.grid, a.counts, wave_sub_bin(a.wpb), kf0, kt0, b0 ? 1u : 0u,
-                       acc0 && n0 != c0, kf1, kt1, b1 ? 1u : 0u, acc1 && n1 != c1);
-  } else {
-    if (acc0 && n0 != c0) move_count<COUNT64>(a.counts, c0, n0, b0);
-    if (acc1 && n1 != c1) move_count<COUNT64>(a.counts, c1, n1, b1);
-  }
-  return (uint32_t)(__popcll(__ballot(acc_a)) + __popcll(__ballot(acc_b)));
+// Old cell and its field value (plane `pl` floats into omega): the first gather.
+__device__ __forceinline__ void trial_from(const SweepArgs &a, uint32_t pl, Trial &b) {
+  cell3(a.grid, b.r.x, b.r.y, b.r.z, b.x, b.y, b.z);
+  b.c = cell_index(a.grid, b.x, b.y, b.z);
+  b.wo = field_at(a.omega, pl, b.c);
+}
+
+// Trial position t = fma(a, v, r) (at most one cell away) and its cell.
+__device__ __forceinline__ void trial_to(const SweepArgs &a, Rand4 w, Trial &b) {
+  b.t = F3{fmaf(a.step, uniform11(w.x), b.r.x), fmaf(a.step, uniform11(w.y), b.r.y),
+           fmaf(a.step, uniform11(w.z), b.r.z)};
+  b.sx = shift_cell(b.x, b.r.x, b.t.x, a.grid.nx);
+  b.sy = shift_cell(b.y, b.r.y, b.t.y, a.grid.ny);
+  b.sz = shift_cell(b.z, b.r.z, b.t.z, a.grid.nz);
+  b.n = cell_index(a.grid, b.sx, b.sy, b.sz);
+}
+
+// Energy change of the field term (and the self term of a move that changes cell).
+__device__ __forceinline__ float trial_field(const SweepArgs &a, const Trial &b) {
+  return (b.wn - b.wo) * a.inv_nref + (b.n != b.c ? a.self_term : 0.0f);
+}
+
+// The values at the trial cells of two beads, where a trial leaves its cell.
+// The empty asm statements hide the loaded registers (a plain choice between them
+// and the old-cell values becomes a load with a default, which waits for the
+// default first).  The second gather waits for the first and for the old-cell
+// gathers: a trial cell mostly shares its line with the old one, and a gather
+// issued while that line is still on its way fetches it again (134M-bead melt:
+// 1232 us per sweep, 1284 with all four in flight together).
+__device__ __forceinline__ void trial_gather(const SweepArgs &a, uint32_t pla, Trial &x, uint32_t plb,
+                                             Trial &y) {
+  float ga = 0.0f, gb = 0.0f;
+  if (x.n != x.c) ga = field_at(a.omega, pla, x.n);
+  asm volatile("" : "+v"(ga));
+  if (y.n != y.c) gb = field_at(a.omega, plb, y.n);
+  asm volatile("" : "+v"(gb));
+  x.wn = x.n != x.c ? ga : x.wo;
+  y.wn = y.n != y.c ? gb : y.wo;
 }
 
 // ---------------------------------------------------------------------------
@@ -419,11 +387,98 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
 //   dE = (k0/2) sum_bonds (|r'-r_j|^2 - |r-r_j|^2) + (omega_t(c') - omega_t(c))/N.
 // A trial position depends only on the bead itself, so both trial positions of
 // a lane and the field values they need are fetched before either set moves;
-// only the bond term waits for the other set.  Per lane the two beads are
-// relabelled once by the chain's set order ("a" moves first, "b" second), so
-// the passes need no per-pass selection.  Requires a < 1 cell (host-checked):
-// a trial position is then at most one cell away along each axis.
+// only the bond term waits for the other set.  Requires a < 1 cell
+// (host-checked): a trial position is then at most one cell away along each axis.
 //
+// Order of the work: the position loads, then the draws (they need no position
+// and cover the loads), then the two beads of a lane are relabelled by the
+// chain's set order ("a" moves first, "b" second) and everything after is
+// written for a and b, so that only positions and draws pass through a choice per
+// lane, and the positions once more for the store (two 12-byte stores to the
+// beads' own places instead write each line in halves: 1228 -> 1279 us).  The kernel is
+// bound by its vector instructions (about 80% of its cycles) together with the
+// L1 and L2 traffic of the gathers.
+// ---------------------------------------------------------------------------
+// One wave's tile of local moves: positions r0/r1 already loaded for lane map m.
+// EVEN: every chain has an even number of beads, so a lane's two beads both
+// exist where the lane is active.
+template <bool COUNT64, bool EVEN, bool BINNED, bool NT = false>
+__device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap &m, float *cp,
+                                               F3 r0, F3 r1) {
+  const uint32_t i0 = 2u * m.k;
+  const uint32_t gchain = a.chain_base + m.chain;
+  const Rand4 w0 = philox(gchain, i0 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
+  const uint32_t odd = set_order_bit(a, m, w0.x);
+  const Rand4 w1 = philox(gchain, (i0 + 1u) | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
+  const bool odd_first = odd != 0u;
+  const Rand4 wa = odd_first ? w1 : w0, wb = odd_first ? w0 : w1;
+  const uint32_t ia = i0 + odd, ib = i0 + 1u - odd;
+  const bool has_a = EVEN ? m.has0 : (odd_first ? m.has1 : m.has0);
+  const bool has_b = EVEN ? m.has0 : (odd_first ? m.has0 : m.has1);
+  Trial A, B;
+  A.r = sel(odd_first, r1, r0);
+  B.r = sel(odd_first, r0, r1);
+  const bool ta = ia >= a.n_a, tb = ib >= a.n_a;   // bead types
+  const uint32_t pla = ta ? a.grid.n_cells : 0u, plb = tb ? a.grid.n_cells : 0u;
+  trial_from(a, pla, A);
+  trial_from(a, plb, B);
+  trial_to(a, wa, A);
+  trial_to(a, wb, B);
+  // brick keys of the four cells now, so that the coordinates die here
+  const uint32_t kfa = BINNED ? brick_key(a.bin, A.x, A.y, A.z) : 0u;
+  const uint32_t kta = BINNED ? brick_key(a.bin, A.sx, A.sy, A.sz) : 0u;
+  const uint32_t kfb = BINNED ? brick_key(a.bin, B.x, B.y, B.z) : 0u;
+  const uint32_t ktb = BINNED ? brick_key(a.bin, B.sx, B.sy, B.sz) : 0u;
+  trial_gather(a, pla, A, plb, B);
+  const bool ok_a = has_a & move_allowed(a, A.c, A.n), ok_b = has_b & move_allowed(a, B.c, B.n);
+  const float dfa = trial_field(a, A), dfb = trial_field(a, B);
+  // bonded neighbours of a: own b and b of the adjacent lane (lane k-1 if a is
+  // even, lane k+1 if a is odd); of b: own a and a of the other adjacent lane
+  const int up = m.lane < 63 ? m.lane + 1 : m.lane, dn = m.lane > 0 ? m.lane - 1 : m.lane;
+  const int src_a = odd_first ? up : dn, src_b = odd_first ? dn : up;
+  const bool lo_ok = m.k > 0, hi_ok = i0 + 2u < a.n;   // beads 2k-1 and 2k+2 exist
+  const float lo_w = lo_ok ? 1.0f : 0.0f, hi_w = hi_ok ? 1.0f : 0.0f;
+  const float wadj_a = odd_first ? hi_w : lo_w, wadj_b = odd_first ? lo_w : hi_w;
+
+  // pass 1: set of a
+  F3 ra = A.r;
+  bool acc_a;
+  {
+    const F3 nb = {shfl_f(B.r.x, src_a), shfl_f(B.r.y, src_a), shfl_f(B.r.z, src_a)};
+    const F3 d = A.t - A.r;
+    F3 own = bond_term(A.r, B.r, d);
+    if (!EVEN) own = (has_b ? 1.0f : 0.0f) * own;
+    const F3 q = add_weighted(own, wadj_a, bond_term(A.r, nb, d));
+    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + dfa;
+    acc_a = ok_a & metropolis(d_e, uniform01(wa.w));
+    ra = acc_a ? A.t : ra;
+  }
+  // pass 2: set of b, against the updated a beads
+  F3 rb = B.r;
+  bool acc_b;
+  {
+    const F3 nb = {shfl_f(ra.x, src_b), shfl_f(ra.y, src_b), shfl_f(ra.z, src_b)};
+    const F3 d = B.t - B.r;
+    F3 own = bond_term(B.r, ra, d);
+    if (!EVEN) own = (has_a ? 1.0f : 0.0f) * own;
+    const F3 q = add_weighted(own, wadj_b, bond_term(B.r, nb, d));
+    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + dfb;
+    acc_b = ok_b & metropolis(d_e, uniform01(wb.w));
+    rb = acc_b ? B.t : rb;
+  }
+  store_pair<EVEN, NT>(cp, m, sel(odd_first, rb, ra), sel(odd_first, ra, rb));
+  const bool mv_a = acc_a & (A.n != A.c), mv_b = acc_b & (B.n != B.c);
+  if (BINNED) {
+    bin_moves<COUNT64>(a.bin, a.grid, a.counts, wave_sub_bin(a.wpb), kfa, kta, ta ? 1u : 0u, mv_a,
+                       kfb, ktb, tb ? 1u : 0u, mv_b);
+  } else {
+    if (mv_a) move_count<COUNT64>(a.counts, A.c, A.n, ta);
+    if (mv_b) move_count<COUNT64>(a.counts, B.c, B.n, tb);
+  }
+  return (uint32_t)(__popcll(__ballot(acc_a)) + __popcll(__ballot(acc_b)));
+}
+
+// ---------------------------------------------------------------------------
 // Tiles (one wave's chains): one per wave, or drawn from per-XCD counters in
 // a persistent grid (TileIter).
 // ---------------------------------------------------------------------------
