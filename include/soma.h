@@ -85,7 +85,8 @@ typedef enum soma_status {
 
 /* How the SET sweeps keep the occupation histogram (Eq. (4), Sec. 3.1.1)
  * current; see soma_set_histogram. */
-#define SOMA_HIST_DIRECT 0u /* one memory-side atomic per +-1 count update (default) */
+#define SOMA_HIST_DIRECT 0u /* one memory-side atomic per +-1 count update; sweeps expected to
+                               make many updates go through the bins (default) */
 #define SOMA_HIST_BINNED 1u /* updates binned by brick of 16x16x8 cells, then applied
                                brick by brick in LDS */
 
@@ -318,10 +319,12 @@ int32_t soma_set_sweep_threads(soma_system *sys, uint32_t threads);
 /* Count updates of the SET-order sweeps (local, smart-MC, bond-Gibbs and
  * mixed moves of linear chains; the histogram of Eq. (4), Sec. 3.1.1).
  * SOMA_HIST_DIRECT: a bead that changes cell adds -1 and +1 to the packed
- * counts with two device atomics.  SOMA_HIST_BINNED: the grid is cut into
+ * counts with two device atomics, except in sweeps (local, smart-MC and
+ * bond-Gibbs moves, one wave per tile) whose expected number of updates makes the
+ * bins of the other mode the faster way.  SOMA_HIST_BINNED: the grid is cut into
  * bricks of 16 x 16 x 8 cells (x fastest; partial bricks at the faces); each
- * wave groups its updates by brick, reserves room in the brick's bin in the
- * workspace with one atomic per (wave, brick) and stores them there; after
+ * block groups its updates by brick, reserves room in the brick's bin in the
+ * workspace with one atomic per (block, brick) and stores them there; after
  * the sweep one workgroup per brick adds its bin to the counts in LDS (a bin
  * that is full takes further updates as direct atomics).  soma_mc_sweep,
  * soma_cycle and captured cycles run that step themselves, so the counts are

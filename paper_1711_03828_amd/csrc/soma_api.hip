@@ -19,6 +19,7 @@
 #include "soma_sweep.hpp"
 #include "soma_molecule.hpp"
 #include "soma_arch.hpp"
+#include "soma_apply.hpp"
 #include "soma_train.hpp"
 #include "soma_batch.hpp"
 #include "soma_sq.hpp"
@@ -74,7 +75,7 @@ struct Derived {
   uint64_t ws_bytes = 0;
   uint32_t field_blocks = 1;  // blocks of the field update (and its FP64 partial sums)
   // per-brick bins of count updates (soma_set_histogram): bricks of 16 x 16 x 8 cells
-  uint32_t nbx = 0, nby = 0, nbz = 0, bin_cap = 0;
+  uint32_t nbx = 0, nby = 0, nbz = 0, bin_cap = 0, sub_shift = 0;
   uint64_t n_bricks = 0, off_bin_count = 0, off_bins = 0;
   bool bins_ok = false;
   uint64_t off_queue = 0;   // tile counters of persistent local sweeps
@@ -166,13 +167,15 @@ int32_t derive(const soma_config *c, Derived *d) {
     // per sub-bin: twice its share of about half a brick's beads, plus slack
     // (a recount fills about half a brick's beads, a smart-MC sweep about 0.45)
     const double per_brick = (double)d->n_beads * soma::kBrickCells / (double)n_cells;
-    uint64_t cap = (uint64_t)std::ceil(1.1 * per_brick / soma::kSubBins) + 64u;
+    d->sub_shift = d->n_bricks < soma::kFewBricks ? soma::kMaxSubShift : soma::kMaxSubShift - 1u;
+    const uint32_t n_sub = 1u << d->sub_shift;
+    uint64_t cap = (uint64_t)std::ceil(1.1 * per_brick / n_sub) + 64u;
     cap = (cap + 15u) / 16u * 16u;
     if (cap > (1ull << 22)) cap = 1ull << 22;
     d->bin_cap = (uint32_t)cap;
     d->off_bin_count = d->ws_bytes;
-    d->off_bins = align_up(d->off_bin_count + 4ull * d->n_bricks * soma::kSubBins);
-    d->ws_bytes = align_up(d->off_bins + 4ull * d->n_bricks * soma::kSubBins * cap);
+    d->off_bins = align_up(d->off_bin_count + 4ull * d->n_bricks * n_sub);
+    d->ws_bytes = align_up(d->off_bins + 4ull * d->n_bricks * n_sub * cap);
   }
   return SOMA_OK;
 }
@@ -202,6 +205,27 @@ int32_t launch_zero(void *p, uint64_t bytes, hipStream_t s) {
   return SOMA_OK;
 }
 
+// Applies the bins to `planes` count planes, one workgroup per brick.
+int32_t launch_apply(const soma_config *c, const Derived &d, const soma::BinArgs &b, void *counts,
+                     uint32_t planes, hipStream_t s) {
+  const bool c64 = c->count_width == 32, few = d.n_bricks < soma::kFewBricks;
+  const size_t lds = (size_t)planes * soma::kBrickCells * (c64 ? 8u : 4u);
+  const dim3 grid((uint32_t)d.n_bricks), block(few ? soma::kApplyWide : soma::kApplyNarrow);
+  const soma::Grid g = make_grid(c, d.n_cells);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, b, g, counts, planes);
+  };
+  if (few) {
+    if (c64) launch(soma::bin_apply_kernel<true, soma::kApplyWide>);
+    else launch(soma::bin_apply_kernel<false, soma::kApplyWide>);
+  } else {
+    if (c64) launch(soma::bin_apply_kernel<true, soma::kApplyNarrow>);
+    else launch(soma::bin_apply_kernel<false, soma::kApplyNarrow>);
+  }
+  LAUNCH_TRY();
+  return SOMA_OK;
+}
+
 // From-scratch histogram.  With bins (`bins` not null: the system's workspace
 // holds them), each species' beads go through the per-brick bins and one
 // apply pass per brick; otherwise one device atomic per bead.
@@ -226,16 +250,7 @@ int32_t launch_hist(const soma_config *c, const Derived &d, const float *pos, vo
                            dim3(256), 0, s, p, nb, S.n, S.n_a, g, counts, d.arch[sp], *bins, v2);
       LAUNCH_TRY();
     }
-    const uint32_t planes = (d.n_types + 1u) / 2u;
-    const size_t lds = (size_t)planes * soma::kBrickCells * (c->count_width == 32 ? 8u : 4u);
-    if (c->count_width == 32)
-      hipLaunchKernelGGL(soma::bin_apply_kernel<true>, dim3((uint32_t)d.n_bricks),
-                         dim3(soma::kApplyThreads), lds, s, *bins, g, counts, planes);
-    else
-      hipLaunchKernelGGL(soma::bin_apply_kernel<false>, dim3((uint32_t)d.n_bricks),
-                         dim3(soma::kApplyThreads), lds, s, *bins, g, counts, planes);
-    LAUNCH_TRY();
-    return SOMA_OK;
+    return launch_apply(c, d, *bins, counts, (d.n_types + 1u) / 2u, s);
   }
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
     const soma_species &S = c->species[sp];
@@ -277,6 +292,13 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.ctr = nullptr;
   a.ctr_by = 0;
   return a;
+}
+
+// Counts of 64 MiB and more are read with the non-temporal hint (measured on the
+// 134M-bead melt: 3.7% off the SCMF cycle, the next sweep's field gathers hitting
+// the last-level cache more often).
+bool stream_counts(const soma_config *c, const Derived &d) {
+  return (uint64_t)d.n_cells * (c->count_width == 32 ? 8u : 4u) >= (64ull << 20);
 }
 
 // ctr, ctr_by: sweep counter that this refresh advances (the last one of a call).
@@ -323,11 +345,7 @@ int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float
   soma::FieldArgs a = field_args(c, d, counts, omega, partials, halo);
   a.ctr = ctr;
   a.ctr_by = ctr_by;
-  // counts of 64 MiB and more are read with the non-temporal hint (measured on
-  // the 134M-bead melt: 3.7% off the SCMF cycle, the next sweep's field
-  // gathers hitting the last-level cache more often)
-  const bool c64 = c->count_width == 32;
-  const bool nt = (uint64_t)d.n_cells * (c64 ? 8u : 4u) >= (64ull << 20);
+  const bool c64 = c->count_width == 32, nt = stream_counts(c, d);
   const dim3 grid(blocks), block(256);
   if (c64) {
     if (nt) hipLaunchKernelGGL((soma::field_update_kernel<true, true>), grid, block, 0, s, a);
@@ -452,6 +470,7 @@ struct soma_system {
   uint32_t substeps = 1;      // field refreshes per SCMF cycle (chain subsets)
   uint32_t scheme = SOMA_SCHEME_SET;  // iteration order of local moves
   uint32_t hist_mode = soma::kHistDirect;  // count updates of the SET sweeps (soma_set_histogram)
+  bool hist_auto = true;      // direct mode: sweeps with many updates may go through the bins
   uint32_t sweep_threads = 256;  // block size of the local, smart-MC and bond-Gibbs sweeps
   uint32_t self_term = 0;        // add the bead's own share to cell-changing moves (soma_set_self_term)
   float4 *grad = nullptr;     // optional gradient field (caller-owned), see soma_set_grad_field
@@ -483,6 +502,7 @@ struct soma_system {
     b.bin_count = reinterpret_cast<uint32_t *>(ws + d.off_bin_count);
     b.bins = reinterpret_cast<uint32_t *>(ws + d.off_bins);
     b.cap = d.bin_cap;
+    b.sub_shift = d.sub_shift;
     b.nbx = d.nbx;
     b.nby = d.nby;
     b.nbz = d.nbz;
@@ -576,19 +596,7 @@ void launch_sweep_b(bool binned, uint32_t kind, dim3 grid, dim3 threads, hipStre
 // workgroup per brick; the SET sweep kernels bin updates of types 0 and 1
 // only, which live in count plane 0).
 int32_t launch_bin_apply(soma_system *sys, hipStream_t s) {
-  const soma::BinArgs b = sys->bins();
-  const bool c64 = sys->cfg.count_width == 32;
-  const uint32_t planes = 1u;
-  const size_t lds = (size_t)planes * soma::kBrickCells * (c64 ? 8u : 4u);
-  const dim3 grid((uint32_t)sys->d.n_bricks), block(soma::kApplyThreads);
-  if (c64)
-    hipLaunchKernelGGL(soma::bin_apply_kernel<true>, grid, block, lds, s, b, sys->grid,
-                       sys->buf.counts, planes);
-  else
-    hipLaunchKernelGGL(soma::bin_apply_kernel<false>, grid, block, lds, s, b, sys->grid,
-                       sys->buf.counts, planes);
-  LAUNCH_TRY();
-  return SOMA_OK;
+  return launch_apply(&sys->cfg, sys->d, sys->bins(), sys->buf.counts, 1u, s);
 }
 
 // The second difference of the grid Hamiltonian per bead and cell, in kT:
@@ -667,12 +675,45 @@ bool species_vec2(const soma_system *sys, uint32_t sp) {
 // Chains sub_j, sub_j + sub_k, ... of a species of n chains.
 uint32_t subset_size(uint32_t n, uint32_t k, uint32_t j) { return n > j ? (n - j + k - 1) / k : 0u; }
 
-// One sweep of chain subset j of k of every species (k = 1: all chains); `off`
-// is added to the device sweep counter.
-int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t off,
-                     uint32_t k = 1, uint32_t j = 0) {
+// Whether a sweep of chain subset j of k in the default histogram mode sends its
+// count updates through the bins: where their atomics are expected to take longer
+// than the bins do.  Measured: 23 ps per memory-side atomic (two per bead that
+// changes cell); the bins cost about 10 us a launch (their part of the kernel that
+// applies them and of the sweep's barriers), a pass over the counts, and 0.1 ns
+// per wave.  Per SCMF cycle, atomics against bins, 256-thread blocks: 24^3 cells,
+// 33k beads 8.1 / 12.5 us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71;
+// film of 16M beads 170 / 161; bond-Gibbs moves of 1M beads 61 / 31; smart-MC moves
+// of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their blocks' LDS is full:
+// 978 / 1018 us), and so do persistent grids, whose waves reserve room one by one.
+bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
+  if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED || sys->sweep_blocks) return false;
   const soma_config *c = &sys->cfg;
-  const bool binned = sys->hist_mode == soma::kHistBinned;
+  double moved = 0.0, waves = 0.0;
+  for (uint32_t sp = 0; sp < c->n_species; ++sp) {
+    const soma_species &S = c->species[sp];
+    if (!S.n_chains || sys->d.arch[sp]) continue;
+    const double chains = subset_size(S.n_chains, k, j);
+    // mean displacement along an axis = chance of another cell there: uniform in
+    // [-a, a], or Gaussian of variance 2 A (smart MC) or 1 / k0 (bond-Gibbs)
+    const double per_axis = kind == SOMA_MOVE_LOCAL ? 0.5 * c->local_a
+                            : 0.8 * std::sqrt(kind == SOMA_MOVE_SMC ? 2.0 * c->smc_a : 1.0 / S.k0);
+    const double stay = 1.0 - std::min(per_axis, 1.0);
+    moved += chains * S.n * (1.0 - stay * stay * stay);
+    waves += chains / (64u / ((S.n + 1u) / 2u));
+  }
+  const double atomics = 2.0 * 23e-12 * moved;
+  const double bins = 10e-6 + (double)sys->d.counts_bytes / 2e12 + 1e-10 * waves;
+  return atomics > bins;
+}
+
+// One sweep of chain subset j of k of every species (k = 1: all chains); `off`
+// is added to the device sweep counter.  *pending (if not null) receives whether
+// the bins hold updates that are still to be applied; with null they are applied.
+int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t off,
+                     uint32_t k = 1, uint32_t j = 0, bool *pending = nullptr) {
+  const soma_config *c = &sys->cfg;
+  const bool binned = sys->hist_mode == soma::kHistBinned ||
+                      (sys->hist_auto && sys->scheme == SOMA_SCHEME_SET && bins_pay(sys, kind, k, j));
   bool any_binned = false;
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
     const soma_species &S = c->species[sp];
@@ -723,7 +764,8 @@ int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t of
     LAUNCH_TRY();
     any_binned |= binned;
   }
-  if (any_binned) return launch_bin_apply(sys, s);
+  if (pending) *pending = any_binned;
+  else if (any_binned) return launch_bin_apply(sys, s);
   return SOMA_OK;
 }
 
@@ -762,11 +804,51 @@ int32_t launch_grad(soma_system *sys, hipStream_t s) {
   return SOMA_OK;
 }
 
-// Stage 1 of the cycle: fields from the counts, then the gradient field if kept.
-// advance > 0: the sweep counter moves on by that many sweeps.
-int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0) {
-  int32_t r = launch_field(&sys->cfg, sys->d, sys->buf.counts, sys->buf.omega, sys->fpart(), s,
-                           sys->halo(), advance ? sys->sweep_ctr() : nullptr, advance);
+// The bins applied and the fields refreshed in one launch (two bead types).
+// Without statistics one block per brick; with them at most as many as there are
+// partials, each over several bricks.
+int32_t launch_apply_field(soma_system *sys, hipStream_t s, bool stats, uint32_t advance) {
+  const bool c64 = sys->cfg.count_width == 32;
+  const size_t lds = (size_t)soma::kBrickCells * (c64 ? 8u : 4u);
+  soma::FieldArgs a = field_args(&sys->cfg, sys->d, sys->buf.counts, sys->buf.omega,
+                                 stats ? sys->fpart() : nullptr, sys->halo());
+  a.ctr = advance ? sys->sweep_ctr() : nullptr;
+  a.ctr_by = advance;
+  const uint32_t n_bricks = (uint32_t)sys->d.n_bricks, parts = sys->d.field_blocks;
+  const bool nt = stream_counts(&sys->cfg, sys->d);
+  const dim3 grid(stats ? std::min(n_bricks, parts) : n_bricks);
+  const dim3 block(nt ? soma::kApplyFieldThreads<true> : soma::kApplyFieldThreads<false>);
+  const soma::BinArgs b = sys->bins();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, b, sys->grid, a, n_bricks, parts);
+  };
+  if (nt) {
+    if (c64) launch(soma::apply_field_kernel<true, true>);
+    else launch(soma::apply_field_kernel<false, true>);
+  } else {
+    if (c64) launch(soma::apply_field_kernel<true, false>);
+    else launch(soma::apply_field_kernel<false, false>);
+  }
+  LAUNCH_TRY();
+  return SOMA_OK;
+}
+
+// Stage 1 of the cycle: fields from the counts (with `pending` after the bins are
+// applied), then the gradient field if kept.  advance > 0: the sweep counter moves
+// on by that many sweeps.  stats: leave the count sums and H_nb.
+int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0, bool pending = false,
+                       bool stats = true) {
+  int32_t r = SOMA_OK;
+  if (pending && sys->d.n_types <= 2) {
+    r = launch_apply_field(sys, s, stats, advance);
+    if (!r && sys->grad) r = launch_grad(sys, s);
+    return r;
+  }
+  if (pending) r = launch_bin_apply(sys, s);
+  if (r) return r;
+  r = launch_field(&sys->cfg, sys->d, sys->buf.counts, sys->buf.omega,
+                   stats ? sys->fpart() : nullptr, s, sys->halo(),
+                   advance ? sys->sweep_ctr() : nullptr, advance);
   if (!r && sys->grad) r = launch_grad(sys, s);
   return r;
 }
@@ -774,13 +856,16 @@ int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0) {
 // n SCMF cycles: for each of the system's k chain subsets, its sweep and then
 // the field refresh (k = 1: sweep, refresh).  The last refresh advances the
 // device sweep counter by n (a launch of its own took 1.4 us of a small melt's
-// 12 us cycle, and the gap before it).
+// 12 us cycle, and the gap before it); only it leaves count sums and H_nb, which
+// nothing reads in between.
 int32_t enqueue_cycles(soma_system *sys, uint32_t n, uint32_t kind, hipStream_t s) {
   const uint32_t k = sys->substeps;
   for (uint32_t i = 0; i < n; ++i)
     for (uint32_t j = 0; j < k; ++j) {
-      int32_t r = launch_sweep(sys, kind, s, i, k, j);
-      if (!r) r = refresh_fields(sys, s, i + 1u == n && j + 1u == k ? n : 0u);
+      bool pending = false;
+      int32_t r = launch_sweep(sys, kind, s, i, k, j, &pending);
+      const bool last = i + 1u == n && j + 1u == k;
+      if (!r) r = refresh_fields(sys, s, last ? n : 0u, pending, last);
       if (r) return r;
     }
   return SOMA_OK;
@@ -960,6 +1045,7 @@ int32_t soma_set_histogram(soma_system *sys, uint32_t mode) {
   if (mode == SOMA_HIST_BINNED && !sys->d.bins_ok)
     return fail(SOMA_E_UNSUPPORTED, "binned count updates need fewer than 2^21 bricks of 16x16x8 cells");
   sys->hist_mode = mode == SOMA_HIST_BINNED ? soma::kHistBinned : soma::kHistDirect;
+  sys->hist_auto = mode == SOMA_HIST_DIRECT;
   return SOMA_OK;
 }
 
@@ -1972,7 +2058,7 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   if (!binned) return SOMA_OK;
   // every system's bins into its counts: one workgroup per brick of the batch
   const uint32_t n_sys = (uint32_t)b->sys.size();
-  const dim3 agrid(b->brick_first[n_sys]), ablock(soma::kApplyThreads);
+  const dim3 agrid(b->brick_first[n_sys]), ablock(soma::kApplyWide);
   const size_t lds = (size_t)soma::kBrickCells * (b->c64 ? 8u : 4u);
   if (b->c64)
     hipLaunchKernelGGL(soma::batched_bin_apply_kernel<true>, agrid, ablock, lds, s, b->d_apply,
@@ -2383,6 +2469,7 @@ int32_t soma_autotune(soma_system *sys, uint32_t cycles, uint32_t move_kind,
     sys->sweep_blocks = grid;
     if (!mol) {
       sys->hist_mode = (mode & 1u) ? soma::kHistBinned : soma::kHistDirect;
+      sys->hist_auto = false;   // the measured choice, not the expected one
       sys->sweep_threads = 64u * (((mode >> 1) & 7u) + 1u);
     }
   };

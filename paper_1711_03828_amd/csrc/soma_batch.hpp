@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
   __shared__ __bf16 s_act[KIND == 2 ? 4 : 1][KIND == 2 ? 64 * kActStride : 1];
   __shared__ float s_z[KIND == 2 ? 4 : 1][KIND == 2 ? 64 * 8 : 1];
   __shared__ __bf16 s_w[KIND == 2 ? kWRows * kWStride : 1];
+  __shared__ BinSlot<BINNED, 4u, false> s_bin;
   uint32_t net_sg = 0xFFFFFFFFu;   // segment whose weights s_w holds (mixed sweeps)
   uint32_t item, end, stride;
   if (L.mode == 0) {   // grid is a multiple of 8 blocks (host-checked)
@@ -56,6 +57,7 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
   }
   for (; item < end; item += stride) {   // block-uniform loop
     const uint32_t sg = range_of(L.seg_first, L.n_segs, item);
+    if constexpr (BINNED) bins_begin(s_bin);
     SweepArgs a = resolve_sweep(L.segs[sg].a, L.sweep_off);
     a.sub_k = L.sub_k;
     a.sub_j = L.sub_j;
@@ -66,11 +68,11 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
       float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
       F3 r0, r1;
       load_pair<VEC2>(cp, m, r0, r1);
-      finish_block(a, local_tile<COUNT64, VEC2, BINNED>(a, m, cp, r0, r1));
+      finish_block(a, local_tile<COUNT64, VEC2, BINNED>(a, m, cp, r0, r1, s_bin));
     } else if (KIND == 1) {
-      finish_block(a, smc_wave<COUNT64, VEC2, BINNED>(a, m));
+      finish_block(a, smc_wave<COUNT64, VEC2, BINNED>(a, m, s_bin));
     } else if (KIND == 3) {
-      finish_block(a, smc_wave<COUNT64, VEC2, BINNED, true>(a, m));
+      finish_block(a, smc_wave<COUNT64, VEC2, BINNED, true>(a, m, s_bin));
     } else {
       const MixArgs mx = L.segs[sg].mx;
       if (sg != net_sg) {   // block-uniform: a new segment's network
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
       }
       uint32_t cnt[3];
       mixed_wave<COUNT64, VEC2, BINNED>(a, mx, m, s_act[KIND == 2 ? m.wib : 0],
-                                       s_z[KIND == 2 ? m.wib : 0], s_w, cnt);
+                                       s_z[KIND == 2 ? m.wib : 0], s_w, cnt, s_bin);
       mixed_finish(a, mx, cnt);
     }
   }
@@ -97,13 +99,13 @@ struct BinApplySeg {
 };
 
 template <bool COUNT64>
-__global__ __launch_bounds__(kApplyThreads) void batched_bin_apply_kernel(
+__global__ __launch_bounds__(kApplyWide) void batched_bin_apply_kernel(
     const BinApplySeg *__restrict__ segs, const uint32_t *__restrict__ brick_first,
     uint32_t n_sys) {
   extern __shared__ uint32_t s_cnt[];
   const uint32_t s = range_of(brick_first, n_sys, blockIdx.x);
   const BinApplySeg x = segs[s];
-  bin_apply_brick<COUNT64>(x.b, x.g, x.counts, 1u, blockIdx.x - brick_first[s], s_cnt);
+  bin_apply_brick<COUNT64, kApplyWide>(x.b, x.g, x.counts, 1u, blockIdx.x - brick_first[s], s_cnt);
 }
 
 }  // namespace soma

@@ -2,10 +2,11 @@
 // through per-brick bins of count updates instead of one memory-side atomic
 // per update.
 //
-// The grid is cut into bricks of 16 x 16 x 8 cells.  A wave that moves beads
+// The grid is cut into bricks of 16 x 16 x 8 cells.  A block that moves beads
 // to other cells counts its +-1 updates per brick in a small LDS table,
-// reserves room in each brick's bin with one atomic per (wave, brick) and
-// writes the updates there with plain stores; a bin that is full takes the
+// reserves room in each brick's bin with one atomic per (block, brick) and
+// writes the updates there with plain stores (the waves of a persistent grid,
+// which run different numbers of tiles, do so wave by wave); a bin that is full takes the
 // rest as direct atomics on the counts.  Afterwards `bin_apply_kernel` gives
 // every brick one workgroup: the brick's count words go to LDS, the bin's
 // updates are added with LDS atomics, and the words go back.  Integer additions are exact and
@@ -29,22 +30,34 @@ constexpr uint32_t kHistBinned = 1u;         // per-brick bins, applied by bin_a
 constexpr uint32_t kUpdPresent = 0x8000u;
 constexpr uint32_t kUpdMinus = 0x4000u;
 
-// Every brick has kSubBins sub-bins; a wave appends to sub-bin (wave index
-// mod kSubBins), so that the waves working on one region of the grid at the
-// same time (they share its bricks) spread their reservations over
-// different counters instead of queueing on one.
-constexpr uint32_t kSubShift = 4u, kSubBins = 1u << kSubShift;
+// Every brick has 1 << sub_shift sub-bins; a block (or wave) appends to the one of
+// its index, so that those working on one region of the grid at the same time
+// (they share its bricks) spread their reservations over different counters
+// instead of queueing on one (a returning atomic on one address takes about 100
+// ns at the memory side).  16 sub-bins on grids of fewer than kFewBricks bricks,
+// whose counters are few; 8 on larger ones, where the entries of a brick then lie
+// in fewer lines (134M-bead melt, 13,824 bricks: 1107 us per sweep, 1147 with 16;
+// a batch of small melts: 323 against 292 us the other way round).
+constexpr uint32_t kMaxSubShift = 4u, kSubBins = 1u << kMaxSubShift, kFewBricks = 2048u;
 
 struct BinArgs {
-  uint32_t *bins;        // [n_bricks][kSubBins][cap] entries
-  uint32_t *bin_count;   // [n_bricks][kSubBins] entries written (beyond cap: went direct)
+  uint32_t *bins;        // [n_bricks][1 << sub_shift][cap] entries
+  uint32_t *bin_count;   // [n_bricks][1 << sub_shift] entries written (beyond cap: went direct)
   uint32_t cap;          // entries per sub-bin
+  uint32_t sub_shift;
   uint32_t nbx, nby, nbz;
 };
 
-// Sub-bin of the calling wave (wpb waves per block).
-__device__ __forceinline__ uint32_t wave_sub_bin(uint32_t wpb) {
-  return ((blockIdx.x * wpb) + (threadIdx.x >> 6)) & (kSubBins - 1u);
+// Sub-bin of the calling block, and of the calling wave (wpb waves per block).
+// Blocks that work on one region are either consecutive (no remapping) or eight
+// apart (one XCD's contiguous range); b + floor(b / 8) runs through every residue
+// in both cases.  (b mod 16 alone gives an XCD's blocks two of the 16 sub-bins,
+// which fill up and send the rest to direct atomics.)
+__device__ __forceinline__ uint32_t block_sub_bin(const BinArgs &b) {
+  return (blockIdx.x + (blockIdx.x >> 3)) & ((1u << b.sub_shift) - 1u);
+}
+__device__ __forceinline__ uint32_t wave_sub_bin(const BinArgs &b, uint32_t wpb) {
+  return ((blockIdx.x + (blockIdx.x >> 3)) * wpb + (threadIdx.x >> 6)) & ((1u << b.sub_shift) - 1u);
 }
 
 // Brick key of cell (x, y, z): brick index << 11 | cell inside the brick.
@@ -111,31 +124,28 @@ __device__ __forceinline__ void apply_entry_direct(const BinArgs &b, const Grid 
   }
 }
 
-// Per-wave table of the bricks a wave's updates fall in: kTabSlots slots of
-// {brick, count} in LDS, open addressing with linear probing.  Built for one
-// bin_append call and discarded after it.
-constexpr uint32_t kTabSlots = 32u;
+// Table of the bricks that a block's (or a wave's) updates fall in: SLOTS slots
+// of {brick, count} in LDS, open addressing with linear probing.
+constexpr uint32_t kWaveSlots = 32u, kBlockSlots = 256u;
 constexpr uint32_t kTabEmpty = 0xFFFFFFFFu;   // no brick (brick indices are below 2^21)
-constexpr uint32_t kNoSlot = 0xFFu;
-constexpr uint32_t kMaxWaves = 8u;            // waves per block that may call bin_append
+constexpr uint32_t kNoSlot = 0xFFFFu;
 
-__device__ __forceinline__ uint32_t tab_hash(uint32_t brick) {
-  return (__umul24(brick, 0x9E3779u) >> 11) & (kTabSlots - 1u);
-}
+// Slot of `brick` in the table (claimed if new) << 16 | the entry's rank among
+// the table's entries for that brick; kNoSlot << 16 if kMaxProbe slots are taken
+// by other bricks (chains scattered over more bricks than the table is for).
+constexpr uint32_t kMaxProbe = 32u;
 
-// Slot of `brick` in the wave's table (claimed if new) << 16 | the entry's
-// rank among the wave's entries for that brick; kNoSlot << 16 if the table is
-// full.
+template <uint32_t SLOTS>
 __device__ __forceinline__ uint32_t tab_insert(uint2 *tab, uint32_t brick) {
-  uint32_t h = tab_hash(brick);
+  uint32_t h = (__umul24(brick, 0x9E3779u) >> 11) & (SLOTS - 1u);
   uint32_t probe = 0;
 #pragma unroll 1
-  for (; probe < kTabSlots; ++probe) {
+  for (; probe < kMaxProbe; ++probe) {
     const uint32_t old = atomicCAS(&tab[h].x, kTabEmpty, brick);
     if (old == kTabEmpty || old == brick) break;
-    h = (h + 1u) & (kTabSlots - 1u);
+    h = (h + 1u) & (SLOTS - 1u);
   }
-  if (probe == kTabSlots) return kNoSlot << 16;
+  if (probe == kMaxProbe) return kNoSlot << 16;
   return (h << 16) | atomicAdd(&tab[h].y, 1u);
 }
 
@@ -147,7 +157,7 @@ __device__ __forceinline__ void tab_put(const BinArgs &b, const Grid &g, void *c
                                         uint32_t v) {
   const uint32_t h = q >> 16;
   const uint32_t pos = h != kNoSlot ? tab[h].y + (q & 0xFFFFu) : 0xFFFFFFFFu;
-  if (pos < b.cap) b.bins[(size_t)((k << kSubShift) | sub) * b.cap + pos] = v;
+  if (pos < b.cap) b.bins[(size_t)((k << b.sub_shift) | sub) * b.cap + pos] = v;
   else apply_entry_direct<COUNT64>(b, g, counts, k, v);
 }
 
@@ -157,98 +167,154 @@ __device__ __forceinline__ uint32_t mbcnt64(uint64_t m) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Appends the entries of a wave to their bricks' bins.  Each lane offers up
-// to four entries (slot s: brick ks, value vs, wanted if bit s of `want`).
-// All lanes of the wave must call this together (wave-uniform control flow).
-// The wanted entries are first packed into a wave-private LDS list (slot 0 of
-// every lane, then slot 1, ...), so that the steps below run once per 64
-// entries with every lane busy, rather than once per slot with the few lanes
-// whose bead changed cell.  The entries are counted per brick in the wave's
-// LDS table (the rank of an entry is its place among the wave's entries for
-// its brick), one lane per brick reserves that many places in the brick's
-// sub-bin `sub` with one atomic, and every entry is stored at reserved base +
-// rank.  LDS operations of one wave execute in issue order, so neither the
-// list nor the table needs a barrier between the steps.
+// Up to four entries of each lane (slot s: brick ks, value vs, wanted if bit s of
+// `want`), packed into the wave's LDS list (slot 0 of every lane, then slot 1,
+// ...): entry lane + 64 p of the list in e[p].  So the steps that follow run once
+// per 64 entries with every lane busy, rather than once per slot with the few
+// lanes whose bead changed cell.  LDS operations of one wave execute in issue
+// order, so the list needs no barrier.
 constexpr uint32_t kListSlots = 4u * 64u;
 
-template <bool COUNT64>
-__device__ __forceinline__ void bin_append(const BinArgs &b, const Grid &g, void *counts,
-                                           uint32_t sub, uint32_t k0, uint32_t k1, uint32_t k2,
-                                           uint32_t k3, uint32_t v0, uint32_t v1, uint32_t v2,
-                                           uint32_t v3, uint32_t want) {
-  __shared__ uint2 s_tab[kMaxWaves * kTabSlots];
-  __shared__ uint2 s_list[kMaxWaves * kListSlots];
+struct BinEntries {
+  uint2 e[4];      // {brick, value}
+  uint32_t q[4];   // table slot << 16 | rank
+  uint32_t n;      // entries of the wave
+};
+
+__device__ __forceinline__ BinEntries pack_entries(uint2 *list, uint32_t k0, uint32_t k1, uint32_t k2,
+                                                   uint32_t k3, uint32_t v0, uint32_t v1, uint32_t v2,
+                                                   uint32_t v3, uint32_t want) {
   const uint32_t lane = __lane_id();
-  uint2 *tab = s_tab + (threadIdx.x >> 6) * kTabSlots;
-  uint2 *list = s_list + (threadIdx.x >> 6) * kListSlots;
-  if (lane < kTabSlots) tab[lane] = make_uint2(kTabEmpty, 0u);
   const uint64_t m0 = __ballot((want & 1u) != 0u), m1 = __ballot((want & 2u) != 0u);
   const uint64_t m2 = __ballot((want & 4u) != 0u), m3 = __ballot((want & 8u) != 0u);
   const uint32_t o1 = (uint32_t)__popcll(m0), o2 = o1 + (uint32_t)__popcll(m1);
-  const uint32_t o3 = o2 + (uint32_t)__popcll(m2), n = o3 + (uint32_t)__popcll(m3);
+  const uint32_t o3 = o2 + (uint32_t)__popcll(m2);
+  BinEntries b;
+  b.n = o3 + (uint32_t)__popcll(m3);
   if (want & 1u) list[mbcnt64(m0)] = make_uint2(k0, v0);
   if (want & 2u) list[o1 + mbcnt64(m1)] = make_uint2(k1, v1);
   if (want & 4u) list[o2 + mbcnt64(m2)] = make_uint2(k2, v2);
   if (want & 8u) list[o3 + mbcnt64(m3)] = make_uint2(k3, v3);
   __builtin_amdgcn_wave_barrier();
-  // entry lane + 64 p of the list in pass p (n is wave-uniform)
-  uint2 e[4];
-  uint32_t q[4];   // slot << 16 | rank
 #pragma unroll
   for (uint32_t p = 0; p < 4u; ++p) {
-    e[p] = make_uint2(0u, 0u);
-    q[p] = 0u;
-    if (64u * p < n) {
-      const uint32_t j = 64u * p + lane;
-      if (j < n) {
-        e[p] = list[j];
-        q[p] = tab_insert(tab, e[p].x);
-      }
-    }
+    b.e[p] = make_uint2(0u, 0u);
+    b.q[p] = 0u;
+    if (64u * p < b.n && 64u * p + lane < b.n) b.e[p] = list[64u * p + lane];
   }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < kTabSlots) {   // one reservation per brick; the slot keeps its base
-    const uint2 t = tab[lane];
-    if (t.x != kTabEmpty) tab[lane].y = atomicAdd(b.bin_count + ((t.x << kSubShift) | sub), t.y);
-  }
-  __builtin_amdgcn_wave_barrier();
+  return b;
+}
+
+template <uint32_t SLOTS>
+__device__ __forceinline__ void insert_entries(uint2 *tab, BinEntries &b) {
+  const uint32_t lane = __lane_id();
 #pragma unroll
-  for (uint32_t p = 0; p < 4u; ++p) {
-    if (64u * p < n && 64u * p + lane < n)
-      tab_put<COUNT64>(b, g, counts, tab, sub, e[p].x, q[p], e[p].y);
+  for (uint32_t p = 0; p < 4u; ++p)
+    if (64u * p < b.n && 64u * p + lane < b.n) b.q[p] = tab_insert<SLOTS>(tab, b.e[p].x);
+}
+
+// One reservation per brick of the table; the slot keeps its base.
+__device__ __forceinline__ void reserve_slot(const BinArgs &b, uint2 *slot, uint32_t sub) {
+  const uint2 t = *slot;
+  if (t.x != kTabEmpty) slot->y = atomicAdd(b.bin_count + ((t.x << b.sub_shift) | sub), t.y);
+}
+
+template <bool COUNT64>
+__device__ __forceinline__ void put_entries(const BinArgs &b, const Grid &g, void *counts,
+                                            const uint2 *tab, uint32_t sub, const BinEntries &n) {
+  const uint32_t lane = __lane_id();
+#pragma unroll
+  for (uint32_t p = 0; p < 4u; ++p)
+    if (64u * p < n.n && 64u * p + lane < n.n)
+      tab_put<COUNT64>(b, g, counts, tab, sub, n.e[p].x, n.q[p], n.e[p].y);
+}
+
+// LDS of the binned count updates of a block of up to WAVES waves.  WAVEWISE:
+// tables per wave (persistent grids), else one for the block.
+template <uint32_t WAVES, bool WAVEWISE>
+struct BinLds {
+  uint2 tab[WAVEWISE ? WAVES * kWaveSlots : kBlockSlots];
+  uint2 list[WAVES * kListSlots];
+};
+
+// Empties the block's table; before the first append, with nothing of an
+// earlier one outstanding.  Waves start together here, so the barrier is cheap.
+template <uint32_t WAVES, bool WAVEWISE>
+__device__ __forceinline__ void bins_begin(BinLds<WAVES, WAVEWISE> &s) {
+  if (WAVEWISE) return;
+  for (uint32_t i = threadIdx.x; i < kBlockSlots; i += blockDim.x) s.tab[i] = make_uint2(kTabEmpty, 0u);
+  __syncthreads();
+}
+
+// Appends entries to their bricks' bins: they are counted per brick in the table
+// (the rank of an entry is its place among the table's entries for its brick),
+// one lane per brick reserves that many places in the brick's sub-bin with one
+// atomic, and every entry is stored at reserved base + rank.  Every lane of the
+// wave, and of the block unless WAVEWISE, calls this together, once per
+// bins_begin.  The 8 waves of a 512-thread block work on neighbouring chains and
+// share most of their bricks: with one reservation per (block, brick) instead of
+// one per (wave, brick) the binned local sweep of the 134M-bead melt takes 1102 us
+// (was 1237), of 8.4M beads on 96^3 cells 58 us (101), of a 16M-bead film, whose
+// few bricks make the counters few, 132 us (280).
+template <bool COUNT64, uint32_t WAVES, bool WAVEWISE>
+__device__ __forceinline__ void bin_append(BinLds<WAVES, WAVEWISE> &s, const BinArgs &b, const Grid &g,
+                                           void *counts, uint32_t wpb, uint32_t k0, uint32_t k1,
+                                           uint32_t k2, uint32_t k3, uint32_t v0, uint32_t v1,
+                                           uint32_t v2, uint32_t v3, uint32_t want) {
+  const uint32_t lane = __lane_id(), wv = threadIdx.x >> 6;
+  uint2 *list = s.list + wv * kListSlots;
+  if (WAVEWISE) {
+    uint2 *tab = s.tab + wv * kWaveSlots;
+    const uint32_t sub = wave_sub_bin(b, wpb);
+    if (lane < kWaveSlots) tab[lane] = make_uint2(kTabEmpty, 0u);
+    BinEntries n = pack_entries(list, k0, k1, k2, k3, v0, v1, v2, v3, want);
+    insert_entries<kWaveSlots>(tab, n);
+    __builtin_amdgcn_wave_barrier();
+    if (lane < kWaveSlots) reserve_slot(b, tab + lane, sub);
+    __builtin_amdgcn_wave_barrier();
+    put_entries<COUNT64>(b, g, counts, tab, sub, n);
+    __builtin_amdgcn_wave_barrier();
+    return;
   }
-  __builtin_amdgcn_wave_barrier();
+  const uint32_t sub = block_sub_bin(b);
+  BinEntries n = pack_entries(list, k0, k1, k2, k3, v0, v1, v2, v3, want);
+  insert_entries<kBlockSlots>(s.tab, n);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < kBlockSlots; i += blockDim.x) reserve_slot(b, s.tab + i, sub);
+  __syncthreads();
+  put_entries<COUNT64>(b, g, counts, s.tab, sub, n);
 }
 
 // The count updates of a lane's two beads (bead e moved from the cell with
-// brick key from[e] to to[e] if moved[e]; t[e] its type), as bin entries of
-// sub-bin `sub`:
-// one entry when both cells lie in one brick, else one entry per brick.
-template <bool COUNT64>
-__device__ __forceinline__ void bin_moves(const BinArgs &b, const Grid &g, void *counts,
-                                          uint32_t sub, uint32_t from0, uint32_t to0, uint32_t t0,
-                                          bool moved0, uint32_t from1, uint32_t to1, uint32_t t1,
-                                          bool moved1) {
+// brick key from[e] to to[e] if moved[e]; t[e] its type), as bin entries: one
+// when both cells lie in one brick, else one per brick.
+template <bool COUNT64, uint32_t WAVES, bool WAVEWISE>
+__device__ __forceinline__ void bin_moves(BinLds<WAVES, WAVEWISE> &s, const BinArgs &b, const Grid &g,
+                                          void *counts, uint32_t wpb, uint32_t from0, uint32_t to0,
+                                          uint32_t t0, bool moved0, uint32_t from1, uint32_t to1,
+                                          uint32_t t1, bool moved1) {
   const uint32_t hm0 = kUpdPresent | kUpdMinus | (t0 << 11) | (from0 & 2047u);
   const uint32_t hp0 = kUpdPresent | (t0 << 11) | (to0 & 2047u);
   const uint32_t hm1 = kUpdPresent | kUpdMinus | (t1 << 11) | (from1 & 2047u);
   const uint32_t hp1 = kUpdPresent | (t1 << 11) | (to1 & 2047u);
   const bool same0 = (from0 >> 11) == (to0 >> 11), same1 = (from1 >> 11) == (to1 >> 11);
   const uint32_t want = (moved0 ? (same0 ? 1u : 3u) : 0u) | (moved1 ? (same1 ? 4u : 12u) : 0u);
-  bin_append<COUNT64>(b, g, counts, sub, from0 >> 11, to0 >> 11, from1 >> 11, to1 >> 11,
+  bin_append<COUNT64>(s, b, g, counts, wpb, from0 >> 11, to0 >> 11, from1 >> 11, to1 >> 11,
                       same0 ? (hm0 | (hp0 << 16)) : hm0, hp0 << 16,
                       same1 ? (hm1 | (hp1 << 16)) : hm1, hp1 << 16, want);
 }
 
 // From-scratch histogram of one species through the bins (counts cleared
 // before): lane q of the grid takes beads 2q and 2q+1 of the species (one
-// entry when both lie in one brick), so that a wave of 128 consecutive beads
+// entry when both lie in one brick), so that a block of 512 consecutive beads
 // reserves room once per brick it touches.  Positions are read as three
 // 8-byte pairs when `vec2` (8-byte aligned species start).
 template <bool COUNT64>
 __global__ __launch_bounds__(256) void density_hist_binned_kernel(
     const float *pos, uint64_t n_beads, uint32_t n, uint32_t n_a, Grid g, void *counts,
     const ArchDev *arch, BinArgs b, uint32_t vec2) {
+  __shared__ BinLds<4u, false> s_bin;
+  bins_begin(s_bin);
   const uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t i0 = 2 * q, i1 = 2 * q + 1;
   const bool has0 = i0 < n_beads, has1 = i1 < n_beads;
@@ -277,21 +343,22 @@ __global__ __launch_bounds__(256) void density_hist_binned_kernel(
   const uint32_t v0 = (has1 && same) ? (h0 | (h1 << 16)) : h0;
   const uint32_t v1 = h1 << 16;
   // a lane without bead 2q has only bead 2q+1 absent too (n_beads is the end)
-  bin_append<COUNT64>(b, g, counts, wave_sub_bin(blockDim.x >> 6), k0 >> 11, k1 >> 11, 0u, 0u,
-                      v0, v1, 0u, 0u, want);
+  bin_append<COUNT64>(s_bin, b, g, counts, 4u, k0 >> 11, k1 >> 11, 0u, 0u, v0, v1, 0u, 0u, want);
 }
 
-// Applies the bins to the counts: one workgroup of kApplyThreads per brick.
+// Applies the bins to the counts: one workgroup of THREADS per brick.
 // The brick's count words (every plane) are staged in LDS, the bin's updates
 // added with LDS atomics, the words written back, and the bin emptied for the
 // next sweep.  The sub-bins' fill levels load together with the counts, and
 // their entries are taken as one flat index range, kApplyBatch independent
 // loads per thread at a time, so that a block waits on memory a few times
 // rather than twice per sub-bin.
+// 512 threads where the bricks are few and every round trip counts (a film of 450
+// bricks: 11.5 us with the fields, 16.8 with 256), 256 where there are enough
+// of them to fill the device (13,824 bricks: 152 us, 157 with 512).
 // LDS: planes x 2048 words (u16 pairs) or 2 x planes x 2048 halves (u32 pairs).
-constexpr uint32_t kApplyThreads = 256u;
+constexpr uint32_t kApplyWide = 512u, kApplyNarrow = 256u;
 constexpr uint32_t kApplyBatch = 4u;
-constexpr uint32_t kApplyPerThread = kBrickCells / kApplyThreads;   // cells per thread and plane
 
 template <bool COUNT64>
 __device__ __forceinline__ void apply_entry_lds(uint32_t *s_cnt, uint32_t planes, uint32_t e) {
@@ -312,35 +379,55 @@ __device__ __forceinline__ void apply_entry_lds(uint32_t *s_cnt, uint32_t planes
   }
 }
 
-// The body of one brick's workgroup (s_cnt: the dynamic LDS of the counts).
-template <bool COUNT64>
-__device__ __forceinline__ void bin_apply_brick(const BinArgs &b, const Grid &g, void *counts,
-                                                uint32_t planes, uint32_t brick, uint32_t *s_cnt) {
-  __shared__ uint32_t s_fill[kSubBins];
-  const uint32_t tid = threadIdx.x;
-  uint32_t fill = 0u;
-  if (tid < kSubBins) fill = b.bin_count[(brick << kSubShift) | tid];
+// Origin of a brick.
+__device__ __forceinline__ void brick_origin(const BinArgs &b, uint32_t brick, uint32_t &x0,
+                                             uint32_t &y0, uint32_t &z0) {
   const uint32_t bx = brick % b.nbx, rest = brick / b.nbx;
   const uint32_t by = rest % b.nby, bz = rest / b.nby;
-  const uint32_t x0 = bx * 16u, y0 = by * 16u, z0 = bz * 8u;
-  // cell l = tid + u * kApplyThreads of the brick: a thread keeps x = x0 + (tid & 15)
-  const uint32_t x = x0 + (tid & 15u);
+  x0 = bx * 16u;
+  y0 = by * 16u;
+  z0 = bz * 8u;
+}
+
+// The brick's counts with its bin's updates added, in LDS (s_cnt), and the bin
+// emptied; ends with a barrier.  Cell l = tid + u THREADS of the brick is
+// (x0 + (l & 15), y0 + ((l >> 4) & 15), z0 + (l >> 8)).
+// NT: counts and entries are read with the non-temporal hint.
+template <bool NT, class T>
+__device__ __forceinline__ T load_hint(const T *p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+template <bool COUNT64, uint32_t THREADS, bool NT = false>
+__device__ __forceinline__ void bin_gather_brick(const BinArgs &b, const Grid &g, const void *counts,
+                                                 uint32_t planes, uint32_t brick, uint32_t *s_cnt) {
+  __shared__ uint32_t s_fill[kSubBins];
+  const uint32_t tid = threadIdx.x, n_sub = 1u << b.sub_shift;
+  uint32_t fill = 0u;
+  if (tid < n_sub) fill = b.bin_count[(brick << b.sub_shift) | tid];
+  uint32_t x0, y0, z0;
+  brick_origin(b, brick, x0, y0, z0);
+  const uint32_t x = x0 + (tid & 15u), y = y0 + ((tid >> 4) & 15u);
+  constexpr uint32_t kPer = kBrickCells / THREADS;   // cells per thread and plane
   for (uint32_t p = 0; p < planes; ++p) {
-    uint2 v[kApplyPerThread];
+    uint2 v[kPer];
 #pragma unroll
-    for (uint32_t u = 0; u < kApplyPerThread; ++u) {
-      const uint32_t l = tid + u * kApplyThreads;
-      const uint32_t y = y0 + ((l >> 4) & 15u), z = z0 + (l >> 8);
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint32_t z = z0 + ((tid + u * THREADS) >> 8);
       v[u] = make_uint2(0u, 0u);
       if (x < (uint32_t)g.nx && y < (uint32_t)g.ny && z < (uint32_t)g.nz) {
         const size_t w = (size_t)p * g.n_cells + ((size_t)z * g.ny + y) * g.nx + x;
-        if (COUNT64) v[u] = reinterpret_cast<const uint2 *>(counts)[w];
-        else v[u].x = reinterpret_cast<const uint32_t *>(counts)[w];
+        if (COUNT64) {
+          const unsigned long long q = load_hint<NT>(reinterpret_cast<const unsigned long long *>(counts) + w);
+          v[u] = make_uint2((uint32_t)q, (uint32_t)(q >> 32));
+        } else {
+          v[u].x = load_hint<NT>(reinterpret_cast<const uint32_t *>(counts) + w);
+        }
       }
     }
 #pragma unroll
-    for (uint32_t u = 0; u < kApplyPerThread; ++u) {
-      const uint32_t i = p * kBrickCells + tid + u * kApplyThreads;
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint32_t i = p * kBrickCells + tid + u * THREADS;
       if (COUNT64) reinterpret_cast<uint2 *>(s_cnt)[i] = v[u];
       else s_cnt[i] = v[u].x;
     }
@@ -355,12 +442,12 @@ __device__ __forceinline__ void bin_apply_brick(const BinArgs &b, const Grid &g,
     start[s] = total;
     total += s_fill[s];
   }
-  const uint32_t *bins = b.bins + (size_t)(brick << kSubShift) * b.cap;
-  for (uint32_t j0 = 0; j0 < total; j0 += kApplyBatch * kApplyThreads) {
+  const uint32_t *bins = b.bins + (size_t)(brick << b.sub_shift) * b.cap;
+  for (uint32_t j0 = 0; j0 < total; j0 += kApplyBatch * THREADS) {
     uint32_t e[kApplyBatch];
 #pragma unroll
     for (uint32_t u = 0; u < kApplyBatch; ++u) {
-      const uint32_t j = j0 + u * kApplyThreads + tid;
+      const uint32_t j = j0 + u * THREADS + tid;
       e[u] = 0u;
       if (j < total) {
         uint32_t sb = 0u, base = 0u;
@@ -370,21 +457,34 @@ __device__ __forceinline__ void bin_apply_brick(const BinArgs &b, const Grid &g,
           sb = past ? s : sb;
           base = past ? start[s] : base;
         }
-        e[u] = bins[(size_t)sb * b.cap + (j - base)];
+        e[u] = load_hint<NT>(bins + (size_t)sb * b.cap + (j - base));
       }
     }
 #pragma unroll
     for (uint32_t u = 0; u < kApplyBatch; ++u) apply_entry_lds<COUNT64>(s_cnt, planes, e[u]);
   }
   __syncthreads();
+  if (tid < n_sub) b.bin_count[(brick << b.sub_shift) | tid] = 0u;
+}
+
+// The body of one brick's workgroup (s_cnt: the dynamic LDS of the counts).
+template <bool COUNT64, uint32_t THREADS>
+__device__ __forceinline__ void bin_apply_brick(const BinArgs &b, const Grid &g, void *counts,
+                                                uint32_t planes, uint32_t brick, uint32_t *s_cnt) {
+  bin_gather_brick<COUNT64, THREADS>(b, g, counts, planes, brick, s_cnt);
+  const uint32_t tid = threadIdx.x;
+  uint32_t x0, y0, z0;
+  brick_origin(b, brick, x0, y0, z0);
+  const uint32_t x = x0 + (tid & 15u), y = y0 + ((tid >> 4) & 15u);
+  constexpr uint32_t kPer = kBrickCells / THREADS;   // cells per thread and plane
+  if (x >= (uint32_t)g.nx || y >= (uint32_t)g.ny) return;
   for (uint32_t p = 0; p < planes; ++p) {
 #pragma unroll
-    for (uint32_t u = 0; u < kApplyPerThread; ++u) {
-      const uint32_t l = tid + u * kApplyThreads;
-      const uint32_t y = y0 + ((l >> 4) & 15u), z = z0 + (l >> 8);
-      if (x < (uint32_t)g.nx && y < (uint32_t)g.ny && z < (uint32_t)g.nz) {
+    for (uint32_t u = 0; u < kPer; ++u) {
+      const uint32_t z = z0 + ((tid + u * THREADS) >> 8);
+      if (z < (uint32_t)g.nz) {
         const size_t w = (size_t)p * g.n_cells + ((size_t)z * g.ny + y) * g.nx + x;
-        const uint32_t i = p * kBrickCells + l;
+        const uint32_t i = p * kBrickCells + tid + u * THREADS;
         if (COUNT64)
           reinterpret_cast<uint2 *>(counts)[w] = reinterpret_cast<const uint2 *>(s_cnt)[i];
         else
@@ -392,14 +492,13 @@ __device__ __forceinline__ void bin_apply_brick(const BinArgs &b, const Grid &g,
       }
     }
   }
-  if (tid < kSubBins) b.bin_count[(brick << kSubShift) | tid] = 0u;
 }
 
-template <bool COUNT64>
-__global__ __launch_bounds__(kApplyThreads) void bin_apply_kernel(BinArgs b, Grid g, void *counts,
-                                                                  uint32_t planes) {
+template <bool COUNT64, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS) void bin_apply_kernel(BinArgs b, Grid g, void *counts,
+                                                            uint32_t planes) {
   extern __shared__ uint32_t s_cnt[];
-  bin_apply_brick<COUNT64>(b, g, counts, planes, blockIdx.x, s_cnt);
+  bin_apply_brick<COUNT64, THREADS>(b, g, counts, planes, blockIdx.x, s_cnt);
 }
 
 }  // namespace soma

@@ -218,12 +218,37 @@ __device__ __forceinline__ void load4(const void *counts, uint32_t q,
   }
 }
 
+// The block's sums (up to eight waves) as partial `blk`: wave shuffles, then through
+// LDS in the order of the waves.
+__device__ __forceinline__ void field_partials(FieldPartials *p, uint32_t blk,
+                                               unsigned long long sum_a, unsigned long long sum_b,
+                                               double h) {
+  __shared__ unsigned long long s_a[8], s_b[8];
+  __shared__ double s_h[8];
+  for (int off = 32; off > 0; off >>= 1) {
+    sum_a += __shfl_down(sum_a, off, 64);
+    sum_b += __shfl_down(sum_b, off, 64);
+    h += __shfl_down(h, off, 64);
+  }
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (uint32_t w = 1; w < blockDim.x >> 6; ++w) {
+      sum_a += s_a[w];
+      sum_b += s_b[w];
+      h += s_h[w];
+    }
+    p->sum_a[blk] = sum_a;
+    p->sum_b[blk] = sum_b;
+    p->h_nb[blk] = h;
+  }
+}
+
 // Block `blk` of the `nblk` blocks that serve one grid: a grid-stride loop
 // over groups of four cells, then the block's partial sums (FP64 H_nb).
 template <bool COUNT64, bool NT = false>
 __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uint32_t nblk) {
-  __shared__ unsigned long long s_a[4], s_b[4];
-  __shared__ double s_h[4];
   const uint32_t n4 = a.n_cells >> 2;
   const uint32_t stride = nblk * blockDim.x;
   const uint32_t tid = blk * blockDim.x + threadIdx.x;
@@ -307,20 +332,7 @@ __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uin
     }
   }
   if (!stats) return;
-  // block reduction: wave shuffles, then four waves through LDS
-  for (int off = 32; off > 0; off >>= 1) {
-    sum_a += __shfl_down(sum_a, off, 64);
-    sum_b += __shfl_down(sum_b, off, 64);
-    h += __shfl_down(h, off, 64);
-  }
-  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
-  if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    a.partials->sum_a[blk] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    a.partials->sum_b[blk] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-    a.partials->h_nb[blk] = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
-  }
+  field_partials(a.partials, blk, sum_a, sum_b, h);
 }
 
 template <bool COUNT64, bool NT = false>
@@ -434,8 +446,6 @@ template <bool COUNT64, uint32_t NT>
 __global__ __launch_bounds__(256) void field_multi_kernel(const MultiFieldArgs a) {
   constexpr uint32_t NP = (NT + 1u) / 2u;   // count planes
   advance_counter(a.ctr, a.ctr_by, blockIdx.x);
-  __shared__ unsigned long long s_a[4], s_b[4];
-  __shared__ double s_h[4];
   const bool stats = a.partials != nullptr;
   const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
   unsigned long long sum_a = 0, sum_b = 0;
@@ -492,19 +502,7 @@ __global__ __launch_bounds__(256) void field_multi_kernel(const MultiFieldArgs a
     }
   }
   if (!stats) return;
-  for (int off = 32; off > 0; off >>= 1) {
-    sum_a += __shfl_down(sum_a, off, 64);
-    sum_b += __shfl_down(sum_b, off, 64);
-    h += __shfl_down(h, off, 64);
-  }
-  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
-  if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    a.partials->sum_a[blockIdx.x] = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    a.partials->sum_b[blockIdx.x] = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-    a.partials->h_nb[blockIdx.x] = ((s_h[0] + s_h[1]) + s_h[2]) + s_h[3];
-  }
+  field_partials(a.partials, blockIdx.x, sum_a, sum_b, h);
 }
 
 // Per-type totals of the counts: block b writes out[b * kMaxTypes + t].

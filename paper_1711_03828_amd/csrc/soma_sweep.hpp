@@ -18,6 +18,8 @@
 // bit-identical to counting the final positions from scratch.
 #pragma once
 
+#include <type_traits>
+
 #include "soma_bins.hpp"
 #include "soma_device.hpp"
 #include "soma_mlp.hpp"
@@ -301,6 +303,11 @@ __device__ __forceinline__ void finish_block(const SweepArgs &a, uint32_t n_acc)
   __syncthreads();
 }
 
+// The LDS of a kernel's binned count updates, or a placeholder without them.
+struct NoBins {};
+template <bool BINNED, uint32_t WAVES, bool WAVEWISE>
+using BinSlot = std::conditional_t<BINNED, BinLds<WAVES, WAVEWISE>, NoBins>;
+
 // Order of the two sets for this chain and sweep: bit 0 of the first word of
 // bead 0's draw, broadcast from the chain's first lane (the displacement uses
 // only bits 9..31 of that word).
@@ -402,9 +409,9 @@ __device__ __forceinline__ void trial_gather(const SweepArgs &a, uint32_t pla, T
 // One wave's tile of local moves: positions r0/r1 already loaded for lane map m.
 // EVEN: every chain has an even number of beads, so a lane's two beads both
 // exist where the lane is active.
-template <bool COUNT64, bool EVEN, bool BINNED, bool NT = false>
+template <bool COUNT64, bool EVEN, bool BINNED, bool NT = false, class Bins>
 __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap &m, float *cp,
-                                               F3 r0, F3 r1) {
+                                               F3 r0, F3 r1, Bins &bins) {
   const uint32_t i0 = 2u * m.k;
   const uint32_t gchain = a.chain_base + m.chain;
   const Rand4 w0 = philox(gchain, i0 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
@@ -468,9 +475,9 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
   }
   store_pair<EVEN, NT>(cp, m, sel(odd_first, rb, ra), sel(odd_first, ra, rb));
   const bool mv_a = acc_a & (A.n != A.c), mv_b = acc_b & (B.n != B.c);
-  if (BINNED) {
-    bin_moves<COUNT64>(a.bin, a.grid, a.counts, wave_sub_bin(a.wpb), kfa, kta, ta ? 1u : 0u, mv_a,
-                       kfb, ktb, tb ? 1u : 0u, mv_b);
+  if constexpr (BINNED) {
+    bin_moves<COUNT64>(bins, a.bin, a.grid, a.counts, a.wpb, kfa, kta, ta ? 1u : 0u, mv_a, kfb, ktb,
+                       tb ? 1u : 0u, mv_b);
   } else {
     if (mv_a) move_count<COUNT64>(a.counts, A.c, A.n, ta);
     if (mv_b) move_count<COUNT64>(a.counts, B.c, B.n, tb);
@@ -488,13 +495,15 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
 template <bool COUNT64, bool VEC2, bool BINNED, bool PERSIST = false, bool NT = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5)))
 void mc_sweep_local_kernel(const SweepArgs a_in) {
+  __shared__ BinSlot<BINNED, 8u, PERSIST> s_bin;
+  if constexpr (BINNED) bins_begin(s_bin);
   const SweepArgs a = resolve_sweep(a_in, 0u);
   if (!PERSIST) {   // one tile per wave
     const LaneMap m = lane_map(a);
     float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
     F3 r0, r1;
     load_pair<VEC2, NT>(cp, m, r0, r1);
-    finish_block(a, local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1));
+    finish_block(a, local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1, s_bin));
     return;
   }
   const TileIter it = tile_iter(a);
@@ -506,7 +515,7 @@ void mc_sweep_local_kernel(const SweepArgs a_in) {
     float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
     F3 r0, r1;
     load_pair<VEC2, NT>(cp, m, r0, r1);
-    n_acc += local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1);
+    n_acc += local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1, s_bin);
     t = tile_of(it, vn);
   }
   finish_block(a, n_acc);
@@ -559,8 +568,8 @@ __device__ __forceinline__ float field_and_grad(const SweepArgs &a, uint32_t pl,
 // then cancel in the Metropolis-Hastings ratio, which leaves
 // exp(-(omega(c') - omega(c))/N).  Same draws as smart MC.
 // ---------------------------------------------------------------------------
-template <bool COUNT64, bool VEC2, bool BINNED, bool GIBBS = false>
-__device__ __forceinline__ uint32_t smc_wave(const SweepArgs &a, const LaneMap &m) {
+template <bool COUNT64, bool VEC2, bool BINNED, bool GIBBS = false, class Bins>
+__device__ __forceinline__ uint32_t smc_wave(const SweepArgs &a, const LaneMap &m, Bins &bins) {
   const uint32_t N = a.n;
   const uint32_t i0 = 2u * m.k, i1 = i0 + 1u;
   float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * N * 3u + 6u * m.k;
@@ -693,9 +702,9 @@ __device__ __forceinline__ uint32_t smc_wave(const SweepArgs &a, const LaneMap &
   }
 
   store_pair<VEC2>(cp, m, r0, r1);
-  if (BINNED) {
-    bin_moves<COUNT64>(a.bin, a.grid, a.counts, wave_sub_bin(a.wpb), from0, to0, b0 ? 1u : 0u,
-                       moved0, from1, to1, b1 ? 1u : 0u, moved1);
+  if constexpr (BINNED) {
+    bin_moves<COUNT64>(bins, a.bin, a.grid, a.counts, a.wpb, from0, to0, b0 ? 1u : 0u, moved0, from1,
+                       to1, b1 ? 1u : 0u, moved1);
   } else {
     if (moved0) move_count<COUNT64>(a.counts, from0, to0, b0);
     if (moved1) move_count<COUNT64>(a.counts, from1, to1, b1);
@@ -707,8 +716,10 @@ __device__ __forceinline__ uint32_t smc_wave(const SweepArgs &a, const LaneMap &
 // persistent grid (SweepArgs::queue).
 template <bool COUNT64, bool VEC2, bool BINNED, bool GIBBS, bool PERSIST>
 __device__ __forceinline__ void smc_tiles(const SweepArgs &a) {
+  __shared__ BinSlot<BINNED, 8u, PERSIST> s_bin;
+  if constexpr (BINNED) bins_begin(s_bin);
   if (!PERSIST) {   // one tile per wave
-    finish_block(a, smc_wave<COUNT64, VEC2, BINNED, GIBBS>(a, lane_map(a)));
+    finish_block(a, smc_wave<COUNT64, VEC2, BINNED, GIBBS>(a, lane_map(a), s_bin));
     return;
   }
   const TileIter it = tile_iter(a);
@@ -716,7 +727,7 @@ __device__ __forceinline__ void smc_tiles(const SweepArgs &a) {
   uint32_t t = tile_of(it, tile_draw(it));
   while (t < it.t_end) {
     const uint32_t vn = tile_draw(it);
-    n_acc += smc_wave<COUNT64, VEC2, BINNED, GIBBS>(a, lane_map_tile(a, t, true));
+    n_acc += smc_wave<COUNT64, VEC2, BINNED, GIBBS>(a, lane_map_tile(a, t, true), s_bin);
     t = tile_of(it, vn);
   }
   finish_block(a, n_acc);
@@ -764,10 +775,10 @@ struct MixArgs {
 // network outputs ([64][8] floats), sw the block's LDS copy of the network's
 // weights.  Returns through cnt the wave's accepted local moves, accepted
 // learned moves and learned attempts.
-template <bool COUNT64, bool VEC2, bool BINNED>
+template <bool COUNT64, bool VEC2, bool BINNED, class Bins>
 __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx, const LaneMap &m,
                                            __bf16 *act, float *zb, const __bf16 *sw,
-                                           uint32_t cnt[3]) {
+                                           uint32_t cnt[3], Bins &bins) {
   __bf16 *row = act + m.lane * kActStride;
   const uint32_t N = a.n;
   const uint32_t i0 = 2u * m.k, i1 = i0 + 1u;
@@ -881,9 +892,8 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
     n_att_l += (uint32_t)__popcll(__ballot(learned));
   }
   store_pair<VEC2>(cp, m, r0, r1);
-  if (BINNED) {
-    bin_moves<COUNT64>(a.bin, a.grid, a.counts, wave_sub_bin(a.wpb),
-                       cell_brick_key(a.bin, a.grid, from0),
+  if constexpr (BINNED) {
+    bin_moves<COUNT64>(bins, a.bin, a.grid, a.counts, a.wpb, cell_brick_key(a.bin, a.grid, from0),
                        cell_brick_key(a.bin, a.grid, to0), b0 ? 1u : 0u, moved0,
                        cell_brick_key(a.bin, a.grid, from1), cell_brick_key(a.bin, a.grid, to1),
                        b1 ? 1u : 0u, moved1);
@@ -923,13 +933,16 @@ __global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_i
   __shared__ __bf16 s_act[4][64 * kActStride];
   __shared__ float s_z[4][64 * 8];
   __shared__ __bf16 s_w[kWRows * kWStride];
+  __shared__ BinSlot<BINNED, 4u, PERSIST> s_bin;
+  if constexpr (BINNED) bins_begin(s_bin);
   net_weights_to_lds(mx.net, s_w);
   __syncthreads();
   const SweepArgs a = resolve_sweep(a_in, 0u);
   const uint32_t wib = threadIdx.x >> 6;
   uint32_t cnt[3] = {0u, 0u, 0u};
   if (!PERSIST) {   // one tile per wave
-    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map(a), s_act[wib], s_z[wib], s_w, cnt);
+    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map(a), s_act[wib], s_z[wib], s_w, cnt,
+                                      s_bin);
     mixed_finish(a, mx, cnt);
     return;
   }
@@ -940,7 +953,7 @@ __global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_i
     const uint32_t vn = tile_draw(it);
     uint32_t c[3];
     mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map_tile(a, t, true), s_act[wib], s_z[wib],
-                                      s_w, c);
+                                      s_w, c, s_bin);
     cnt[0] += c[0];
     cnt[1] += c[1];
     cnt[2] += c[2];

@@ -139,6 +139,60 @@ def test_binned_graph_replays_equal_eager_cycles(orc):
     graph.close()
 
 
+@pytest.mark.parametrize("kind,width,n,option", [
+    ("gibbs", 16, 32, "walls"), ("gibbs", 32, 31, "substeps"), ("smc", 32, 32, "grad"),
+    ("smc", 16, 17, "captured"), ("local", 16, 45, "ext"), ("local", 32, 32, "captured")])
+def test_default_mode_with_many_updates_equals_atomics(orc, kind, width, n, option):
+    """Sweeps whose expected updates send the default mode through the bins (with the fields
+    refreshed by the kernel that applies them), against the same cycles with atomics (a grid limit
+    of its own, never reached, keeps them): the same bits, on a ragged grid."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Melt
+    grid = (45, 37, 29)
+    chains = 900_000 // n
+    sp = [Species(chains, n, n // 2)]
+    k0 = np.float32(3.0 * 31 / 36.0)
+    pos = synth.gaussian_walks(41, chains, n, grid, 1 / math.sqrt(float(k0)))
+    if option == "walls":   # keep the start out of the wall plane z = 0
+        z = np.mod(pos[:, 2], np.float32(grid[2]))
+        pos[:, 2] = np.where(z < 1, z + np.float32(1), z)
+    cfg = custom_config(grid, sp, k0=k0, n_ref=32, chi_n=25.0, kappa_n=50.0, local_a=0.45,
+                        smc_a=0.05625, count_width=width, seed=6)
+    move = {"local": C.SOMA_MOVE_LOCAL, "smc": C.SOMA_MOVE_SMC, "gibbs": C.SOMA_MOVE_GIBBS}[kind]
+    melts = [Melt(cfg, positions=torch.from_numpy(pos)) for _ in range(2)]
+    C.soma_set_sweep_blocks(melts[1].handle, 1 << 30)
+    ext = torch.from_numpy(synth.uniform_field(7, melts[0].n_cells, -2.0, 2.0)).cuda()
+    mask = torch.from_numpy(synth.pack_mask(synth.wall_cells(grid, [0])).view(np.int32)).cuda()
+    flush("case", kind, width, n, option)
+    for m in melts:
+        if option in ("walls", "ext"):
+            m.set_external(ext, mask if option == "walls" else None)
+        if option == "grad":
+            m.keep_grad_field()
+        if option == "substeps":
+            m.set_substeps(2)
+        if option == "captured":
+            m.capture_cycle(3, move)
+    for rep in range(3):
+        for m in melts:
+            if option == "captured":
+                m.run_cycle(1)
+            else:
+                m.cycle(3, move)
+        torch.cuda.synchronize()
+        a, b = melts
+        assert torch.equal(a.pos, b.pos) and torch.equal(a.counts, b.counts), rep
+        assert torch.equal(a.omega, b.omega), rep
+        oa, ob = a.observables(), b.observables()
+        assert oa.h_nb == pytest.approx(ob.h_nb, rel=1e-12)
+        assert (oa.count_a, oa.count_b, list(oa.accepted)) == (ob.count_a, ob.count_b, list(ob.accepted))
+        assert oa.counts_conserved == 1 and oa.error_flags == 0
+    np.testing.assert_array_equal(melts[0].counts_planes(), _recount(orc, melts[0], sp, grid))
+    for m in melts:
+        m.sweep(2, move)
+    _compare(orc, melts[1], melts[0], sp, grid, "two sweeps")
+
+
 def test_binned_fullsize_equals_direct():
     """134,217,728 beads on 384x384x192 cells, 32-bit counts: one local sweep
     and one smart-MC sweep in each mode from the same state; positions and
