@@ -58,11 +58,12 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
   for (; item < end; item += stride) {   // block-uniform loop
     const uint32_t sg = range_of(L.seg_first, L.n_segs, item);
     if constexpr (BINNED) bins_begin(s_bin);
-    SweepArgs a = resolve_sweep(L.segs[sg].a, L.sweep_off);
+    SweepArgs a = load_uniform(&L.segs[sg].a);
+    a.sweep += L.sweep_off + load_uniform(a.sweep_ctr);
     a.sub_k = L.sub_k;
     a.sub_j = L.sub_j;
     a.n_sub = a.n_chains > L.sub_j ? (a.n_chains - L.sub_j + L.sub_k - 1u) / L.sub_k : 0u;
-    const uint32_t tile = (item - L.seg_first[sg]) * 4u + (threadIdx.x >> 6);
+    const uint32_t tile = (item - load_uniform(L.seg_first + sg)) * 4u + (threadIdx.x >> 6);
     const LaneMap m = lane_map_tile(a, tile, true);
     if (KIND == 0) {
       float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(256, 2) void batched_sweep_kernel(const BatchLaunch
     } else if (KIND == 3) {
       finish_block(a, smc_wave<COUNT64, VEC2, BINNED, true>(a, m, s_bin));
     } else {
-      const MixArgs mx = L.segs[sg].mx;
+      const MixArgs mx = load_uniform(&L.segs[sg].mx);
       if (sg != net_sg) {   // block-uniform: a new segment's network
         __syncthreads();
         net_weights_to_lds(mx.net, s_w);
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(kApplyWide) void batched_bin_apply_kernel(
     uint32_t n_sys) {
   extern __shared__ uint32_t s_cnt[];
   const uint32_t s = range_of(brick_first, n_sys, blockIdx.x);
-  const BinApplySeg x = segs[s];
-  bin_apply_brick<COUNT64, kApplyWide>(x.b, x.g, x.counts, 1u, blockIdx.x - brick_first[s], s_cnt);
+  const BinApplySeg x = load_uniform(segs + s);
+  bin_apply_brick<COUNT64, kApplyWide>(x.b, x.g, x.counts, 1u, blockIdx.x - load_uniform(brick_first + s), s_cnt);
 }
 
 }  // namespace soma

@@ -543,15 +543,34 @@ __global__ __launch_bounds__(256) void type_count_kernel(const void *counts, uin
 }
 
 // Blocks of the grid-field update for a number of systems are given out in
-// contiguous ranges: system s owns blocks [first[s], first[s+1]).
+// contiguous ranges: system s owns blocks [first[s], first[s+1]).  The largest s
+// with first[s] <= x: the wave compares 64 entries at once (a binary search is
+// a chain of dependent loads, six round trips for 64 systems, before a block can
+// start).  Wave-uniform.
 __device__ __forceinline__ uint32_t range_of(const uint32_t *first, uint32_t n, uint32_t x) {
-  uint32_t lo = 0, hi = n;  // first[lo] <= x < first[hi]
-  while (hi - lo > 1u) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (first[mid] <= x) lo = mid;
-    else hi = mid;
+  uint32_t s = 0u;
+  for (uint32_t i = 1u; i < n; i += 64u) {
+    const uint32_t k = i + __lane_id();
+    s += (uint32_t)__popcll(__ballot(k < n && first[min(k, n - 1u)] <= x));
   }
-  return lo;
+  return s;
+}
+
+// A record at a wave-uniform address that nothing writes while the kernel runs,
+// through the scalar cache (constant address space).  Its fields stay in scalar
+// registers; as ordinary loads they would take vector registers and the vector
+// memory path, since the kernel stores through other pointers.
+template <class T>
+__device__ __forceinline__ T load_uniform(const T *p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) uint32_t *ConstWords;
+  const ConstWords q = (ConstWords)(uintptr_t)p;
+  uint32_t w[sizeof(T) / 4];
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(T) / 4; ++i) w[i] = q[i];
+  T t;
+  __builtin_memcpy(&t, w, sizeof t);
+  return t;
 }
 
 template <bool COUNT64>
@@ -560,8 +579,9 @@ __global__ __launch_bounds__(256) void batched_field_kernel(const FieldArgs *fa,
                                                             uint32_t *const *ctrs,
                                                             uint32_t ctr_by) {
   const uint32_t s = range_of(first, n_sys, blockIdx.x);
-  if (ctr_by) advance_counter(ctrs[s], ctr_by, blockIdx.x - first[s]);
-  field_body<COUNT64>(fa[s], blockIdx.x - first[s], first[s + 1] - first[s]);
+  const uint32_t f0 = load_uniform(first + s), f1 = load_uniform(first + s + 1u);
+  if (ctr_by) advance_counter(ctrs[s], ctr_by, blockIdx.x - f0);
+  field_body<COUNT64>(load_uniform(fa + s), blockIdx.x - f0, f1 - f0);
 }
 
 // Halo copy of the fields rebuilt from the field planes (after the caller has
