@@ -482,7 +482,8 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
  * grid_blocks 0 (one block per item, default) or a persistent grid. */
 int32_t soma_batch_set_launch(soma_batch *b, uint32_t mode, uint32_t grid_blocks);
 /* Count updates of batched sweeps (Eq. (4), Sec. 3.1.1), as soma_set_histogram
- * for one system: SOMA_HIST_DIRECT (default) or SOMA_HIST_BINNED, where each
+ * for one system: SOMA_HIST_DIRECT (default; device atomics, or the bins for
+ * sweeps expected to make many updates) or SOMA_HIST_BINNED, where each
  * sweep appends to the bins of every system's own workspace and one more launch
  * applies all of them brick by brick (mixed sweeps of a batch keep direct
  * atomics).  Counts, fields and trajectories are the same bits either way.  SOMA_E_UNSUPPORTED for SOMA_HIST_BINNED unless every

@@ -278,9 +278,6 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.inv_rho = inv_rho_f(d);
   a.chi_n = c->chi_n;
   a.kappa_n = c->kappa_n;
-  a.inv_rho_d = inv_rho_d(d);
-  a.chi_n_d = (double)c->chi_n;
-  a.kappa_n_d = (double)c->kappa_n;
   a.partials = partials;
   a.clear = 0;
   a.halo = d.halo_plane ? halo : nullptr;
@@ -520,6 +517,16 @@ struct soma_system {
 
 namespace {
 
+// sum over the free cells of kappaN/2 (phi_A + phi_B - 1)^2 plus the interaction
+// term (Eqs. (5), (6), (8); phi = n / rho_bar) from the integer sums of the last
+// refresh; extended precision, as the three parts of the square nearly cancel.
+double h_nb_sum(const soma_system *sys, const soma::Totals &t) {
+  const long double r = inv_rho_d(sys->d), n1 = t.n1, n2 = t.n2, nab = t.nab;
+  const long double square = r * r * n2 - 2.0L * r * n1 + (long double)sys->d.n_free;
+  const long double inter = sys->d.form == 0 ? -0.25L * (n2 - 4.0L * nab) : nab;
+  return (double)(0.5L * (long double)sys->cfg.kappa_n * square + (long double)sys->cfg.chi_n * r * r * inter);
+}
+
 // The system's recount goes through the bins whenever its grid has them.
 int32_t launch_hist_sys(soma_system *sys, hipStream_t s) {
   soma::BinArgs b;
@@ -675,18 +682,11 @@ bool species_vec2(const soma_system *sys, uint32_t sp) {
 // Chains sub_j, sub_j + sub_k, ... of a species of n chains.
 uint32_t subset_size(uint32_t n, uint32_t k, uint32_t j) { return n > j ? (n - j + k - 1) / k : 0u; }
 
-// Whether a sweep of chain subset j of k in the default histogram mode sends its
-// count updates through the bins: where their atomics are expected to take longer
-// than the bins do.  Measured: 23 ps per memory-side atomic (two per bead that
-// changes cell); the bins cost about 10 us a launch (their part of the kernel that
-// applies them and of the sweep's barriers), a pass over the counts, and 0.1 ns
-// per wave.  Per SCMF cycle, atomics against bins, 256-thread blocks: 24^3 cells,
-// 33k beads 8.1 / 12.5 us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71;
-// film of 16M beads 170 / 161; bond-Gibbs moves of 1M beads 61 / 31; smart-MC moves
-// of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their blocks' LDS is full:
-// 978 / 1018 us), and so do persistent grids, whose waves reserve room one by one.
-bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
-  if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED || sys->sweep_blocks) return false;
+// Expected seconds of the count updates of a sweep of chain subset j of k, as
+// memory-side atomics and through the bins (without the bins' cost per launch),
+// added to what is there.
+void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j, double &atomics,
+                     double &bins) {
   const soma_config *c = &sys->cfg;
   double moved = 0.0, waves = 0.0;
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
@@ -701,8 +701,26 @@ bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
     moved += chains * S.n * (1.0 - stay * stay * stay);
     waves += chains / (64u / ((S.n + 1u) / 2u));
   }
-  const double atomics = 2.0 * 23e-12 * moved;
-  const double bins = 10e-6 + (double)sys->d.counts_bytes / 2e12 + 1e-10 * waves;
+  atomics += 2.0 * 23e-12 * moved;
+  bins += (double)sys->d.counts_bytes / 2e12 + 1e-10 * waves;
+}
+constexpr double kBinsPerLaunch = 10e-6;
+
+// Whether a sweep in the default histogram mode sends its count updates through
+// the bins: where their atomics are expected to take longer than the bins do.
+// Measured: 23 ps per memory-side atomic (two per bead that changes cell); the
+// bins cost about 10 us a launch (their part of the kernel that applies them and
+// of the sweep's barriers), a pass over the counts, and 0.1 ns per wave.  Per SCMF
+// cycle, atomics against bins, 256-thread blocks: 24^3 cells, 33k beads 8.1 / 12.5
+// us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71; film of 16M beads
+// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 57; bond-Gibbs moves of 1M beads
+// 61 / 31; smart-MC moves of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their
+// blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
+// system, whose waves reserve room one by one.
+bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
+  if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED || sys->sweep_blocks) return false;
+  double atomics = 0.0, bins = kBinsPerLaunch;
+  add_update_cost(sys, kind, k, j, atomics, bins);
   return atomics > bins;
 }
 
@@ -1418,7 +1436,7 @@ int32_t soma_observables(soma_system *sys, soma_obs *out, void *stream) {
   out->b2_sum = t.b2;
   out->e_bond = t.e_bond;
   out->e_field = t.e_field;
-  out->h_nb = t.h_nb / (inv_rho_d(sys->d) * (double)c->n_ref);
+  out->h_nb = (sys->d.n_types > 2 ? t.h_nb : h_nb_sum(sys, t)) / (inv_rho_d(sys->d) * (double)c->n_ref);
   out->error_flags = t.err;
   out->counts_conserved =
       (t.sum_a == sys->d.n_a_total && t.sum_b == sys->d.n_beads - sys->d.n_a_total) ? 1u : 0u;
@@ -1929,11 +1947,12 @@ struct soma_batch {
   uint32_t mode = 0, grid_blocks = 0;  // launch shape (results do not depend on it)
   // binned count updates: every system's own bins, one apply launch for all
   uint32_t hist = 0;                    // soma::kHistDirect or soma::kHistBinned
+  bool hist_auto = true;                // direct mode: the bins where they pay
   bool bins_ok = false;                 // every system has bins and two bead types
   std::vector<soma::BinApplySeg> apply;
-  std::vector<uint32_t> brick_first;
+  std::vector<uint32_t> brick_first, af_first;   // blocks of the apply and of the apply + field launch
   soma::BinApplySeg *d_apply = nullptr;
-  uint32_t *d_brick_first = nullptr;
+  uint32_t *d_brick_first = nullptr, *d_af_first = nullptr;
   uint32_t substeps = 1;                // chain subsets per cycle (field refresh after each)
   CycleGraph graph;
   ~soma_batch() { graph.release(); }
@@ -1942,7 +1961,7 @@ struct soma_batch {
 namespace {
 
 struct BatchLayout {
-  uint64_t segs[4], seg_first, fargs, fb_first, ctrs, apply, brick_first, total;
+  uint64_t segs[4], seg_first, fargs, fb_first, ctrs, apply, brick_first, af_first, total;
 };
 
 BatchLayout batch_layout(uint64_t n_segs, uint64_t n_sys) {
@@ -1963,6 +1982,8 @@ BatchLayout batch_layout(uint64_t n_segs, uint64_t n_sys) {
   L.apply = o;
   o = align_up(o + n_sys * sizeof(soma::BinApplySeg));
   L.brick_first = o;
+  o = align_up(o + (n_sys + 1) * 4);
+  L.af_first = o;
   o = align_up(o + (n_sys + 1) * 4);
   L.total = o;
   return L;
@@ -2023,8 +2044,10 @@ void launch_batch_t(bool binned, uint32_t kind, dim3 grid, hipStream_t s,
   else launch_batch_k<C64, V2, false>(kind, grid, s, L);
 }
 
+// *pending (if not null) receives whether the systems' bins hold updates that are
+// still to be applied; with null they are applied.
 int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t off,
-                           uint32_t j) {
+                           uint32_t j, bool *pending = nullptr) {
   soma::BatchLaunch L;
   L.sub_k = b->substeps;
   L.sub_j = j;
@@ -2046,7 +2069,13 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   const dim3 grid(blocks);
   // mixed sweeps keep direct atomics: their LDS tiles leave no room for the
   // bin tables at two blocks per compute unit
-  const bool binned = b->hist == soma::kHistBinned && kind != SOMA_MOVE_MIXED;
+  bool binned = b->hist == soma::kHistBinned;
+  if (!binned && b->hist_auto && b->bins_ok) {   // as bins_pay, for the whole batch
+    double atomics = 0.0, bins = kBinsPerLaunch;
+    for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins);
+    binned = atomics > bins;
+  }
+  binned = binned && kind != SOMA_MOVE_MIXED;
   if (b->c64) {
     if (b->v2) launch_batch_t<true, true>(binned, kind, grid, s, L);
     else launch_batch_t<true, false>(binned, kind, grid, s, L);
@@ -2055,7 +2084,8 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
     else launch_batch_t<false, false>(binned, kind, grid, s, L);
   }
   LAUNCH_TRY();
-  if (!binned) return SOMA_OK;
+  if (pending) *pending = binned;
+  if (!binned || pending) return SOMA_OK;
   // every system's bins into its counts: one workgroup per brick of the batch
   const uint32_t n_sys = (uint32_t)b->sys.size();
   const dim3 agrid(b->brick_first[n_sys]), ablock(soma::kApplyWide);
@@ -2070,9 +2100,33 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   return SOMA_OK;
 }
 
+// Gradient fields of the systems that keep one.
+int32_t batch_grads(soma_batch *b, hipStream_t s) {
+  for (soma_system *x : b->sys)
+    if (x->grad) {
+      const int32_t r = launch_grad(x, s);
+      if (r) return r;
+    }
+  return SOMA_OK;
+}
+
 // advance > 0: every system's sweep counter moves on by that many sweeps.
-int32_t launch_batch_field(soma_batch *b, hipStream_t s, uint32_t advance = 0) {
+// pending: the bins are applied first, by the same launch.
+int32_t launch_batch_field(soma_batch *b, hipStream_t s, uint32_t advance = 0, bool pending = false,
+                           bool stats = true) {
   const uint32_t n_sys = (uint32_t)b->sys.size();
+  if (pending) {
+    const dim3 grid(b->af_first[n_sys]), block(soma::kApplyWide);
+    const size_t lds = (size_t)soma::kBrickCells * (b->c64 ? 8u : 4u);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, block, lds, s, b->d_apply, b->d_fargs, b->d_af_first, n_sys,
+                         b->d_ctrs, advance, stats ? 1u : 0u);
+    };
+    if (b->c64) launch(soma::batched_apply_field_kernel<true>);
+    else launch(soma::batched_apply_field_kernel<false>);
+    LAUNCH_TRY();
+    return batch_grads(b, s);
+  }
   const dim3 grid(b->fb_first[n_sys]);
   if (b->c64)
     hipLaunchKernelGGL(soma::batched_field_kernel<true>, grid, dim3(256), 0, s, b->d_fargs,
@@ -2081,12 +2135,7 @@ int32_t launch_batch_field(soma_batch *b, hipStream_t s, uint32_t advance = 0) {
     hipLaunchKernelGGL(soma::batched_field_kernel<false>, grid, dim3(256), 0, s, b->d_fargs,
                        b->d_fb_first, n_sys, b->d_ctrs, advance);
   LAUNCH_TRY();
-  for (soma_system *x : b->sys)   // gradient fields of the systems that keep one
-    if (x->grad) {
-      const int32_t r = launch_grad(x, s);
-      if (r) return r;
-    }
-  return SOMA_OK;
+  return batch_grads(b, s);
 }
 
 int32_t launch_batch_counter(soma_batch *b, uint32_t by, hipStream_t s) {
@@ -2101,8 +2150,10 @@ int32_t launch_batch_counter(soma_batch *b, uint32_t by, hipStream_t s) {
 int32_t enqueue_batch_cycles(soma_batch *b, uint32_t n, uint32_t kind, hipStream_t s) {
   for (uint32_t i = 0; i < n; ++i)
     for (uint32_t j = 0; j < b->substeps; ++j) {
-      int32_t r = launch_batch_sweep(b, kind, s, i, j);
-      if (!r) r = launch_batch_field(b, s, i + 1u == n && j + 1u == b->substeps ? n : 0u);
+      bool pending = false;
+      int32_t r = launch_batch_sweep(b, kind, s, i, j, &pending);
+      const bool last = i + 1u == n && j + 1u == b->substeps;
+      if (!r) r = launch_batch_field(b, s, last ? n : 0u, pending, last);
       if (r) return r;
     }
   return SOMA_OK;
@@ -2185,6 +2236,7 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
   }
   b->bins_ok = true;
   b->brick_first.push_back(0);
+  b->af_first.push_back(0);
   for (uint32_t i = 0; i < n; ++i) {
     soma_system *x = systems[i];
     b->bins_ok = b->bins_ok && x->d.bins_ok && x->d.n_types <= 2;
@@ -2192,7 +2244,10 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
     if (x->d.bins_ok) a.b = x->bins();
     a.g = x->grid;
     a.counts = x->buf.counts;
+    a.n_bricks = x->d.bins_ok ? (uint32_t)x->d.n_bricks : 0u;
+    a.n_parts = x->d.field_blocks;
     b->apply.push_back(a);
+    b->af_first.push_back(b->af_first.back() + std::min(a.n_bricks, a.n_parts));
     const uint64_t next = (uint64_t)b->brick_first.back() + (x->d.bins_ok ? x->d.n_bricks : 0u);
     b->bins_ok = b->bins_ok && next < (1ull << 31);
     b->brick_first.push_back((uint32_t)std::min<uint64_t>(next, 1ull << 31));
@@ -2205,6 +2260,7 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
   b->d_ctrs = reinterpret_cast<uint32_t **>(ws + lay.ctrs);
   b->d_apply = reinterpret_cast<soma::BinApplySeg *>(ws + lay.apply);
   b->d_brick_first = reinterpret_cast<uint32_t *>(ws + lay.brick_first);
+  b->d_af_first = reinterpret_cast<uint32_t *>(ws + lay.af_first);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   auto put = [&](void *dst, const void *src, size_t bytes) -> int32_t {
     HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
@@ -2218,6 +2274,7 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
   if (!rc) rc = put(b->d_ctrs, b->ctrs.data(), b->ctrs.size() * 8);
   if (!rc) rc = put(b->d_apply, b->apply.data(), b->apply.size() * sizeof(soma::BinApplySeg));
   if (!rc) rc = put(b->d_brick_first, b->brick_first.data(), b->brick_first.size() * 4);
+  if (!rc) rc = put(b->d_af_first, b->af_first.data(), b->af_first.size() * 4);
   if (!rc) {  // the host tables must outlive the copies
     const hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) rc = fail(SOMA_E_HIP, "batch tables: %s", hipGetErrorString(e));
@@ -2238,6 +2295,7 @@ int32_t soma_batch_set_histogram(soma_batch *b, uint32_t mode) {
     return fail(SOMA_E_UNSUPPORTED,
                 "binned count updates need bins in every system and two bead types");
   b->hist = mode == SOMA_HIST_BINNED ? soma::kHistBinned : soma::kHistDirect;
+  b->hist_auto = mode == SOMA_HIST_DIRECT;
   return SOMA_OK;
 }
 
@@ -2535,6 +2593,7 @@ int32_t soma_batch_autotune(soma_batch *b, uint32_t cycles, uint32_t move_kind,
                          [&](uint32_t mode, uint32_t grid) {
                            b->mode = mode & 1u;
                            b->hist = (mode >> 1) ? soma::kHistBinned : soma::kHistDirect;
+                           b->hist_auto = false;
                            b->grid_blocks = grid;
                          },
                          [&]() -> int32_t { return soma_batch_cycle(b, 1, move_kind, stream); },

@@ -18,7 +18,7 @@ __device__ __forceinline__ void store_hint(T *p, T v) {
 }
 
 // Blocks blk, blk + nblk, ... of the bricks of one grid.  With partials the
-// refresh also leaves the count sums and H_nb (one partial per block, zeros in
+// refresh also leaves the sums of the counts (one partial per block, zeros in
 // the rest of the n_parts entries that observables read).
 // NT: counts and bin entries pass with the non-temporal hint (as in the field
 // kernel: grids whose counts outgrow the caches keep their fields there instead).
@@ -29,8 +29,7 @@ __device__ __forceinline__ void apply_field_bricks(const BinArgs &b, const Grid 
                                                    uint32_t *s_cnt) {
   const uint32_t tid = threadIdx.x;
   const bool stats = a.partials != nullptr;
-  unsigned long long sum_a = 0, sum_b = 0;
-  double h = 0.0;
+  FieldSums sums = {};
   for (uint32_t brick = blk; brick < n_bricks; brick += nblk) {
     bin_gather_brick<COUNT64, THREADS, NT>(b, g, a.counts, 1u, brick, s_cnt);
     uint32_t x0, y0, z0;
@@ -63,22 +62,17 @@ __device__ __forceinline__ void apply_field_bricks(const BinArgs &b, const Grid 
         a.omega[c] = va;
         a.omega[a.n_cells + c] = vb;
         if (a.halo) halo_put_rx(a, r, x, va, vb);
-        if (stats) {
-          sum_a += na;
-          sum_b += nb;
-          if (!off) h += hnb_cell(na, nb, a);
-        }
+        if (stats) field_sum(sums, na, nb, off);
       }
     }
     if (brick + nblk < n_bricks) __syncthreads();   // s_cnt is reused
   }
   if (!stats) return;
-  field_partials(a.partials, blk, sum_a, sum_b, h);
+  field_partials(a.partials, blk, sums);
   for (uint32_t i = blk + nblk; i < n_parts; i += nblk)
-    if (tid == 0u) {
-      a.partials->sum_a[i] = a.partials->sum_b[i] = 0ull;
-      a.partials->h_nb[i] = 0.0;
-    }
+    if (tid == 0u)
+      a.partials->sum_a[i] = a.partials->sum_b[i] = a.partials->n1[i] = a.partials->n2[i] =
+          a.partials->nab[i] = 0ull;
 }
 
 // Large grids (NT) have bricks enough for narrow blocks.

@@ -10,14 +10,24 @@ namespace soma {
 constexpr uint32_t kFieldBlocks = 1024u;  // largest grid of the field kernel
 // Cells per block below that: one group of four per thread, so that a small
 // grid is one round trip to memory on as many compute units as it can use
-// (24^3 cells: 14 blocks and 3.1 us, against 4 blocks of four rounds and 5.5 us).
+// (24^3 cells: 14 blocks and 4.1 us, against 4 blocks of four rounds and 5.5 us).
 constexpr uint32_t kFieldBlockCells = 1024u;
 
 // Per-block sums of the last field refresh, one array per quantity (their
-// reduction then reads whole lines).
+// reduction then reads whole lines).  With two bead types H_nb is a polynomial in
+// the counts, so the blocks leave integer sums over the free cells and the host
+// evaluates it once: exact sums, whichever kernel and launch shape took them.
+// More types: h_nb per block in FP64.
 struct FieldPartials {
-  unsigned long long sum_a[kFieldBlocks], sum_b[kFieldBlocks];
+  unsigned long long sum_a[kFieldBlocks], sum_b[kFieldBlocks];   // all cells
+  unsigned long long n1[kFieldBlocks], n2[kFieldBlocks], nab[kFieldBlocks];   // see FieldSums
   double h_nb[kFieldBlocks];
+};
+
+// Sums of the counts n_A, n_B over cells: n_A and n_B over all cells; n_A + n_B,
+// (n_A + n_B)^2 and n_A n_B over the free ones.
+struct FieldSums {
+  unsigned long long a, b, n1, n2, nab;
 };
 
 // ---------------------------------------------------------------------------
@@ -85,14 +95,13 @@ __global__ __launch_bounds__(256) void zero_kernel(uint32_t *p, uint64_t n_words
 //   omega_A = fma(chiN, phi_B, t),  omega_B = fma(chiN, phi_A, t)
 // in this FP32 order (the library is built without FP contraction).
 // Optionally clears the counts in the same pass and accumulates the count
-// sums and H_nb (Eqs. (5), (6), (8), FP64) per block.
+// sums (of H_nb, Eqs. (5), (6), (8), among them) per block.
 // ---------------------------------------------------------------------------
 struct FieldArgs {
   void *counts;
   float *omega;
   uint32_t n_cells;
   float inv_rho, chi_n, kappa_n;
-  double inv_rho_d, chi_n_d, kappa_n_d;
   FieldPartials *partials;  // may be null
   int clear;
   // optional copy of the fields with one periodic halo cell at each end of every
@@ -179,12 +188,15 @@ __device__ __forceinline__ void field_cell(uint32_t na, uint32_t nb,
   }
 }
 
-__device__ __forceinline__ double hnb_cell(uint32_t na, uint32_t nb,
-                                           const FieldArgs &a) {
-  const double pa = (double)na * a.inv_rho_d, pb = (double)nb * a.inv_rho_d;
-  const double dev = pa + pb - 1.0;
-  const double inter = a.form == 0 ? -0.25 * a.chi_n_d * (pa - pb) * (pa - pb) : a.chi_n_d * pa * pb;
-  return 0.5 * a.kappa_n_d * dev * dev + inter;
+// Adds one cell's counts (off: impenetrable, left out of H_nb).
+__device__ __forceinline__ void field_sum(FieldSums &s, uint32_t na, uint32_t nb, bool off) {
+  s.a += na;
+  s.b += nb;
+  if (off) return;
+  const unsigned long long n = (unsigned long long)na + nb;
+  s.n1 += n;
+  s.n2 += n * n;
+  s.nab += (unsigned long long)na * nb;
 }
 
 // NT: the counts are read with the non-temporal hint (grids whose counts
@@ -218,42 +230,46 @@ __device__ __forceinline__ void load4(const void *counts, uint32_t q,
   }
 }
 
-// The block's sums (up to eight waves) as partial `blk`: wave shuffles, then through
-// LDS in the order of the waves.
-__device__ __forceinline__ void field_partials(FieldPartials *p, uint32_t blk,
-                                               unsigned long long sum_a, unsigned long long sum_b,
-                                               double h) {
-  __shared__ unsigned long long s_a[8], s_b[8];
-  __shared__ double s_h[8];
-  for (int off = 32; off > 0; off >>= 1) {
-    sum_a += __shfl_down(sum_a, off, 64);
-    sum_b += __shfl_down(sum_b, off, 64);
-    h += __shfl_down(h, off, 64);
-  }
+// The sums of a block (up to eight waves) of NV values: wave shuffles, then through
+// LDS in the order of the waves; in thread 0.
+template <class T, int NV>
+__device__ __forceinline__ void block_totals(T (&v)[NV]) {
+  __shared__ T s[8][NV];
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] += __shfl_down(v[j], off, 64);
   const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
-  if (lane == 0) { s_a[wv] = sum_a; s_b[wv] = sum_b; s_h[wv] = h; }
+  if (lane == 0)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) s[wv][j] = v[j];
   __syncthreads();
+  if (threadIdx.x == 0)
+    for (uint32_t w = 1; w < blockDim.x >> 6; ++w)
+#pragma unroll
+      for (int j = 0; j < NV; ++j) v[j] += s[w][j];
+}
+
+// The block's sums as partial `blk`.
+__device__ __forceinline__ void field_partials(FieldPartials *p, uint32_t blk, const FieldSums &s) {
+  unsigned long long v[5] = {s.a, s.b, s.n1, s.n2, s.nab};
+  block_totals(v);
   if (threadIdx.x == 0) {
-    for (uint32_t w = 1; w < blockDim.x >> 6; ++w) {
-      sum_a += s_a[w];
-      sum_b += s_b[w];
-      h += s_h[w];
-    }
-    p->sum_a[blk] = sum_a;
-    p->sum_b[blk] = sum_b;
-    p->h_nb[blk] = h;
+    p->sum_a[blk] = v[0];
+    p->sum_b[blk] = v[1];
+    p->n1[blk] = v[2];
+    p->n2[blk] = v[3];
+    p->nab[blk] = v[4];
   }
 }
 
 // Block `blk` of the `nblk` blocks that serve one grid: a grid-stride loop
-// over groups of four cells, then the block's partial sums (FP64 H_nb).
+// over groups of four cells, then the block's partial sums.
 template <bool COUNT64, bool NT = false>
 __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uint32_t nblk) {
   const uint32_t n4 = a.n_cells >> 2;
   const uint32_t stride = nblk * blockDim.x;
   const uint32_t tid = blk * blockDim.x + threadIdx.x;
-  unsigned long long sum_a = 0, sum_b = 0;
-  double h = 0.0;
+  FieldSums sums = {};
   const bool stats = a.partials != nullptr;
   float4 *oa4 = reinterpret_cast<float4 *>(a.omega);
   const bool b_aligned = (a.n_cells & 3u) == 0u;
@@ -269,11 +285,7 @@ __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uin
       field_cell(na[j], nb[j], a, va[j], vb[j]);
       const bool off = ((fb >> j) & 1u) != 0u;
       if (a.ext || a.forbid) field_extras(a, 4u * q + j, off, va[j], vb[j]);
-      if (stats) {
-        sum_a += na[j];
-        sum_b += nb[j];
-        if (!off) h += hnb_cell(na[j], nb[j], a);
-      }
+      if (stats) field_sum(sums, na[j], nb[j], off);
     }
     oa4[q] = make_float4(va[0], va[1], va[2], va[3]);
     if (a.halo) {   // four consecutive cells: one division, then step along the row
@@ -325,14 +337,10 @@ __device__ __forceinline__ void field_body(const FieldArgs &a, uint32_t blk, uin
     a.omega[c] = va;
     a.omega[a.n_cells + c] = vb;
     if (a.halo) halo_put(a, c, va, vb);
-    if (stats) {
-      sum_a += na;
-      sum_b += nb;
-      if (!off) h += hnb_cell(na, nb, a);
-    }
+    if (stats) field_sum(sums, na, nb, off);
   }
   if (!stats) return;
-  field_partials(a.partials, blk, sum_a, sum_b, h);
+  field_partials(a.partials, blk, sums);
 }
 
 template <bool COUNT64, bool NT = false>
@@ -502,7 +510,15 @@ __global__ __launch_bounds__(256) void field_multi_kernel(const MultiFieldArgs a
     }
   }
   if (!stats) return;
-  field_partials(a.partials, blockIdx.x, sum_a, sum_b, h);
+  unsigned long long n[2] = {sum_a, sum_b};
+  double hv[1] = {h};
+  block_totals(n);
+  block_totals(hv);
+  if (threadIdx.x == 0) {
+    a.partials->sum_a[blockIdx.x] = n[0];
+    a.partials->sum_b[blockIdx.x] = n[1];
+    a.partials->h_nb[blockIdx.x] = hv[0];
+  }
 }
 
 // Per-type totals of the counts: block b writes out[b * kMaxTypes + t].

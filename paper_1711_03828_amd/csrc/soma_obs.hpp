@@ -13,7 +13,7 @@ constexpr uint32_t kObsSums = 5u;   // Re^2, Rg^2, b^2, bond energy, field energ
 struct Totals {
   unsigned long long accepted[4];   // local, smart MC, learned, bond-Gibbs
   unsigned long long attempted_learned;
-  unsigned long long sum_a, sum_b;
+  unsigned long long sum_a, sum_b, n1, n2, nab;   // FieldSums
   double re2, rg2, b2, e_bond, e_field, h_nb;
   uint32_t err, pad;
 };
@@ -176,11 +176,11 @@ __global__ __launch_bounds__(256) void chain_obs_kernel(const ObsArgs a) {
 }
 
 // Fixed-order reduction of all partials into one Totals record: one block, one
-// wave per quantity (five chain sums, H_nb, two count sums, four acceptance
+// wave per quantity (five chain sums, H_nb, five count sums, four acceptance
 // counters, the learned attempts).  acc_slots holds kAccSlots counters for each
 // of local, smart-MC, learned and bond-Gibbs moves; att_slots the attempted
 // learned moves.
-constexpr uint32_t kTotalsWaves = 13u;
+constexpr uint32_t kTotalsWaves = 16u;
 
 // Sum of an array over the wave, eight loads in flight.
 template <class T>
@@ -207,9 +207,10 @@ __global__ __launch_bounds__(64 * kTotalsWaves) void reduce_totals_kernel(
   if (q <= kObsSums) {
     d = wave_array_sum(q < kObsSums ? op + (size_t)q * n_op : fp->h_nb, q < kObsSums ? n_op : n_fp);
   } else {
-    const bool field = q < 8u;
-    const unsigned long long *p = q == 6u ? fp->sum_a : q == 7u ? fp->sum_b
-                                  : q < 12u ? acc_slots + (q - 8u) * kAccSlots : att_slots;
+    const bool field = q < 11u;
+    const unsigned long long *p = q == 6u ? fp->sum_a : q == 7u ? fp->sum_b : q == 8u ? fp->n1
+                                  : q == 9u ? fp->n2 : q == 10u ? fp->nab
+                                  : q < 15u ? acc_slots + (q - 11u) * kAccSlots : att_slots;
     n = wave_array_sum(p, field ? n_fp : kAccSlots);
   }
   if ((threadIdx.x & 63u) != 0u) return;
@@ -222,12 +223,15 @@ __global__ __launch_bounds__(64 * kTotalsWaves) void reduce_totals_kernel(
     case 5: out->h_nb = d; break;
     case 6: out->sum_a = n; break;
     case 7: out->sum_b = n; break;
-    case 12:
+    case 8: out->n1 = n; break;
+    case 9: out->n2 = n; break;
+    case 10: out->nab = n; break;
+    case 15:
       out->attempted_learned = n;
       out->err = *err;
       out->pad = 0;
       break;
-    default: out->accepted[q - 8u] = n;
+    default: out->accepted[q - 11u] = n;
   }
 }
 

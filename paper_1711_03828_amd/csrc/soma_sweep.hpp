@@ -402,9 +402,9 @@ __device__ __forceinline__ void trial_gather(const SweepArgs &a, uint32_t pla, T
 // chain's set order ("a" moves first, "b" second) and everything after is
 // written for a and b, so that only positions and draws pass through a choice per
 // lane, and the positions once more for the store (two 12-byte stores to the
-// beads' own places instead write each line in halves: 1228 -> 1279 us).  The kernel is
-// bound by its vector instructions (about 80% of its cycles) together with the
-// L1 and L2 traffic of the gathers.
+// beads' own places instead write each line in halves: 1228 -> 1279 us).  Small grids
+// are bound by the vector instructions, large ones by the lines that the gathers
+// pull through L1 and L2 and by the count updates.
 // ---------------------------------------------------------------------------
 // One wave's tile of local moves: positions r0/r1 already loaded for lane map m.
 // EVEN: every chain has an even number of beads, so a lane's two beads both
