@@ -713,7 +713,7 @@ constexpr double kBinsPerLaunch = 10e-6;
 // of the sweep's barriers), a pass over the counts, and 0.1 ns per wave.  Per SCMF
 // cycle, atomics against bins, 256-thread blocks: 24^3 cells, 33k beads 8.1 / 12.5
 // us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71; film of 16M beads
-// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 57; bond-Gibbs moves of 1M beads
+// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 54; bond-Gibbs moves of 1M beads
 // 61 / 31; smart-MC moves of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their
 // blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
 // system, whose waves reserve room one by one.
@@ -2088,7 +2088,7 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   if (!binned || pending) return SOMA_OK;
   // every system's bins into its counts: one workgroup per brick of the batch
   const uint32_t n_sys = (uint32_t)b->sys.size();
-  const dim3 agrid(b->brick_first[n_sys]), ablock(soma::kApplyWide);
+  const dim3 agrid(b->brick_first[n_sys]), ablock(soma::kBatchApplyThreads);
   const size_t lds = (size_t)soma::kBrickCells * (b->c64 ? 8u : 4u);
   if (b->c64)
     hipLaunchKernelGGL(soma::batched_bin_apply_kernel<true>, agrid, ablock, lds, s, b->d_apply,
@@ -2116,7 +2116,7 @@ int32_t launch_batch_field(soma_batch *b, hipStream_t s, uint32_t advance = 0, b
                            bool stats = true) {
   const uint32_t n_sys = (uint32_t)b->sys.size();
   if (pending) {
-    const dim3 grid(b->af_first[n_sys]), block(soma::kApplyWide);
+    const dim3 grid(b->af_first[n_sys]), block(soma::kBatchApplyThreads);
     const size_t lds = (size_t)soma::kBrickCells * (b->c64 ? 8u : 4u);
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, grid, block, lds, s, b->d_apply, b->d_fargs, b->d_af_first, n_sys,

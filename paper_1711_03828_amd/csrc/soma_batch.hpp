@@ -101,23 +101,28 @@ struct BinApplySeg {
   uint32_t n_bricks, n_parts;   // bricks; partials of the melt's field refresh
 };
 
+// Small melts have few bricks in all (some 200 for 24 melts) and many updates in
+// each, so a brick takes 16 waves: 17.0 us for the apply and field launch, 20.2
+// with eight, 30.1 with four.
+constexpr uint32_t kBatchApplyThreads = 1024u;
+
 template <bool COUNT64>
-__global__ __launch_bounds__(kApplyWide) void batched_bin_apply_kernel(
+__global__ __launch_bounds__(kBatchApplyThreads) void batched_bin_apply_kernel(
     const BinApplySeg *__restrict__ segs, const uint32_t *__restrict__ brick_first,
     uint32_t n_sys) {
   extern __shared__ uint32_t s_cnt[];
   const uint32_t s = range_of(brick_first, n_sys, blockIdx.x);
   const BinApplySeg x = load_uniform(segs + s);
-  bin_apply_brick<COUNT64, kApplyWide>(x.b, x.g, x.counts, 1u, blockIdx.x - load_uniform(brick_first + s), s_cnt);
+  bin_apply_brick<COUNT64, kBatchApplyThreads>(x.b, x.g, x.counts, 1u, blockIdx.x - load_uniform(brick_first + s), s_cnt);
 }
 
 // The bins of every melt applied and its fields refreshed in one launch (melt s
 // owns the blocks [first[s], first[s + 1]), each over the melt's bricks in steps of
-// that many blocks), as apply_field_kernel.  24 melts of 0.5k to 33k chains: 20.2
+// that many blocks), as apply_field_kernel.  24 melts of 0.5k to 33k chains: 17.0
 // us where the two kernels before it took 14.3 and 5.0 and the gap between them 2;
 // with atomics the sweep took 60 us and the field kernel 5, with bins 37 and this.
 template <bool COUNT64>
-__global__ __launch_bounds__(kApplyWide) void batched_apply_field_kernel(
+__global__ __launch_bounds__(kBatchApplyThreads) void batched_apply_field_kernel(
     const BinApplySeg *__restrict__ segs, const FieldArgs *__restrict__ fa,
     const uint32_t *__restrict__ first, uint32_t n_sys, uint32_t *const *ctrs, uint32_t ctr_by,
     uint32_t stats) {
@@ -128,7 +133,7 @@ __global__ __launch_bounds__(kApplyWide) void batched_apply_field_kernel(
   FieldArgs a = load_uniform(fa + s);
   if (!stats) a.partials = nullptr;
   if (ctr_by) advance_counter(ctrs[s], ctr_by, blockIdx.x - f0);
-  apply_field_bricks<COUNT64, false, kApplyWide>(x.b, x.g, a, x.n_bricks, blockIdx.x - f0, f1 - f0,
+  apply_field_bricks<COUNT64, false, kBatchApplyThreads>(x.b, x.g, a, x.n_bricks, blockIdx.x - f0, f1 - f0,
                                                  x.n_parts, s_cnt);
 }
 

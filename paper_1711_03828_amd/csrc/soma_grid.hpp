@@ -230,11 +230,11 @@ __device__ __forceinline__ void load4(const void *counts, uint32_t q,
   }
 }
 
-// The sums of a block (up to eight waves) of NV values: wave shuffles, then through
+// The sums of a block (up to 16 waves) of NV values: wave shuffles, then through
 // LDS in the order of the waves; in thread 0.
 template <class T, int NV>
 __device__ __forceinline__ void block_totals(T (&v)[NV]) {
-  __shared__ T s[8][NV];
+  __shared__ T s[16][NV];
   for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
     for (int j = 0; j < NV; ++j) v[j] += __shfl_down(v[j], off, 64);
