@@ -461,6 +461,7 @@ struct soma_system {
   uint64_t mixed_moves = 0;   // bead moves made by mixed sweeps (local or learned)
   uint32_t net_mask = 0;      // species with an installed network (bit per species)
   uint32_t arch_mask = 0;     // species with a general architecture (bit per species)
+  uint32_t arch_pair = 0;     // those of at most two independent sets (mc_sweep_pair_kernel)
   uint32_t arch_type0[SOMA_MAX_SPECIES] = {};  // A monomers per molecule of those species
   uint32_t arch_per_wave[SOMA_MAX_SPECIES] = {};  // molecules per wave of their sweep
   uint32_t arch_max_type[SOMA_MAX_SPECIES] = {};  // largest type code of their monomers
@@ -745,6 +746,18 @@ int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t of
     a.n_sub = subset_size(S.n_chains, k, j);
     if (a.n_sub == 0) continue;
     const bool c64 = c->count_width == 32;
+    if (sys->arch_pair >> sp & 1u) {   // architecture of at most two independent sets
+      const uint32_t per_wave = sys->arch_per_wave[sp], lanes = 64u / per_wave;
+      const dim3 grid((a.n_sub + 4u * per_wave - 1u) / (4u * per_wave));
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a, sys->d.arch[sp], per_wave, lanes,
+                           65536u / lanes + 1u);
+      };
+      if (c64) launch(soma::mc_sweep_pair_kernel<true>);
+      else launch(soma::mc_sweep_pair_kernel<false>);
+      LAUNCH_TRY();
+      continue;
+    }
     if (sys->d.arch[sp]) {   // general architecture: per_wave molecules per wave (local moves, SET)
       const uint32_t per_block = 4u * sys->arch_per_wave[sp];
       const dim3 grid((a.n_sub + per_block - 1u) / per_block);
@@ -1264,6 +1277,19 @@ const char *decode_architecture(const uint32_t *w, uint32_t n_words, uint32_t n_
   uint32_t largest = 1;
   for (uint32_t c = 0; c < k; ++c) largest = std::max<uint32_t>(largest, t.set_start[c + 1] - t.set_start[c]);
   t.per_wave = std::max(1u, std::min(64u / largest, soma::kArchMaxN / n));
+  t.pair = k <= 2 && largest <= 64 ? 1u : 0u;
+  for (uint32_t i = 0; i < n; ++i)
+    if (t.nb_start[i + 1] - t.nb_start[i] > (int)soma::kArchRecBonds) t.pair = 0u;
+  if (t.pair)
+    for (uint32_t c = 0; c < k; ++c)
+      for (uint32_t m = t.set_start[c]; m < t.set_start[c + 1]; ++m) {
+        const uint32_t i = t.member[m], n_b = t.nb_start[i + 1] - t.nb_start[i];
+        uint8_t *rec = t.rec[c][m - t.set_start[c]];
+        rec[0] = (uint8_t)i;
+        rec[1] = t.type[i];
+        rec[2] = (uint8_t)(0x80u | n_b);
+        std::memcpy(rec + 3, t.nb + t.nb_start[i], n_b);
+      }
   return nullptr;
 }
 
@@ -1286,10 +1312,12 @@ int32_t soma_set_architecture(soma_system *sys, uint32_t species, const uint32_t
     sys->arch_mask |= 1u << species;
     sys->arch_type0[species] = t.n_type0;
     sys->arch_per_wave[species] = t.per_wave;
+    sys->arch_pair = t.pair ? sys->arch_pair | 1u << species : sys->arch_pair & ~(1u << species);
     sys->arch_max_type[species] = *std::max_element(t.type, t.type + t.n);
     sys->d.arch[species] = sys->arch(species);
   } else {
     sys->arch_mask &= ~(1u << species);
+    sys->arch_pair &= ~(1u << species);
     sys->d.arch[species] = nullptr;
   }
   // expected A count for the conservation check

@@ -118,4 +118,104 @@ __global__ __launch_bounds__(256) void mc_sweep_arch_kernel(const SweepArgs a_in
   finish_block(a, n_acc);
 }
 
+// Sum of bond_term over the monomer's bonds in list order (record rec, positions of
+// its molecule at sp), two partners per step.
+__device__ __forceinline__ F3 pair_bonds(const float4 *sp, uint4 rec, F3 r, F3 d) {
+  const uint32_t n = (rec.x >> 16) & 0x7Fu;
+  F3 q = {0.f, 0.f, 0.f};
+  uint32_t w = (rec.x >> 24) | (rec.y << 8);   // the next four partners
+  uint32_t w1 = __builtin_amdgcn_alignbyte(rec.z, rec.y, 3u), w2 = __builtin_amdgcn_alignbyte(rec.w, rec.z, 3u);
+  uint32_t w3 = rec.w >> 24;
+#pragma unroll 1
+  for (uint32_t b = 0; b < n; b += 2u) {
+    const float4 p0 = sp[w & 0xFFu], p1 = sp[(w >> 8) & 0xFFu];
+    q = q + bond_term(r, F3{p0.x, p0.y, p0.z}, d);
+    const F3 q1 = q + bond_term(r, F3{p1.x, p1.y, p1.z}, d);
+    q = sel(b + 1u < n, q1, q);
+    w = __builtin_amdgcn_alignbyte(w1, w, 2u);
+    w1 = __builtin_amdgcn_alignbyte(w2, w1, 2u);
+    w2 = __builtin_amdgcn_alignbyte(w3, w2, 2u);
+    w3 >>= 16;
+  }
+  return q;
+}
+
+// The same moves for architectures of at most two independent sets (linear chains,
+// stars, combs, even rings; at most 64 members per set and kArchRecBonds bonds per
+// monomer), as local_tile: a molecule's lane l holds member l of either set, whose
+// draws, cells and field gathers are independent of the other set and go first; the
+// two are relabelled by the molecule's set order, and only bond terms and outcomes
+// wait for the set before, through LDS.  8.4M monomers in six-armed stars of three
+// types on 96^3 cells: 94.5 us, mc_sweep_arch_kernel 165.6; bound by its vector
+// instructions (the bond loop runs as long as the hub's list in both passes) and the
+// count atomics, which the bins do not shorten here (100.6 us and 12 to apply them).
+// per_wave molecules per wave on `lanes` lanes each; inv_lanes = floor(65536 / lanes) + 1.
+template <bool COUNT64>
+__global__ __launch_bounds__(256) void mc_sweep_pair_kernel(
+    const SweepArgs a_in, const ArchDev *__restrict__ A, uint32_t per_wave, uint32_t lanes,
+    uint32_t inv_lanes) {
+  __shared__ float4 s_pos[4][kArchMaxN];
+  const SweepArgs a = resolve_sweep(a_in, 0u);
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t mi = (lane * inv_lanes) >> 16, li = lane - mi * lanes;
+  const uint32_t cl = (xcd_remap(blockIdx.x, gridDim.x) * 4u + wv) * per_wave + mi;
+  const bool mine = mi < per_wave && cl < a.n_sub;   // this lane's molecule exists
+  const uint32_t chain = mine ? cl * a.sub_k + a.sub_j : 0u, gchain = a.chain_base + chain;
+  const uint4 *rec = reinterpret_cast<const uint4 *>(A->rec[0]) + li;
+  const uint4 rec0 = rec[0], rec1 = rec[64];
+  const uint32_t i0 = rec0.x & 0xFFu, i1 = rec1.x & 0xFFu;
+  float *cp = a.pos + (size_t)chain * a.n * 3u;
+  f32x3_bead *p0 = reinterpret_cast<f32x3_bead *>(cp + 3u * i0);
+  f32x3_bead *p1 = reinterpret_cast<f32x3_bead *>(cp + 3u * i1);
+  const F3 r0 = (F3)*p0, r1 = (F3)*p1;
+  const Rand4 w0 = philox(gchain, i0 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
+  const Rand4 w1 = philox(gchain, i1 | (kPurposeMoveA << 16), a.sweep, a.replica, a.seed_lo, a.seed_hi);
+  // monomer 0 is the first member of set 0
+  const uint32_t bit = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane - li) << 2), (int)(w0.x & 1u));
+  const bool odd = a.set_order == 0u && bit != 0u;
+  const bool has0 = mine && (rec0.x & 0x800000u) != 0u, has1 = mine && (rec1.x & 0x800000u) != 0u;
+  const bool has_a = odd ? has1 : has0, has_b = odd ? has0 : has1;
+  const Rand4 wa = odd ? w1 : w0, wb = odd ? w0 : w1;
+  const uint4 ka = odd ? rec1 : rec0, kb = odd ? rec0 : rec1;
+  float4 *sp = s_pos[wv] + (mine ? mi : 0u) * a.n;
+  if (has0) sp[i0] = make_float4(r0.x, r0.y, r0.z, 0.f);
+  if (has1) sp[i1] = make_float4(r1.x, r1.y, r1.z, 0.f);
+  Trial X, Y;
+  X.r = sel(odd, r1, r0);
+  Y.r = sel(odd, r0, r1);
+  const uint32_t ta = (ka.x >> 8) & 0xFFu, tb = (kb.x >> 8) & 0xFFu;   // types: field planes
+  const uint32_t pla = ta * a.grid.n_cells, plb = tb * a.grid.n_cells;
+  trial_from(a, pla, X);
+  trial_from(a, plb, Y);
+  trial_to(a, wa, X);
+  trial_to(a, wb, Y);
+  trial_gather(a, pla, X, plb, Y);
+  const bool ok_a = has_a & move_allowed(a, X.c, X.n), ok_b = has_b & move_allowed(a, Y.c, Y.n);
+  wave_lds_fence();
+  F3 ra = X.r, rb = Y.r;
+  bool acc_a, acc_b;
+  {
+    const F3 d = X.t - X.r, q = pair_bonds(sp, ka, X.r, d);
+    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + (X.wn - X.wo) * a.inv_nref;
+    acc_a = ok_a & metropolis(d_e, uniform01(wa.w));
+    ra = acc_a ? X.t : ra;
+    if (acc_a) sp[ka.x & 0xFFu] = make_float4(ra.x, ra.y, ra.z, 0.f);
+  }
+  wave_lds_fence();
+  {
+    const F3 d = Y.t - Y.r, q = pair_bonds(sp, kb, Y.r, d);
+    const float d_e = a.half_k0 * (d.x * q.x + d.y * q.y + d.z * q.z) + (Y.wn - Y.wo) * a.inv_nref;
+    acc_b = ok_b & metropolis(d_e, uniform01(wb.w));
+    rb = acc_b ? Y.t : rb;
+  }
+  const F3 o0 = sel(odd, rb, ra), o1 = sel(odd, ra, rb);
+  if (has0) *p0 = f32x3_bead{o0.x, o0.y, o0.z};
+  if (has1) *p1 = f32x3_bead{o1.x, o1.y, o1.z};
+  // count plane type >> 1, half type & 1
+  const uint32_t ca = (ta >> 1) * a.grid.n_cells, cb = (tb >> 1) * a.grid.n_cells;
+  if (acc_a & (X.n != X.c)) move_count<COUNT64>(a.counts, X.c + ca, X.n + ca, (ta & 1u) != 0u);
+  if (acc_b & (Y.n != Y.c)) move_count<COUNT64>(a.counts, Y.c + cb, Y.n + cb, (tb & 1u) != 0u);
+  finish_block(a, (uint32_t)(__popcll(__ballot(acc_a)) + __popcll(__ballot(acc_b))));
+}
+
 }  // namespace soma

@@ -150,12 +150,17 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t n) {
 constexpr uint32_t kArchMaxN = 128;       // monomers per molecule
 constexpr uint32_t kArchMaxBonds = 2048;  // bond-list entries (each bond twice)
 constexpr uint32_t kArchMaxSets = 16;
+constexpr uint32_t kArchRecBonds = 13;    // partners in a member's record
 
 // One molecule type, decoded from the 32-bit architecture array (Sec. 3.2.1)
 // on the host: types, the bond lists (partners in the array's order) and the
 // independent sets (members of set s: member[set_start[s] .. set_start[s+1])).
-struct ArchDev {
-  uint32_t n, n_sets, n_type0;
+struct alignas(16) ArchDev {
+  // molecules of one or two sets (pair = 1): what the lane of member l of set s needs,
+  // in one load: byte 0 the monomer, 1 its type, 2 its bonds | 0x80 (0: no such
+  // member), then the partners
+  uint8_t rec[2][64][16];
+  uint32_t n, n_sets, n_type0, pair;
   uint32_t per_wave;   // molecules per wave: min(64 / largest set, 128 / n), at least 1
   uint8_t type[kArchMaxN];
   uint8_t member[kArchMaxN];

@@ -129,6 +129,47 @@ def test_architecture_sweep_matches_oracle(C, orc, kind):
     m.close()
 
 
+@pytest.mark.parametrize("kind,width,n_chains", [
+    ("hub13", 16, 1501), ("hub14", 16, 1501), ("hub64", 32, 301), ("hub65", 32, 301),
+    ("line127", 32, 333), ("line128", 16, 333), ("single", 16, 4001), ("two", 32, 2047)])
+def test_two_set_architectures_at_the_edges(C, orc, kind, width, n_chains):
+    """Two-set molecules at the limits of the kernel that serves them (13 bonds per monomer, 64
+    members per set, 1 to 128 monomers; hub14 and hub65 are beyond them), against the oracle, with
+    the bar of the sweeps above; two chain subsets, whose second sees the first one's fields."""
+    from paper_1711_03828_amd.melt import Melt
+    number = int("".join(ch for ch in kind if ch.isdigit()) or {"single": 1, "two": 2}[kind])
+    if kind.startswith("hub"):
+        # 14 and more bonds on one monomer; hub64: its 64 partners are one full set
+        n, bonds = synth.star_bonds(number, 1)
+    else:
+        n, bonds = number, [(i, i + 1) for i in range(number - 1)]
+    types = [i % 2 for i in range(n)]
+    words = synth.encode_architecture(n, types, bonds)
+    grid, k0 = (21, 18, 13), np.float32(2.0)
+    pos = synth.tree_walks(63, n_chains, n, bonds, grid, 1 / math.sqrt(float(k0)))
+    cfg = custom_config(grid, [__import__("oracle").Species(n_chains, n, 0)], k0=k0, n_ref=32, chi_n=20.0,
+                        kappa_n=40.0, local_a=0.3, count_width=width, seed=77)
+    m = Melt(cfg, positions=torch.from_numpy(pos))
+    m.set_architecture(words)
+    omega = m.omega.cpu().numpy()
+    m.sweep(1, C.SOMA_MOVE_LOCAL)
+    torch.cuda.synchronize()
+    got, ref = m.pos.cpu().numpy(), pos.copy()
+    orc.mc_sweep_arch(ref, n_chains, words, omega, grid, k0=k0, n_ref=32, step=np.float32(0.3),
+                      seed=77, sweep=0, threads=8)
+    bad = (got.reshape(n_chains, -1) != ref.reshape(n_chains, -1)).any(axis=1)
+    flush(kind, "mismatched molecules", int(bad.sum()))
+    assert bad.sum() <= math.ceil(1e-6 * n_chains * n)
+    np.testing.assert_array_equal(m.counts_planes(), orc.density_hist_arch(got, n_chains, words, grid))
+    m.set_substeps(2)
+    m.cycle(3)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(m.counts_planes(),
+                                  orc.density_hist_arch(m.pos.cpu().numpy(), n_chains, words, grid))
+    assert m.observables().counts_conserved == 1
+    m.close()
+
+
 def test_ideal_star_on_device(C):
     from paper_1711_03828_amd.melt import Melt
     arms, arm_len = 6, 5
