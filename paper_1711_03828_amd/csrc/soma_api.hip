@@ -59,7 +59,7 @@ struct Derived {
   // workspace layout
   uint64_t off_err = 0, off_acc = 0, off_att = 0, off_net = 0, off_fpart = 0, off_totals = 0,
            off_opart = 0, off_halo = 0, off_arch = 0, off_tcount = 0;
-  uint64_t halo_plane = 0;    // floats per plane of the halo copy (0: not kept)
+  uint64_t halo_words = 0;    // words of the halo copy (0: not kept)
   // external fields (soma_set_external): caller-owned device buffers, null if none;
   // n_free = cells not impenetrable (the reference density counts these)
   const float *ext = nullptr;
@@ -151,10 +151,10 @@ int32_t derive(const soma_config *c, Derived *d) {
   d->off_halo = align_up(d->off_tcount + 8ull * soma::kFieldBlocks * soma::kMaxTypes);
   // the learned proposal reads its 27-cell neighbourhoods from a copy of the
   // fields with one periodic halo cell at both ends of each x row
-  d->halo_plane = c->p_learn > 0.f ? (uint64_t)c->nz * c->ny * (c->nx + 2u) : 0u;
-  if (8ull * d->halo_plane >= (1ull << 32))
+  d->halo_words = c->p_learn > 0.f ? (uint64_t)c->nz * c->ny * (c->nx + 2u) : 0u;
+  if (8ull * d->halo_words >= (1ull << 32))
     return fail(SOMA_E_UNSUPPORTED, "grid too large for the learned proposal's field copy");
-  d->off_queue = align_up(d->off_halo + 8ull * d->halo_plane);
+  d->off_queue = align_up(d->off_halo + 4ull * d->halo_words);
   d->ws_bytes = align_up(d->off_queue + 4ull * soma::kQueueParts * soma::kQueueSub * soma::kQueueStride);
   // bins: room for the updates of about half the beads of a brick per sweep
   // (entries beyond it go to the counts as direct atomics)
@@ -270,7 +270,7 @@ int32_t launch_hist(const soma_config *c, const Derived &d, const float *pos, vo
 }
 
 soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts, float *omega,
-                           soma::FieldPartials *partials, float *halo = nullptr) {
+                           soma::FieldPartials *partials, uint32_t *halo = nullptr) {
   soma::FieldArgs a;
   a.counts = counts;
   a.omega = omega;
@@ -280,9 +280,8 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.kappa_n = c->kappa_n;
   a.partials = partials;
   a.clear = 0;
-  a.halo = d.halo_plane ? halo : nullptr;
+  a.halo = d.halo_words ? halo : nullptr;
   a.nx = c->nx;
-  a.halo_plane = (uint32_t)d.halo_plane;
   a.ext = d.ext;
   a.forbid = d.forbid;
   a.form = d.form;
@@ -300,7 +299,7 @@ bool stream_counts(const soma_config *c, const Derived &d) {
 
 // ctr, ctr_by: sweep counter that this refresh advances (the last one of a call).
 int32_t launch_field(const soma_config *c, const Derived &d, void *counts, float *omega,
-                     soma::FieldPartials *partials, hipStream_t s, float *halo = nullptr,
+                     soma::FieldPartials *partials, hipStream_t s, uint32_t *halo = nullptr,
                      uint32_t *ctr = nullptr, uint32_t ctr_by = 0) {
   const uint32_t blocks = d.field_blocks;
   if (d.n_types > 2) {   // no halo copy, external fields or walls with more than two types
@@ -489,7 +488,7 @@ struct soma_system {
   soma::FieldPartials *fpart() { return reinterpret_cast<soma::FieldPartials *>(ws + d.off_fpart); }
   soma::Totals *totals() { return reinterpret_cast<soma::Totals *>(ws + d.off_totals); }
   double *opart() { return reinterpret_cast<double *>(ws + d.off_opart); }
-  float *halo() { return d.halo_plane ? reinterpret_cast<float *>(ws + d.off_halo) : nullptr; }
+  uint32_t *halo() { return d.halo_words ? reinterpret_cast<uint32_t *>(ws + d.off_halo) : nullptr; }
   unsigned long long *att() { return reinterpret_cast<unsigned long long *>(ws + d.off_att); }
   soma::ArchDev *arch(uint32_t sp) {
     return reinterpret_cast<soma::ArchDev *>(ws + d.off_arch + sp * align_up(sizeof(soma::ArchDev)));
@@ -671,7 +670,6 @@ void sweep_args(soma_system *sys, uint32_t sp, uint32_t kind, soma::SweepArgs &a
   mx.att_slots = sys->att();
   mx.err = sys->err();
   mx.halo = sys->halo();
-  mx.halo_plane = (uint32_t)sys->d.halo_plane;
 }
 
 bool species_vec2(const soma_system *sys, uint32_t sp) {

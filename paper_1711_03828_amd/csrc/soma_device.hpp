@@ -26,6 +26,15 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Two numbers rounded to BF16 (x in the low half).
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  bf16x2 w;
+  w[0] = (__bf16)x;
+  w[1] = (__bf16)y;
+  return __builtin_bit_cast(uint32_t, w);
+}
+
 struct Rand4 {
   uint32_t x, y, z, w;
 };

@@ -104,10 +104,10 @@ struct FieldArgs {
   float inv_rho, chi_n, kappa_n;
   FieldPartials *partials;  // may be null
   int clear;
-  // optional copy of the fields with one periodic halo cell at each end of every
-  // x row: [2][nz*ny][nx + 2] (null: not kept)
-  float *halo;
-  uint32_t nx, halo_plane;
+  // optional copy of the fields for the learned proposal's features, with one
+  // periodic halo cell at each end of every x row: [nz*ny][nx + 2] (null: not kept)
+  uint32_t *halo;
+  uint32_t nx;
   // external fields (null: none): ext [2][n_cells] added to the fields;
   // forbid one bit per cell (bit c % 32 of word c / 32): impenetrable cells get
   // the field 0 and are left out of H_nb
@@ -141,29 +141,34 @@ __device__ __forceinline__ void field_extras(const FieldArgs &a, uint32_t c, boo
   if (off) va = vb = 0.0f;
 }
 
+// A cell of the halo copy is one word: both fields as the BF16 numbers that the
+// network takes (A in the low half), rounded here once instead of at every gather,
+// so that the three cells of a row and both types are one 12-byte load.
+//
+// Writes the cell at column x of row r into the halo copy (and into the halo cell
+// that mirrors it when x is at either end).
+__device__ __forceinline__ void halo_put_rx(const FieldArgs &a, uint32_t r, uint32_t x, float va,
+                                            float vb) {
+  uint32_t *h = a.halo + (size_t)r * (a.nx + 2u);
+  const uint32_t v = bf16_pair(va, vb);
+  h[x + 1u] = v;
+  if (x == 0u) h[a.nx + 1u] = v;
+  if (x + 1u == a.nx) h[0] = v;
+}
+
 // The same for four consecutive cells of one row (nx % 4 == 0, x % 4 == 0): one
-// 16-byte store per plane, 4-byte aligned.
+// 16-byte store, 4-byte aligned.
 typedef float f32x4_halo __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_halo __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ void halo_put4(const FieldArgs &a, uint32_t r, uint32_t x,
                                           const float (&va)[4], const float (&vb)[4]) {
-  float *ha = a.halo + (size_t)r * (a.nx + 2u), *hb = ha + a.halo_plane;
-  *reinterpret_cast<f32x4_halo *>(ha + x + 1u) = f32x4_halo{va[0], va[1], va[2], va[3]};
-  *reinterpret_cast<f32x4_halo *>(hb + x + 1u) = f32x4_halo{vb[0], vb[1], vb[2], vb[3]};
-  if (x == 0u) { ha[a.nx + 1u] = va[0]; hb[a.nx + 1u] = vb[0]; }
-  if (x + 4u == a.nx) { ha[0] = va[3]; hb[0] = vb[3]; }
-}
-
-// Writes the two field values of the cell at column x of row r into the halo
-// copy (and into the halo cell that mirrors it when x is at either end).
-__device__ __forceinline__ void halo_put_rx(const FieldArgs &a, uint32_t r, uint32_t x, float va,
-                                            float vb) {
-  const uint32_t w = a.nx + 2u;
-  float *ha = a.halo + (size_t)r * w, *hb = ha + a.halo_plane;
-  ha[x + 1u] = va;
-  hb[x + 1u] = vb;
-  if (x == 0u) { ha[a.nx + 1u] = va; hb[a.nx + 1u] = vb; }
-  if (x + 1u == a.nx) { ha[0] = va; hb[0] = vb; }
+  uint32_t *h = a.halo + (size_t)r * (a.nx + 2u);
+  const u32x4_halo v = {bf16_pair(va[0], vb[0]), bf16_pair(va[1], vb[1]), bf16_pair(va[2], vb[2]),
+                        bf16_pair(va[3], vb[3])};
+  *reinterpret_cast<u32x4_halo *>(h + x + 1u) = v;
+  if (x == 0u) h[a.nx + 1u] = v[0];
+  if (x + 4u == a.nx) h[0] = v[3];
 }
 
 __device__ __forceinline__ void halo_put(const FieldArgs &a, uint32_t c, float va, float vb) {

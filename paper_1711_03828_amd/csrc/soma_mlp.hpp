@@ -284,21 +284,6 @@ __device__ __forceinline__ void gather_features(const Grid &g, const Neighbourho
   f[57] = bn.x; f[58] = bn.y; f[59] = bn.z;
 }
 
-// The 60 raw features of a row as BF16 (entries 60..63 zero), 8 at a time:
-// the learned move's first layer holds the standardisation.
-__device__ __forceinline__ void store_row(const float (&f)[kNF], __bf16 *row) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    bf16x8 v;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = 8 * c + j;
-      v[j] = k < kNF ? (__bf16)f[k < kNF ? k : 0] : (__bf16)0.0f;
-    }
-    *reinterpret_cast<bf16x8 *>(row + 8 * c) = v;
-  }
-}
-
 // Rewrites only the bond features (54..59) of a row, whose field features are
 // current.
 __device__ __forceinline__ void bond_features_to_row(F3 bp, F3 bn, __bf16 *row) {
@@ -316,46 +301,43 @@ __device__ __forceinline__ void bond_features_to_row(F3 bp, F3 bn, __bf16 *row) 
   *reinterpret_cast<bf16x8 *>(row + 56) = hi;
 }
 
-// Gathers the 60 features of a bead at r into one LDS row of bf16.  Returns
-// the bead's own field in its cell; `cell` receives that cell's index.
-__device__ __forceinline__ float features_to_row(const Grid &g, const float *__restrict__ omega,
-                                                 bool is_b, F3 r, F3 bp, F3 bn, __bf16 *row,
-                                                 uint32_t &cell) {
-  const Neighbourhood nb = neighbourhood(g, r);
-  float f[kNF];
-  gather_features(g, nb, omega, is_b ? g.n_cells : 0u, is_b ? 0u : g.n_cells, bp, bn, f);
-  store_row(f, row);
-  cell = nb.centre;
-  return f[13];   // own field at (dz, dy, dx) = (0, 0, 0)
-}
-
-// features_to_row from the halo copy of the fields ([2][nz*ny][nx + 2], plane
-// size `halo_plane`): each of the 18 rows of three cells is one 12-byte load.
-__device__ __forceinline__ float features_to_row_halo(const Grid &g, const float *__restrict__ halo,
-                                                      uint32_t halo_plane, bool is_b, F3 r,
-                                                      F3 bp, F3 bn, __bf16 *row, uint32_t &cell) {
+// The 60 features of a bead at r into one LDS row of BF16 (entries 60..63 zero): the
+// learned move's first layer holds the standardisation.  `cell` receives the bead's
+// cell.  Fields from the halo copy ([nz*ny][nx + 2], a cell's two BF16 fields per
+// word): nine 12-byte loads of three cells, then byte permutes put
+// the values of the own type before those of the other one.  (Two FP32 planes need
+// 18 loads and 19 cache lines per bead, and outgrow an XCD's L2 on 96^3 cells; the
+// network's inputs are these BF16 numbers either way.)
+__device__ __forceinline__ void features_to_row(const Grid &g, const uint32_t *__restrict__ halo,
+                                                bool is_b, F3 r, F3 bp, F3 bn, __bf16 *row,
+                                                uint32_t &cell) {
   uint32_t cx, cy, cz;
   cell3(g, r.x, r.y, r.z, cx, cy, cz);
   const uint32_t w = (uint32_t)g.nx + 2u;
   const uint32_t ys[3] = {cy == 0 ? g.ny - 1u : cy - 1u, cy, cy + 1 == (uint32_t)g.ny ? 0u : cy + 1u};
   const uint32_t zs[3] = {cz == 0 ? g.nz - 1u : cz - 1u, cz, cz + 1 == (uint32_t)g.nz ? 0u : cz + 1u};
-  const uint32_t own = is_b ? halo_plane : 0u, oth = is_b ? 0u : halo_plane;
-  float f[kNF];
+  typedef uint32_t u32x3u __attribute__((ext_vector_type(3), aligned(4)));
+  uint32_t d[27];
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
     const uint32_t rowb = (zs[q / 3] * (uint32_t)g.ny + ys[q % 3]) * w + cx;
-    const f32x3u a = *reinterpret_cast<const f32x3u *>(reinterpret_cast<const char *>(halo) +
-                                                      ((own + rowb) << 2));
-    const f32x3u b = *reinterpret_cast<const f32x3u *>(reinterpret_cast<const char *>(halo) +
-                                                      ((oth + rowb) << 2));
-    f[3 * q] = a.x; f[3 * q + 1] = a.y; f[3 * q + 2] = a.z;
-    f[27 + 3 * q] = b.x; f[28 + 3 * q] = b.y; f[29 + 3 * q] = b.z;
+    const u32x3u a = *reinterpret_cast<const u32x3u *>(reinterpret_cast<const char *>(halo) + (rowb << 2));
+    d[3 * q] = a.x; d[3 * q + 1] = a.y; d[3 * q + 2] = a.z;
   }
-  f[54] = bp.x; f[55] = bp.y; f[56] = bp.z;
-  f[57] = bn.x; f[58] = bn.y; f[59] = bn.z;
-  store_row(f, row);
+  // units 0..26 the own type's cells, 27..53 the other type's, two per word
+  const uint32_t lo = 0x05040100u, hi = 0x07060302u;
+  const uint32_t own = is_b ? hi : lo, oth = is_b ? lo : hi, mid = is_b ? 0x05040302u : 0x07060100u;
+  u32x4 v[7];
+#pragma unroll
+  for (int j = 0; j < 27; ++j)
+    v[j / 4][j % 4] = j < 13 ? __builtin_amdgcn_perm(d[2 * j + 1], d[2 * j], own)
+                      : j == 13 ? __builtin_amdgcn_perm(d[0], d[26], mid)
+                                : __builtin_amdgcn_perm(d[(2 * j - 26) % 27], d[(2 * j - 27) % 27], oth);
+  v[6][3] = bf16_pair(bp.x, bp.y);
+#pragma unroll
+  for (int c = 0; c < 7; ++c) *reinterpret_cast<u32x4 *>(row + 8 * c) = v[c];
+  *reinterpret_cast<u32x4 *>(row + 56) = u32x4{bf16_pair(bp.z, bn.x), bf16_pair(bn.y, bn.z), 0u, 0u};
   cell = cell_index(g, cx, cy, cz);
-  return f[13];   // own field at (dz, dy, dx) = (0, 0, 0)
 }
 
 // Gaussian head of one sample: mean, sigma and log sigma.

@@ -758,8 +758,7 @@ struct MixArgs {
   float p_learn;                   // probability of the learned move (state-independent)
   unsigned long long *att_slots;   // [kAccSlots] attempted learned moves
   uint32_t *err;                   // device error word (bit 2: non-finite network output)
-  const float *halo;               // fields with x halos [2][nz*ny][nx + 2] (p_learn > 0)
-  uint32_t halo_plane;
+  const uint32_t *halo;            // BF16 fields with x halos [nz*ny][nx + 2] (p_learn > 0)
 };
 
 // ---------------------------------------------------------------------------
@@ -823,7 +822,7 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
     float w_old, w_new, log_q = 0.0f;
     bool net_bad = false;
     if (__ballot(learned) != 0ull) {
-      features_to_row_halo(a.grid, mx.halo, mx.halo_plane, is_b, r, has_l ? left - r : zero3,
+      features_to_row(a.grid, mx.halo, is_b, r, has_l ? left - r : zero3,
                            has_r ? right - r : zero3, row, co);
       w_old = field_at(a.omega, pl, co);   // energies from the field itself
       wave_forward(mx.net, sw, act, zb);
@@ -843,7 +842,7 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
       const F3 bpn = has_l ? left - rn : zero3, bnn = has_r ? right - rn : zero3;
       if (cn != co) {
         uint32_t c2;
-        features_to_row_halo(a.grid, mx.halo, mx.halo_plane, is_b, rn, bpn, bnn, row, c2);
+        features_to_row(a.grid, mx.halo, is_b, rn, bpn, bnn, row, c2);
       } else {
         bond_features_to_row(bpn, bnn, row);
       }
