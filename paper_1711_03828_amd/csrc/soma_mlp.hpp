@@ -87,17 +87,29 @@ __device__ __forceinline__ bf16x8 lds_b8(const __bf16 *p) {
 // bf16 per row (64 + 8 padding: the 16 rows one MFMA A operand reads land in
 // different banks).
 constexpr int kWStride = 72, kWRows = 144;
+// Behind them the biases in FP32 (64, 64 and 16).  Read from LDS where they are
+// used; from global memory the compiler keeps all of them in registers.
+constexpr int kWBias = kWRows * kWStride, kWSize = kWBias + 2 * 144;
 
-// Copies the network's weights to `sw` (all threads of the block; the caller
-// synchronises before the first read).
+// Copies the network's weights and biases to `sw` (all kNetBlock threads of the block;
+// the caller synchronises before the first read).  w1f, w2, w3 and b1f, b2, b3 lie in
+// a row; all loads are in flight together.
+constexpr uint32_t kNetBlock = 256u;   // threads of the blocks that evaluate the network
+
 __device__ __forceinline__ void net_weights_to_lds(const NetDev *__restrict__ net, __bf16 *sw) {
-  for (uint32_t i = threadIdx.x; i < (uint32_t)kWRows * 8u; i += blockDim.x) {
-    const uint32_t r = i >> 3, c = i & 7u;
-    const __bf16 *src = r < 64u ? net->w1f + r * 64u : (r < 128u ? net->w2 + (r - 64u) * 64u
-                                                                 : net->w3 + (r - 128u) * 64u);
-    *reinterpret_cast<uint4 *>(sw + r * kWStride + 8u * c) =
-        *reinterpret_cast<const uint4 *>(src + 8u * c);
+  constexpr uint32_t kWords = (uint32_t)kWRows * 8u, kN = (kWords + kNetBlock - 1u) / kNetBlock;
+  const uint4 *src = reinterpret_cast<const uint4 *>(net->w1f);
+  float *sb = reinterpret_cast<float *>(sw + kWBias);
+  uint4 v[kN];
+#pragma unroll
+  for (uint32_t q = 0; q < kN; ++q) v[q] = src[min(threadIdx.x + q * kNetBlock, kWords - 1u)];
+  const float b = net->b1f[min(threadIdx.x, 143u)];
+#pragma unroll
+  for (uint32_t q = 0; q < kN; ++q) {
+    const uint32_t i = threadIdx.x + q * kNetBlock;
+    if (i < kWords) *reinterpret_cast<uint4 *>(sw + (i >> 3) * kWStride + 8u * (i & 7u)) = v[q];
   }
+  if (threadIdx.x < 144u) sb[threadIdx.x] = b;
 }
 
 // B-operand fragments of a layer's input for the wave's 64 samples: [kb][t]
@@ -131,11 +143,10 @@ __device__ __forceinline__ void frag_from_lds(const __bf16 *act, Frag &f) {
 // Y (g >= 2).  v_permlane32_swap(X, Y) gives [X0 X1 Y0 Y1] and [X2 X3 Y2 Y3]
 // (rows), v_permlane16_swap of those gives [X0 X2 Y0 Y2] (the first four
 // units) and [X1 X3 Y1 Y3] (the last four).
-__device__ __forceinline__ void hidden_layer(const __bf16 *w, const float *__restrict__ bias,
+__device__ __forceinline__ void hidden_layer(const __bf16 *w, const float *bias,
                                              const Frag &in, Frag &out) {
   const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  typedef short i16x4 __attribute__((ext_vector_type(4)));
+  typedef short i16x2 __attribute__((ext_vector_type(2)));
   u32x2 p[4][4];   // [output tile mt][sample tile t]: 4 BF16 units per lane
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
@@ -152,9 +163,14 @@ __device__ __forceinline__ void hidden_layer(const __bf16 *w, const float *__res
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const bf16x4 v = __builtin_convertvector(acc[t], bf16x4);
-      const i16x4 h = __builtin_elementwise_max(__builtin_bit_cast(i16x4, v), (i16x4)0);
-      p[mt][t] = __builtin_bit_cast(u32x2, h);
+      // pairs, kept apart: the vectoriser makes fours of them, which are converted one
+      // number at a time and merged again
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        uint32_t v = bf16_pair(acc[t][2 * c], acc[t][2 * c + 1]);
+        asm("" : "+v"(v));
+        p[mt][t][c] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, v), (i16x2)0));
+      }
     }
   }
 #pragma unroll
@@ -176,15 +192,17 @@ __device__ __forceinline__ void hidden_layer(const __bf16 *w, const float *__res
 
 // Network output z (6 per sample) for the 64 samples whose raw inputs are in
 // LDS tile `act` (row = lane); weights from the block's LDS copy `sw`
-// (net_weights_to_lds), biases from `net`.  z of sample s lands in
-// zout[8 s .. 8 s + 5] (zout may alias `act`: it is written after the last
-// read of `act`).
-__device__ __forceinline__ void wave_forward(const NetDev *__restrict__ net, const __bf16 *sw,
-                                             const __bf16 *act, float *zout) {
+// (net_weights_to_lds).  z of a sample replaces the end of its
+// row, the four zero entries and the padding (row_output); whoever writes the
+// row's features again writes those zeros too.
+__device__ __forceinline__ float *row_output(__bf16 *row) { return reinterpret_cast<float *>(row + 60); }
+
+__device__ __forceinline__ void wave_forward(const __bf16 *sw, __bf16 *act) {
+  const float *sb = reinterpret_cast<const float *>(sw + kWBias);
   Frag f0, f1;
   frag_from_lds(act, f0);
-  hidden_layer(sw, net->b1f, f0, f1);
-  hidden_layer(sw + 64 * kWStride, net->b2, f1, f0);
+  hidden_layer(sw, sb, f0, f1);
+  hidden_layer(sw + 64 * kWStride, sb + 64, f1, f0);
   const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
   f32x4 acc[4];
 #pragma unroll
@@ -197,11 +215,14 @@ __device__ __forceinline__ void wave_forward(const NetDev *__restrict__ net, con
       acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f0.b[kb][t], acc[t], 0, 0, 0);
   }
   __builtin_amdgcn_wave_barrier();
-  if (g < 2) {
+  if (g < 2) {   // lane row 0 holds outputs 0..3, row 1 outputs 4 and 5
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(sb + 128 + 4 * g);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) zout[(16 * t + col) * 8 + 4 * g + r] = acc[t][r] + net->b3[4 * g + r];
+    for (int t = 0; t < 4; ++t) {
+      float2 *z = reinterpret_cast<float2 *>(row_output(act + (16 * t + col) * kActStride) + 4 * g);
+      z[0] = make_float2(acc[t][0] + b[0], acc[t][1] + b[1]);
+      if (g == 0) z[1] = make_float2(acc[t][2] + b[2], acc[t][3] + b[3]);
+    }
   }
 }
 
@@ -359,7 +380,6 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const NetDev *__restri
                                                           const float *__restrict__ feat,
                                                           uint32_t n, float *__restrict__ z) {
   __shared__ __bf16 s_act[4][64 * kActStride];
-  __shared__ float s_z[4][64 * 8];
   const uint32_t wv = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint32_t s = (blockIdx.x * 4u + wv) * 64u + lane;
   __bf16 *row = &s_act[wv][lane * kActStride];
@@ -374,13 +394,13 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const NetDev *__restri
     }
     *reinterpret_cast<bf16x8 *>(row + 8 * c) = v;
   }
-  __shared__ __bf16 s_w[kWRows * kWStride];
+  __shared__ __attribute__((aligned(16))) __bf16 s_w[kWSize];
   net_weights_to_lds(net, s_w);
   __syncthreads();
-  wave_forward(net, s_w, s_act[wv], s_z[wv]);
+  wave_forward(s_w, s_act[wv]);
   if (s < n)
 #pragma unroll
-    for (int o = 0; o < kNO; ++o) z[(size_t)s * kNO + o] = s_z[wv][lane * 8 + o];
+    for (int o = 0; o < kNO; ++o) z[(size_t)s * kNO + o] = row_output(row)[o];
 }
 
 }  // namespace soma

@@ -770,13 +770,12 @@ struct MixArgs {
 // non-finite network output rejects it and raises error bit 2.  The network
 // needs the bond vectors, so the two sets are handled one after the other.
 // ---------------------------------------------------------------------------
-// One wave's chains; act is the wave's LDS feature tile, zb its LDS tile of
-// network outputs ([64][8] floats), sw the block's LDS copy of the network's
-// weights.  Returns through cnt the wave's accepted local moves, accepted
+// One wave's chains; act is the wave's LDS feature tile, sw the block's LDS copy of
+// the network's weights.  Returns through cnt the wave's accepted local moves, accepted
 // learned moves and learned attempts.
 template <bool COUNT64, bool VEC2, bool BINNED, class Bins>
 __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx, const LaneMap &m,
-                                           __bf16 *act, float *zb, const __bf16 *sw,
+                                           __bf16 *act, const __bf16 *sw,
                                            uint32_t cnt[3], Bins &bins) {
   __bf16 *row = act + m.lane * kActStride;
   const uint32_t N = a.n;
@@ -825,9 +824,9 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
       features_to_row(a.grid, mx.halo, is_b, r, has_l ? left - r : zero3,
                            has_r ? right - r : zero3, row, co);
       w_old = field_at(a.omega, pl, co);   // energies from the field itself
-      wave_forward(mx.net, sw, act, zb);
+      wave_forward(sw, act);
       float mu[3], sig[3], lsig[3];
-      head(zb + m.lane * 8, mx.head, mu, sig, lsig);
+      head(row_output(row), mx.head, mu, sig, lsig);
       float xi0, xi1, xi2, xi3;
       box_muller(w.x, w.y, xi0, xi1);
       box_muller(w.z, w.w, xi2, xi3);
@@ -847,9 +846,9 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
         bond_features_to_row(bpn, bnn, row);
       }
       w_new = cn == co ? w_old : field_at(a.omega, pl, cn);
-      wave_forward(mx.net, sw, act, zb);
+      wave_forward(sw, act);
       float mun[3], sign[3], lsign[3];
-      head(zb + m.lane * 8, mx.head, mun, sign, lsign);
+      head(row_output(row), mx.head, mun, sign, lsign);
       float lq = 0.0f;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
@@ -926,12 +925,16 @@ __device__ __forceinline__ void mixed_finish(const SweepArgs &a, const MixArgs &
   __syncthreads();
 }
 
+// Blocks of four waves: feature tiles of 9.2 KB a wave and one copy of the weights
+// (21.3 KB), two blocks per compute unit, so two waves per SIMD; told so, the compiler
+// keeps the matrix results in ordinary registers.  Six waves a block (three per SIMD)
+// spill: 95 us where four take 88 (1M beads).  Bound by vector instructions (60% of
+// the time; the matrix cores 18%) and the gathers.
 template <bool COUNT64, bool VEC2, bool BINNED, bool PERSIST = false>
-__global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_in,
-                                                             const MixArgs mx) {
+__global__ __launch_bounds__(256, 2)
+void mc_sweep_mixed_kernel(const SweepArgs a_in, const MixArgs mx) {
   __shared__ __bf16 s_act[4][64 * kActStride];
-  __shared__ float s_z[4][64 * 8];
-  __shared__ __bf16 s_w[kWRows * kWStride];
+  __shared__ __attribute__((aligned(16))) __bf16 s_w[kWSize];
   __shared__ BinSlot<BINNED, 4u, PERSIST> s_bin;
   if constexpr (BINNED) bins_begin(s_bin);
   net_weights_to_lds(mx.net, s_w);
@@ -940,8 +943,7 @@ __global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_i
   const uint32_t wib = threadIdx.x >> 6;
   uint32_t cnt[3] = {0u, 0u, 0u};
   if (!PERSIST) {   // one tile per wave
-    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map(a), s_act[wib], s_z[wib], s_w, cnt,
-                                      s_bin);
+    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map(a), s_act[wib], s_w, cnt, s_bin);
     mixed_finish(a, mx, cnt);
     return;
   }
@@ -951,8 +953,8 @@ __global__ __launch_bounds__(256) void mc_sweep_mixed_kernel(const SweepArgs a_i
   while (t < it.t_end) {
     const uint32_t vn = tile_draw(it);
     uint32_t c[3];
-    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map_tile(a, t, true), s_act[wib], s_z[wib],
-                                      s_w, c, s_bin);
+    mixed_wave<COUNT64, VEC2, BINNED>(a, mx, lane_map_tile(a, t, true), s_act[wib], s_w, c,
+                                      s_bin);
     cnt[0] += c[0];
     cnt[1] += c[1];
     cnt[2] += c[2];
