@@ -210,14 +210,14 @@ int32_t launch_apply(const soma_config *c, const Derived &d, const soma::BinArgs
                      uint32_t planes, hipStream_t s) {
   const bool c64 = c->count_width == 32, few = d.n_bricks < soma::kFewBricks;
   const size_t lds = (size_t)planes * soma::kBrickCells * (c64 ? 8u : 4u);
-  const dim3 grid((uint32_t)d.n_bricks), block(few ? soma::kApplyWide : soma::kApplyNarrow);
+  const dim3 grid((uint32_t)d.n_bricks), block(few ? soma::kApplyOnlyWide : soma::kApplyNarrow);
   const soma::Grid g = make_grid(c, d.n_cells);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, lds, s, b, g, counts, planes);
   };
   if (few) {
-    if (c64) launch(soma::bin_apply_kernel<true, soma::kApplyWide>);
-    else launch(soma::bin_apply_kernel<false, soma::kApplyWide>);
+    if (c64) launch(soma::bin_apply_kernel<true, soma::kApplyOnlyWide>);
+    else launch(soma::bin_apply_kernel<false, soma::kApplyOnlyWide>);
   } else {
     if (c64) launch(soma::bin_apply_kernel<true, soma::kApplyNarrow>);
     else launch(soma::bin_apply_kernel<false, soma::kApplyNarrow>);
@@ -235,20 +235,29 @@ int32_t launch_hist(const soma_config *c, const Derived &d, const float *pos, vo
   if (rc) return rc;
   const soma::Grid g = make_grid(c, d.n_cells);
   if (bins) {
-    for (uint32_t sp = 0; sp < c->n_species; ++sp) {
-      const soma_species &S = c->species[sp];
-      const uint64_t nb = (uint64_t)S.n_chains * S.n;
+    static_assert(soma::kHistSpecies >= SOMA_MAX_SPECIES, "a slot for every species");
+    constexpr uint64_t kMaxBlocks = 1ull << 23;   // a launch has fewer than 2^32 threads
+    soma::HistArgs h{};
+    uint64_t blocks = 0;
+    for (uint32_t sp = 0; sp <= c->n_species; ++sp) {
+      const uint64_t nb = sp < c->n_species ? (uint64_t)c->species[sp].n_chains * c->species[sp].n : 0u;
+      const uint64_t more = ((nb + 1) / 2 + 255) / 256;
+      if (blocks && (sp == c->n_species || blocks + more > kMaxBlocks)) {
+        const dim3 grid((uint32_t)blocks);
+        if (c->count_width == 32)
+          hipLaunchKernelGGL(soma::density_hist_binned_kernel<true>, grid, dim3(256), 0, s, h, g, counts, *bins);
+        else
+          hipLaunchKernelGGL(soma::density_hist_binned_kernel<false>, grid, dim3(256), 0, s, h, g, counts, *bins);
+        LAUNCH_TRY();
+        h = soma::HistArgs{};
+        blocks = 0;
+      }
       if (!nb) continue;
-      const uint64_t blocks = ((nb + 1) / 2 + 255) / 256;
+      const soma_species &S = c->species[sp];
       const float *p = pos + 3 * d.bead_off[sp];
       const uint32_t v2 = (reinterpret_cast<uintptr_t>(p) % 8u) == 0u ? 1u : 0u;
-      if (c->count_width == 32)
-        hipLaunchKernelGGL(soma::density_hist_binned_kernel<true>, dim3((uint32_t)blocks),
-                           dim3(256), 0, s, p, nb, S.n, S.n_a, g, counts, d.arch[sp], *bins, v2);
-      else
-        hipLaunchKernelGGL(soma::density_hist_binned_kernel<false>, dim3((uint32_t)blocks),
-                           dim3(256), 0, s, p, nb, S.n, S.n_a, g, counts, d.arch[sp], *bins, v2);
-      LAUNCH_TRY();
+      h.sp[h.n_species++] = {p, d.arch[sp], nb, S.n, S.n_a, v2, (uint32_t)blocks};
+      blocks += more;
     }
     return launch_apply(c, d, *bins, counts, (d.n_types + 1u) / 2u, s);
   }

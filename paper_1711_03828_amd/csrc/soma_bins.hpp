@@ -304,18 +304,38 @@ __device__ __forceinline__ void bin_moves(BinLds<WAVES, WAVEWISE> &s, const BinA
                       same1 ? (hm1 | (hp1 << 16)) : hm1, hp1 << 16, want);
 }
 
-// From-scratch histogram of one species through the bins (counts cleared
-// before): lane q of the grid takes beads 2q and 2q+1 of the species (one
-// entry when both lie in one brick), so that a block of 512 consecutive beads
+// From-scratch histogram through the bins (counts cleared before): species s owns
+// the blocks [first[s], first[s + 1]), and lane q of them takes its beads 2q and 2q+1
+// (one entry when both lie in one brick), so that a block of 512 consecutive beads
 // reserves room once per brick it touches.  Positions are read as three
-// 8-byte pairs when `vec2` (8-byte aligned species start).
+// 8-byte pairs where `vec2` (8-byte aligned species start).  One launch for all
+// species: three of 3.0M, 0.7M and 0.7M beads take 30.4 us, 38.4 in launches of their
+// own, and two gaps less.
+constexpr uint32_t kHistSpecies = 8u;
+struct HistSpecies {
+  const float *pos;
+  const ArchDev *arch;
+  uint64_t n_beads;
+  uint32_t n, n_a, vec2, first;
+};
+struct HistArgs {
+  HistSpecies sp[kHistSpecies];   // of n_species used; `first` ascending
+  uint32_t n_species;
+};
+
 template <bool COUNT64>
-__global__ __launch_bounds__(256) void density_hist_binned_kernel(
-    const float *pos, uint64_t n_beads, uint32_t n, uint32_t n_a, Grid g, void *counts,
-    const ArchDev *arch, BinArgs b, uint32_t vec2) {
+__global__ __launch_bounds__(256) void density_hist_binned_kernel(const HistArgs h, Grid g,
+                                                                  void *counts, BinArgs b) {
   __shared__ BinLds<4u, false> s_bin;
   bins_begin(s_bin);
-  const uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  uint32_t sp = 0;
+  for (uint32_t k = 1; k < h.n_species; ++k) sp = blockIdx.x >= h.sp[k].first ? k : sp;
+  const HistSpecies &S = h.sp[sp];
+  const float *pos = S.pos;
+  const ArchDev *arch = S.arch;
+  const uint64_t n_beads = S.n_beads;
+  const uint32_t n = S.n, n_a = S.n_a, vec2 = S.vec2;
+  const uint64_t q = (uint64_t)(blockIdx.x - S.first) * blockDim.x + threadIdx.x;
   const uint64_t i0 = 2 * q, i1 = 2 * q + 1;
   const bool has0 = i0 < n_beads, has1 = i1 < n_beads;
   float r[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -353,11 +373,13 @@ __global__ __launch_bounds__(256) void density_hist_binned_kernel(
 // their entries are taken as one flat index range, kApplyBatch independent
 // loads per thread at a time, so that a block waits on memory a few times
 // rather than twice per sub-bin.
-// 512 threads where the bricks are few and every round trip counts (a film of 450
-// bricks: 11.5 us with the fields, 16.8 with 256), 256 where there are enough
-// of them to fill the device (13,824 bricks: 152 us, 157 with 512).
+// Where the bricks are few and every round trip counts, 512 threads with the fields
+// (a film of 450 bricks: 11.5 us, 16.8 with 256; 131x97x88 cells, 693 bricks: 23, 33
+// with 1024) and 1024 without them, mostly a recount, whose bins are full (420 bricks:
+// 15.8 us, 17.0 with 512; the film: 29 and 36); 256 where there are enough bricks to
+// fill the device (13,824: 152 us, 157 with 512).
 // LDS: planes x 2048 words (u16 pairs) or 2 x planes x 2048 halves (u32 pairs).
-constexpr uint32_t kApplyWide = 512u, kApplyNarrow = 256u;
+constexpr uint32_t kApplyOnlyWide = 1024u, kApplyWide = 512u, kApplyNarrow = 256u;
 constexpr uint32_t kApplyBatch = 4u;
 
 template <bool COUNT64>
