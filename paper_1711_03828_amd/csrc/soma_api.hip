@@ -77,6 +77,7 @@ struct Derived {
   // per-brick bins of count updates (soma_set_histogram): bricks of 16 x 16 x 8 cells
   uint32_t nbx = 0, nby = 0, nbz = 0, bin_cap = 0, sub_shift = 0;
   uint64_t n_bricks = 0, off_bin_count = 0, off_bins = 0;
+  uint64_t off_blocked = 0, blocked_plane = 0;   // blocked copy of the fields (0: not kept)
   bool bins_ok = false;
   uint64_t off_queue = 0;   // tile counters of persistent local sweeps
 };
@@ -88,6 +89,15 @@ uint32_t obs_blocks(const soma_species &sp) {
   const uint32_t per = 4u * (64u / obs_lanes(sp));
   return std::min((sp.n_chains + per - 1u) / per, soma::kObsMaxBlocks);
 }
+
+// Counts of 64 MiB and more are read with the non-temporal hint (measured on the
+// 134M-bead melt: 3.7% off the SCMF cycle, the next sweep's field gathers hitting
+// the last-level cache more often).
+bool stream_counts(const soma_config *c, const Derived &d) {
+  return (uint64_t)d.n_cells * (c->count_width == 32 ? 8u : 4u) >= (64ull << 20);
+}
+// Positions larger than the last-level cache (256 MB) stream past it.
+bool stream_positions(const Derived &d) { return 12ull * d.n_beads > (256ull << 20); }
 
 int32_t derive(const soma_config *c, Derived *d) {
   if (!c) return fail(SOMA_E_INVAL, "config is NULL");
@@ -176,6 +186,12 @@ int32_t derive(const soma_config *c, Derived *d) {
     d->off_bin_count = d->ws_bytes;
     d->off_bins = align_up(d->off_bin_count + 4ull * d->n_bricks * n_sub);
     d->ws_bytes = align_up(d->off_bins + 4ull * d->n_bricks * n_sub * cap);
+    const uint64_t plane = d->n_bricks * soma::kBrickCells;
+    if (stream_counts(c, *d) && stream_positions(*d) && 8ull * plane < (1ull << 32)) {
+      d->blocked_plane = plane;
+      d->off_blocked = d->ws_bytes;
+      d->ws_bytes = align_up(d->off_blocked + 8ull * plane);
+    }
   }
   return SOMA_OK;
 }
@@ -297,13 +313,6 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.ctr = nullptr;
   a.ctr_by = 0;
   return a;
-}
-
-// Counts of 64 MiB and more are read with the non-temporal hint (measured on the
-// 134M-bead melt: 3.7% off the SCMF cycle, the next sweep's field gathers hitting
-// the last-level cache more often).
-bool stream_counts(const soma_config *c, const Derived &d) {
-  return (uint64_t)d.n_cells * (c->count_width == 32 ? 8u : 4u) >= (64ull << 20);
 }
 
 // ctr, ctr_by: sweep counter that this refresh advances (the last one of a call).
@@ -497,6 +506,7 @@ struct soma_system {
   soma::FieldPartials *fpart() { return reinterpret_cast<soma::FieldPartials *>(ws + d.off_fpart); }
   soma::Totals *totals() { return reinterpret_cast<soma::Totals *>(ws + d.off_totals); }
   double *opart() { return reinterpret_cast<double *>(ws + d.off_opart); }
+  float *blocked() { return d.blocked_plane ? reinterpret_cast<float *>(ws + d.off_blocked) : nullptr; }
   uint32_t *halo() { return d.halo_words ? reinterpret_cast<uint32_t *>(ws + d.off_halo) : nullptr; }
   unsigned long long *att() { return reinterpret_cast<unsigned long long *>(ws + d.off_att); }
   soma::ArchDev *arch(uint32_t sp) {
@@ -555,9 +565,12 @@ void launch_sweep_p(uint32_t kind, dim3 grid, dim3 threads, hipStream_t s,
     hipLaunchKernelGGL((soma::mc_sweep_smc_kernel<C64, V2, B, P>), grid, threads, 0, s, a);
   else if (kind == SOMA_MOVE_GIBBS)
     hipLaunchKernelGGL((soma::mc_sweep_gibbs_kernel<C64, V2, B, P>), grid, threads, 0, s, a);
-  else if (B && a.stream_pos)   // measured: no gain with direct atomics
-    hipLaunchKernelGGL((soma::mc_sweep_local_kernel<C64, V2, B, P, true>), grid, threads, 0, s, a);
-  else
+  else if (B && a.stream_pos) {   // measured: no gain with direct atomics
+    if (a.blocked_plane)
+      hipLaunchKernelGGL((soma::mc_sweep_local_kernel<C64, V2, B, P, B, B>), grid, threads, 0, s, a);
+    else
+      hipLaunchKernelGGL((soma::mc_sweep_local_kernel<C64, V2, B, P, B>), grid, threads, 0, s, a);
+  } else
     hipLaunchKernelGGL((soma::mc_sweep_local_kernel<C64, V2, B, P>), grid, threads, 0, s, a);
 }
 
@@ -669,8 +682,8 @@ void sweep_args(soma_system *sys, uint32_t sp, uint32_t kind, soma::SweepArgs &a
   a.self_term = sys->self_term ? self_energy(sys) : 0.0f;
   a.queue = nullptr;   // set by launch_sweep for persistent local grids
   a.wpb = 4u;          // 256-thread blocks unless launch_sweep picks another size
-  // positions larger than the last-level cache (256 MB) stream past it
-  a.stream_pos = 12ull * sys->d.n_beads > (256ull << 20) ? 1u : 0u;
+  a.stream_pos = stream_positions(sys->d) ? 1u : 0u;
+  a.blocked_plane = 0;   // set by launch_sweep where the fields are in the blocked copy
   mx.net = sys->net(sp);
   mx.head.m_max = c->mu_max;
   mx.head.lo = c->log_sigma_min;
@@ -732,14 +745,35 @@ bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
   return atomics > bins;
 }
 
+// Whether the sweep of chain subset j of k sends its count updates through the bins.
+bool sweep_binned(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
+  return sys->hist_mode == soma::kHistBinned ||
+         (sys->hist_auto && sys->scheme == SOMA_SCHEME_SET && bins_pay(sys, kind, k, j));
+}
+
+// Whether the fields between two sweeps of one call may live in the blocked copy alone:
+// plain local sweeps through the bins, whose updates are applied and fields written
+// by apply_field_kernel, of melts that keep the copy (their fields and positions
+// outgrow the caches, so that the sweep is bound by the lines it gathers, of which a
+// chain's cells share fewer when a line holds 4 x 4 x 2 of them: 134M beads, 1034 us
+// per sweep from the copy, 1199 from omega; the refresh takes 153 us into either).
+bool fields_blocked(const soma_system *sys, uint32_t kind, uint32_t k) {
+  if (!sys->d.blocked_plane || kind != SOMA_MOVE_LOCAL || sys->scheme != SOMA_SCHEME_SET ||
+      sys->arch_mask || sys->d.n_types > 2 || sys->d.forbid || sys->grad)
+    return false;
+  for (uint32_t j = 0; j < k; ++j)
+    if (!sweep_binned(sys, kind, k, j)) return false;
+  return true;
+}
+
 // One sweep of chain subset j of k of every species (k = 1: all chains); `off`
 // is added to the device sweep counter.  *pending (if not null) receives whether
 // the bins hold updates that are still to be applied; with null they are applied.
+// blocked: the fields are in the blocked copy (fields_blocked).
 int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t off,
-                     uint32_t k = 1, uint32_t j = 0, bool *pending = nullptr) {
+                     uint32_t k = 1, uint32_t j = 0, bool *pending = nullptr, bool blocked = false) {
   const soma_config *c = &sys->cfg;
-  const bool binned = sys->hist_mode == soma::kHistBinned ||
-                      (sys->hist_auto && sys->scheme == SOMA_SCHEME_SET && bins_pay(sys, kind, k, j));
+  const bool binned = sweep_binned(sys, kind, k, j);
   bool any_binned = false;
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
     const soma_species &S = c->species[sp];
@@ -752,6 +786,10 @@ int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t of
     a.sub_j = j;
     a.n_sub = subset_size(S.n_chains, k, j);
     if (a.n_sub == 0) continue;
+    if (blocked) {
+      a.omega = sys->blocked();
+      a.blocked_plane = (uint32_t)sys->d.blocked_plane;
+    }
     const bool c64 = c->count_width == 32;
     if (sys->arch_pair >> sp & 1u) {   // architecture of at most two independent sets
       const uint32_t per_wave = sys->arch_per_wave[sp], lanes = 64u / per_wave;
@@ -845,13 +883,16 @@ int32_t launch_grad(soma_system *sys, hipStream_t s) {
 // The bins applied and the fields refreshed in one launch (two bead types).
 // Without statistics one block per brick; with them at most as many as there are
 // partials, each over several bricks.
-int32_t launch_apply_field(soma_system *sys, hipStream_t s, bool stats, uint32_t advance) {
+// blocked: the fields go to the blocked copy instead of omega.
+int32_t launch_apply_field(soma_system *sys, hipStream_t s, bool stats, uint32_t advance,
+                           bool blocked) {
   const bool c64 = sys->cfg.count_width == 32;
   const size_t lds = (size_t)soma::kBrickCells * (c64 ? 8u : 4u);
   soma::FieldArgs a = field_args(&sys->cfg, sys->d, sys->buf.counts, sys->buf.omega,
                                  stats ? sys->fpart() : nullptr, sys->halo());
   a.ctr = advance ? sys->sweep_ctr() : nullptr;
   a.ctr_by = advance;
+  a.blocked = blocked ? sys->blocked() : nullptr;
   const uint32_t n_bricks = (uint32_t)sys->d.n_bricks, parts = sys->d.field_blocks;
   const bool nt = stream_counts(&sys->cfg, sys->d);
   const dim3 grid(stats ? std::min(n_bricks, parts) : n_bricks);
@@ -875,10 +916,10 @@ int32_t launch_apply_field(soma_system *sys, hipStream_t s, bool stats, uint32_t
 // applied), then the gradient field if kept.  advance > 0: the sweep counter moves
 // on by that many sweeps.  stats: leave the count sums and H_nb.
 int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0, bool pending = false,
-                       bool stats = true) {
+                       bool stats = true, bool blocked = false) {
   int32_t r = SOMA_OK;
   if (pending && sys->d.n_types <= 2) {
-    r = launch_apply_field(sys, s, stats, advance);
+    r = launch_apply_field(sys, s, stats, advance, blocked);
     if (!r && sys->grad) r = launch_grad(sys, s);
     return r;
   }
@@ -896,14 +937,20 @@ int32_t refresh_fields(soma_system *sys, hipStream_t s, uint32_t advance = 0, bo
 // device sweep counter by n (a launch of its own took 1.4 us of a small melt's
 // 12 us cycle, and the gap before it); only it leaves count sums and H_nb, which
 // nothing reads in between.
+// In between, the fields may go to the blocked copy alone: omega is current again
+// after the last refresh.
 int32_t enqueue_cycles(soma_system *sys, uint32_t n, uint32_t kind, hipStream_t s) {
   const uint32_t k = sys->substeps;
+  const bool may_block = fields_blocked(sys, kind, k);
+  bool blocked = false;   // where the last refresh left the fields
   for (uint32_t i = 0; i < n; ++i)
     for (uint32_t j = 0; j < k; ++j) {
       bool pending = false;
-      int32_t r = launch_sweep(sys, kind, s, i, k, j, &pending);
+      int32_t r = launch_sweep(sys, kind, s, i, k, j, &pending, blocked);
       const bool last = i + 1u == n && j + 1u == k;
-      if (!r) r = refresh_fields(sys, s, last ? n : 0u, pending, last);
+      if (r) return r;
+      blocked = may_block && pending && !last;
+      r = refresh_fields(sys, s, last ? n : 0u, pending, last, blocked);
       if (r) return r;
     }
   return SOMA_OK;

@@ -20,6 +20,7 @@ __device__ __forceinline__ void store_hint(T *p, T v) {
 // Blocks blk, blk + nblk, ... of the bricks of one grid.  With partials the
 // refresh also leaves the sums of the counts (one partial per block, zeros in
 // the rest of the n_parts entries that observables read).
+// NT grids may have the fields in the blocked copy instead of omega (a.blocked).
 // NT: counts and bin entries pass with the non-temporal hint (as in the field
 // kernel: grids whose counts outgrow the caches keep their fields there instead).
 template <bool COUNT64, bool NT, uint32_t THREADS>
@@ -59,8 +60,14 @@ __device__ __forceinline__ void apply_field_bricks(const BinArgs &b, const Grid 
         field_cell(na, nb, a, va, vb);
         const bool off = cell_forbidden(a.forbid, c);
         if (a.ext || a.forbid) field_extras(a, c, off, va, vb);
-        a.omega[c] = va;
-        a.omega[a.n_cells + c] = vb;
+        if (NT && a.blocked) {
+          const uint32_t o = blocked_cell((brick << 11) | i);
+          a.blocked[o] = va;
+          a.blocked[n_bricks * kBrickCells + o] = vb;
+        } else {
+          a.omega[c] = va;
+          a.omega[a.n_cells + c] = vb;
+        }
         if (a.halo) halo_put_rx(a, r, x, va, vb);
         if (stats) field_sum(sums, na, nb, off);
       }

@@ -67,6 +67,14 @@ __device__ __forceinline__ uint32_t brick_key(const BinArgs &b, uint32_t x, uint
   return (brick << 11) | ((z & 7u) << 8) | ((y & 15u) << 4) | (x & 15u);
 }
 
+// Place of the cell with this brick key in a blocked field plane (n_bricks x 2048
+// floats): the key with the cell's bits reordered to z2 z1 y3 y2 x3 x2 z0 y1 y0 x1 x0,
+// so that a 128-byte line holds 4 x 4 x 2 cells instead of 32 of one row.
+__device__ __forceinline__ uint32_t blocked_cell(uint32_t key) {
+  return (key & ~0x1FCu) | ((key & 0x0C0u) << 1) | ((key & 0x00Cu) << 3) | ((key & 0x100u) >> 4) |
+         ((key & 0x030u) >> 2);
+}
+
 // q = floor(c / d) for c < 2^29: an FP32 estimate, refined once with the
 // exact remainder (|error| of the estimate far below 2^23), then fixed by one.
 __device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t d, float inv_d) {

@@ -108,6 +108,7 @@ struct FieldArgs {
   // periodic halo cell at each end of every x row: [nz*ny][nx + 2] (null: not kept)
   uint32_t *halo;
   uint32_t nx;
+  float *blocked;   // see apply_field_bricks (null: the fields go to omega)
   // external fields (null: none): ext [2][n_cells] added to the fields;
   // forbid one bit per cell (bit c % 32 of word c / 32): impenetrable cells get
   // the field 0 and are left out of H_nb

@@ -28,7 +28,7 @@ namespace soma {
 
 struct SweepArgs {
   float *pos;                      // first bead of the species
-  const float *omega;              // [2][n_cells]
+  const float *omega;              // [2][n_cells], or [2][blocked_plane] (kernels with BLK)
   void *counts;                    // packed per-cell counts
   unsigned long long *acc_slots;   // [kAccSlots] accepted-move counters
   Grid grid;
@@ -66,6 +66,7 @@ struct SweepArgs {
   // persistent sweeps: kQueueParts x kQueueSub tile counters, kQueueStride words
   // apart, zero at every launch (null: the static tile order)
   uint32_t *queue;
+  uint32_t blocked_plane;
   // waves per block of the launch (blockDim.x / 64), as a kernel argument: it
   // loads with the other arguments, while the block size itself is a 16-bit
   // field that costs a vector load ahead of everything that depends on it
@@ -348,21 +349,29 @@ struct Trial {
   float wo, wn;
 };
 
+// A cell's place in the field planes: linear, or (BLK) in the blocked copy.
+template <bool BLK>
+__device__ __forceinline__ uint32_t cell_place(const SweepArgs &a, uint32_t x, uint32_t y, uint32_t z) {
+  return BLK ? blocked_cell(brick_key(a.bin, x, y, z)) : cell_index(a.grid, x, y, z);
+}
+
 // Old cell and its field value (plane `pl` floats into omega): the first gather.
+template <bool BLK = false>
 __device__ __forceinline__ void trial_from(const SweepArgs &a, uint32_t pl, Trial &b) {
   cell3(a.grid, b.r.x, b.r.y, b.r.z, b.x, b.y, b.z);
-  b.c = cell_index(a.grid, b.x, b.y, b.z);
+  b.c = cell_place<BLK>(a, b.x, b.y, b.z);
   b.wo = field_at(a.omega, pl, b.c);
 }
 
 // Trial position t = fma(a, v, r) (at most one cell away) and its cell.
+template <bool BLK = false>
 __device__ __forceinline__ void trial_to(const SweepArgs &a, Rand4 w, Trial &b) {
   b.t = F3{fmaf(a.step, uniform11(w.x), b.r.x), fmaf(a.step, uniform11(w.y), b.r.y),
            fmaf(a.step, uniform11(w.z), b.r.z)};
   b.sx = shift_cell(b.x, b.r.x, b.t.x, a.grid.nx);
   b.sy = shift_cell(b.y, b.r.y, b.t.y, a.grid.ny);
   b.sz = shift_cell(b.z, b.r.z, b.t.z, a.grid.nz);
-  b.n = cell_index(a.grid, b.sx, b.sy, b.sz);
+  b.n = cell_place<BLK>(a, b.sx, b.sy, b.sz);
 }
 
 // Energy change of the field term (and the self term of a move that changes cell).
@@ -408,8 +417,8 @@ __device__ __forceinline__ void trial_gather(const SweepArgs &a, uint32_t pla, T
 // ---------------------------------------------------------------------------
 // One wave's tile of local moves: positions r0/r1 already loaded for lane map m.
 // EVEN: every chain has an even number of beads, so a lane's two beads both
-// exist where the lane is active.
-template <bool COUNT64, bool EVEN, bool BINNED, bool NT = false, class Bins>
+// exist where the lane is active.  BLK: the fields are the blocked copy (no walls).
+template <bool COUNT64, bool EVEN, bool BINNED, bool NT = false, bool BLK = false, class Bins>
 __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap &m, float *cp,
                                                F3 r0, F3 r1, Bins &bins) {
   const uint32_t i0 = 2u * m.k;
@@ -426,11 +435,12 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
   A.r = sel(odd_first, r1, r0);
   B.r = sel(odd_first, r0, r1);
   const bool ta = ia >= a.n_a, tb = ib >= a.n_a;   // bead types
-  const uint32_t pla = ta ? a.grid.n_cells : 0u, plb = tb ? a.grid.n_cells : 0u;
-  trial_from(a, pla, A);
-  trial_from(a, plb, B);
-  trial_to(a, wa, A);
-  trial_to(a, wb, B);
+  const uint32_t plane = BLK ? a.blocked_plane : a.grid.n_cells;
+  const uint32_t pla = ta ? plane : 0u, plb = tb ? plane : 0u;
+  trial_from<BLK>(a, pla, A);
+  trial_from<BLK>(a, plb, B);
+  trial_to<BLK>(a, wa, A);
+  trial_to<BLK>(a, wb, B);
   // brick keys of the four cells now, so that the coordinates die here
   const uint32_t kfa = BINNED ? brick_key(a.bin, A.x, A.y, A.z) : 0u;
   const uint32_t kta = BINNED ? brick_key(a.bin, A.sx, A.sy, A.sz) : 0u;
@@ -492,7 +502,8 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
 // Registers capped for five waves per SIMD (96 VGPRs, no spills), so that the
 // persistent grid holds enough waves to cover the latency of its gathers and
 // of the bin reservations.
-template <bool COUNT64, bool VEC2, bool BINNED, bool PERSIST = false, bool NT = false>
+template <bool COUNT64, bool VEC2, bool BINNED, bool PERSIST = false, bool NT = false,
+          bool BLK = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5)))
 void mc_sweep_local_kernel(const SweepArgs a_in) {
   __shared__ BinSlot<BINNED, 8u, PERSIST> s_bin;
@@ -503,7 +514,7 @@ void mc_sweep_local_kernel(const SweepArgs a_in) {
     float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
     F3 r0, r1;
     load_pair<VEC2, NT>(cp, m, r0, r1);
-    finish_block(a, local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1, s_bin));
+    finish_block(a, local_tile<COUNT64, VEC2, BINNED, NT, BLK>(a, m, cp, r0, r1, s_bin));
     return;
   }
   const TileIter it = tile_iter(a);
@@ -515,7 +526,7 @@ void mc_sweep_local_kernel(const SweepArgs a_in) {
     float *cp = a.pos + (size_t)(m.has0 ? m.chain : 0u) * a.n * 3u + 6u * m.k;
     F3 r0, r1;
     load_pair<VEC2, NT>(cp, m, r0, r1);
-    n_acc += local_tile<COUNT64, VEC2, BINNED, NT>(a, m, cp, r0, r1, s_bin);
+    n_acc += local_tile<COUNT64, VEC2, BINNED, NT, BLK>(a, m, cp, r0, r1, s_bin);
     t = tile_of(it, vn);
   }
   finish_block(a, n_acc);

@@ -193,6 +193,42 @@ def test_default_mode_with_many_updates_equals_atomics(orc, kind, width, n, opti
     _compare(orc, melts[1], melts[0], sp, grid, "two sweeps")
 
 
+@pytest.mark.parametrize("width,grid,n,substeps,blocks,threads", [
+    (32, (261, 250, 133), 32, 1, 0, 512), (32, (261, 250, 133), 31, 2, 0, 256),
+    (16, (300, 293, 203), 32, 1, 1024, 512), (32, (261, 250, 133), 45, 1, 700, 256)])
+def test_several_cycles_in_one_call_equal_single_cycles(width, grid, n, substeps, blocks, threads):
+    """Melts past the last-level cache keep the fields between the cycles of one call in another
+    layout: the same bits as cycles called one by one, eager and captured, on ragged grids."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Melt
+    k0 = np.float32(3.0 * 31 / 36.0)
+    chains = 23_000_000 // n
+    cfg = custom_config(grid, [Species(chains, n, n // 2), Species(40_001, 16, 16)], k0=k0, n_ref=32,
+                        chi_n=25.0, kappa_n=50.0, local_a=0.45, count_width=width, seed=8)
+    melts = [Melt(cfg) for _ in range(3)]
+    flush("case", width, grid, n, substeps, blocks)
+    for m in melts:
+        m.set_histogram(C.SOMA_HIST_BINNED)
+        m.set_substeps(substeps)
+        C.soma_set_sweep_threads(m.handle, threads)
+        C.soma_set_sweep_blocks(m.handle, blocks)
+    single, several, graph = melts
+    graph.capture_cycle(3, C.SOMA_MOVE_LOCAL)
+    for rep in range(2):
+        for _ in range(3):
+            single.cycle(1, C.SOMA_MOVE_LOCAL)
+        several.cycle(3, C.SOMA_MOVE_LOCAL)
+        graph.run_cycle(1)
+        torch.cuda.synchronize()
+        for m in (several, graph):
+            assert torch.equal(m.pos, single.pos) and torch.equal(m.counts, single.counts), rep
+            assert torch.equal(m.omega, single.omega), rep
+            o = m.observables()
+            assert o.counts_conserved == 1 and o.error_flags == 0
+    for m in melts:
+        m.close()
+
+
 def test_binned_fullsize_equals_direct():
     """134,217,728 beads on 384x384x192 cells, 32-bit counts: one local sweep
     and one smart-MC sweep in each mode from the same state; positions and
