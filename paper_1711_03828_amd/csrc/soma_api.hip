@@ -310,6 +310,7 @@ soma::FieldArgs field_args(const soma_config *c, const Derived &d, void *counts,
   a.ext = d.ext;
   a.forbid = d.forbid;
   a.form = d.form;
+  a.blocked = nullptr;
   a.ctr = nullptr;
   a.ctr_by = 0;
   return a;
@@ -734,7 +735,7 @@ constexpr double kBinsPerLaunch = 10e-6;
 // of the sweep's barriers), a pass over the counts, and 0.1 ns per wave.  Per SCMF
 // cycle, atomics against bins, 256-thread blocks: 24^3 cells, 33k beads 8.1 / 12.5
 // us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71; film of 16M beads
-// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 54; bond-Gibbs moves of 1M beads
+// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 49; bond-Gibbs moves of 1M beads
 // 61 / 31; smart-MC moves of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their
 // blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
 // system, whose waves reserve room one by one.

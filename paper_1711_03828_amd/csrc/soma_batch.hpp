@@ -100,8 +100,8 @@ struct BinApplySeg {
 };
 
 // Small melts have few bricks in all (some 200 for 24 melts) and many updates in
-// each, so a brick takes 16 waves: 17.0 us for the apply and field launch, 20.2
-// with eight, 30.1 with four.
+// each, so a brick takes 16 waves (the apply and field launch before the entries were
+// taken pairwise: 17.0 us, 20.2 with eight, 30.1 with four; now 12.0).
 constexpr uint32_t kBatchApplyThreads = 1024u;
 
 template <bool COUNT64>
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kBatchApplyThreads) void batched_bin_apply_kernel(
 
 // The bins of every melt applied and its fields refreshed in one launch (melt s
 // owns the blocks [first[s], first[s + 1]), each over the melt's bricks in steps of
-// that many blocks), as apply_field_kernel.  24 melts of 0.5k to 33k chains: 17.0
+// that many blocks), as apply_field_kernel.  24 melts of 0.5k to 33k chains: 12.0
 // us where the two kernels before it took 14.3 and 5.0 and the gap between them 2;
 // with atomics the sweep took 60 us and the field kernel 5, with bins 37 and this.
 template <bool COUNT64>

@@ -38,7 +38,7 @@ constexpr uint32_t kUpdMinus = 0x4000u;
 // whose counters are few; 8 on larger ones, where the entries of a brick then lie
 // in fewer lines (134M-bead melt, 13,824 bricks: 1107 us per sweep, 1147 with 16;
 // a batch of small melts: 323 against 292 us the other way round).
-constexpr uint32_t kMaxSubShift = 4u, kSubBins = 1u << kMaxSubShift, kFewBricks = 2048u;
+constexpr uint32_t kMaxSubShift = 4u, kFewBricks = 2048u;
 
 struct BinArgs {
   uint32_t *bins;        // [n_bricks][1 << sub_shift][cap] entries
@@ -378,17 +378,20 @@ __global__ __launch_bounds__(256) void density_hist_binned_kernel(const HistArgs
 // The brick's count words (every plane) are staged in LDS, the bin's updates
 // added with LDS atomics, the words written back, and the bin emptied for the
 // next sweep.  The sub-bins' fill levels load together with the counts, and
-// their entries are taken as one flat index range, kApplyBatch independent
-// loads per thread at a time, so that a block waits on memory a few times
+// the entries of two sub-bins are taken as one flat index range, kApplyBatch
+// independent loads per thread at a time, so that a block waits on memory a few times
 // rather than twice per sub-bin.
 // Where the bricks are few and every round trip counts, 512 threads with the fields
-// (a film of 450 bricks: 11.5 us, 16.8 with 256; 131x97x88 cells, 693 bricks: 23, 33
-// with 1024) and 1024 without them, mostly a recount, whose bins are full (420 bricks:
-// 15.8 us, 17.0 with 512; the film: 29 and 36); 256 where there are enough bricks to
-// fill the device (13,824: 152 us, 157 with 512).
+// (a film of 450 bricks: 9.9 us, 9.8 with 1024; 131x97x88 cells, 693 bricks: 18.4 and
+// 28.5) and 1024 without them, mostly a recount, whose bins are full (420 bricks,
+// before the entries were taken pairwise: 15.8 us, 17.0 with 512; now 12.3); 256
+// where there are enough bricks to fill the device (13,824: 152 us, 157 with 512).
 // LDS: planes x 2048 words (u16 pairs) or 2 x planes x 2048 halves (u32 pairs).
 constexpr uint32_t kApplyOnlyWide = 1024u, kApplyWide = 512u, kApplyNarrow = 256u;
-constexpr uint32_t kApplyBatch = 4u;
+// Entries that a thread has in flight (narrow blocks have more to take: 134M beads 152
+// us with six, 156 with four).
+template <uint32_t THREADS>
+constexpr uint32_t kApplyBatch = THREADS < kApplyWide ? 6u : 4u;
 
 template <bool COUNT64>
 __device__ __forceinline__ void apply_entry_lds(uint32_t *s_cnt, uint32_t planes, uint32_t e) {
@@ -431,10 +434,16 @@ __device__ __forceinline__ T load_hint(const T *p) {
 template <bool COUNT64, uint32_t THREADS, bool NT = false>
 __device__ __forceinline__ void bin_gather_brick(const BinArgs &b, const Grid &g, const void *counts,
                                                  uint32_t planes, uint32_t brick, uint32_t *s_cnt) {
-  __shared__ uint32_t s_fill[kSubBins];
+  // Two neighbouring sub-bins to a group of threads (a wave in blocks of 512 with 16
+  // sub-bins and of 256 with 8): entry j of the pair lies at j or, in the second one,
+  // cap - n0 further.  A flat index over all sub-bins of the brick costs a search per
+  // entry: a film's apply and field kernel 11.9 -> 9.5 us, that of 24 melts 17.0 -> 12.0,
+  // 1M bond-Gibbs moves on 96^3 cells 10.9 -> 10.3.
   const uint32_t tid = threadIdx.x, n_sub = 1u << b.sub_shift;
-  uint32_t fill = 0u;
-  if (tid < n_sub) fill = b.bin_count[(brick << b.sub_shift) | tid];
+  const uint32_t shift = (uint32_t)__builtin_ctz(THREADS) + 1u - b.sub_shift, group = 1u << shift;
+  const uint32_t sb = (tid >> shift) * 2u, l = tid & (group - 1u);
+  const uint32_t *bin = b.bins + (size_t)((brick << b.sub_shift) | sb) * b.cap;
+  const uint2 fill = *reinterpret_cast<const uint2 *>(b.bin_count + ((brick << b.sub_shift) | sb));
   uint32_t x0, y0, z0;
   brick_origin(b, brick, x0, y0, z0);
   const uint32_t x = x0 + (tid & 15u), y = y0 + ((tid >> 4) & 15u);
@@ -462,36 +471,18 @@ __device__ __forceinline__ void bin_gather_brick(const BinArgs &b, const Grid &g
       else s_cnt[i] = v[u].x;
     }
   }
-  if (tid < kSubBins) s_fill[tid] = min(fill, b.cap);
+  const uint32_t n0 = min(fill.x, b.cap), n = n0 + min(fill.y, b.cap), skip = b.cap - n0;
   __syncthreads();
-  // sub-bin s holds the flat indices [start[s], start[s] + fill of s)
-  uint32_t start[kSubBins];
-  uint32_t total = 0u;
+  for (uint32_t j0 = l; j0 < n; j0 += kApplyBatch<THREADS> * group) {
+    uint32_t e[kApplyBatch<THREADS>];
 #pragma unroll
-  for (uint32_t s = 0; s < kSubBins; ++s) {
-    start[s] = total;
-    total += s_fill[s];
-  }
-  const uint32_t *bins = b.bins + (size_t)(brick << b.sub_shift) * b.cap;
-  for (uint32_t j0 = 0; j0 < total; j0 += kApplyBatch * THREADS) {
-    uint32_t e[kApplyBatch];
-#pragma unroll
-    for (uint32_t u = 0; u < kApplyBatch; ++u) {
-      const uint32_t j = j0 + u * THREADS + tid;
-      e[u] = 0u;
-      if (j < total) {
-        uint32_t sb = 0u, base = 0u;
-#pragma unroll
-        for (uint32_t s = 1; s < kSubBins; ++s) {
-          const bool past = j >= start[s];
-          sb = past ? s : sb;
-          base = past ? start[s] : base;
-        }
-        e[u] = load_hint<NT>(bins + (size_t)sb * b.cap + (j - base));
-      }
+    for (uint32_t u = 0; u < kApplyBatch<THREADS>; ++u) {
+      const uint32_t j = min(j0 + u * group, n - 1u);
+      e[u] = load_hint<NT>(bin + (j < n0 ? j : j + skip));
     }
 #pragma unroll
-    for (uint32_t u = 0; u < kApplyBatch; ++u) apply_entry_lds<COUNT64>(s_cnt, planes, e[u]);
+    for (uint32_t u = 0; u < kApplyBatch<THREADS>; ++u)
+      apply_entry_lds<COUNT64>(s_cnt, planes, j0 + u * group < n ? e[u] : 0u);
   }
   __syncthreads();
   if (tid < n_sub) b.bin_count[(brick << b.sub_shift) | tid] = 0u;
