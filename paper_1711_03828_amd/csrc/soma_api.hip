@@ -706,9 +706,9 @@ uint32_t subset_size(uint32_t n, uint32_t k, uint32_t j) { return n > j ? (n - j
 
 // Expected seconds of the count updates of a sweep of chain subset j of k, as
 // memory-side atomics and through the bins (without the bins' cost per launch),
-// added to what is there.
+// added to what is there; fullest: the longest that one block takes to apply a brick.
 void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j, double &atomics,
-                     double &bins) {
+                     double &bins, double &fullest) {
   const soma_config *c = &sys->cfg;
   double moved = 0.0, waves = 0.0;
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
@@ -725,6 +725,10 @@ void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t
   }
   atomics += 2.0 * 23e-12 * moved;
   bins += (double)sys->d.counts_bytes / 2e12 + 1e-10 * waves;
+  // a brick's entries are added by one block, 1 ns each; all bricks at once while
+  // they fit the device
+  if (sys->d.bins_ok)
+    fullest = std::max(fullest, 1e-9 * moved / (double)std::min<uint64_t>(sys->d.n_bricks, 512u));
 }
 constexpr double kBinsPerLaunch = 10e-6;
 
@@ -732,7 +736,9 @@ constexpr double kBinsPerLaunch = 10e-6;
 // the bins: where their atomics are expected to take longer than the bins do.
 // Measured: 23 ps per memory-side atomic (two per bead that changes cell); the
 // bins cost about 10 us a launch (their part of the kernel that applies them and
-// of the sweep's barriers), a pass over the counts, and 0.1 ns per wave.  Per SCMF
+// of the sweep's barriers), a pass over the counts, 0.1 ns per wave, and what the
+// fullest block takes (0.95M bond-Gibbs moves on 37x23x38 cells, 30 bricks: 54 us a
+// cycle with atomics, 64 with bins).  Per SCMF
 // cycle, atomics against bins, 256-thread blocks: 24^3 cells, 33k beads 8.1 / 12.5
 // us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71; film of 16M beads
 // 170 / 161; a batch of 24 melts, 3.3M beads 65 / 49; bond-Gibbs moves of 1M beads
@@ -741,9 +747,9 @@ constexpr double kBinsPerLaunch = 10e-6;
 // system, whose waves reserve room one by one.
 bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
   if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED || sys->sweep_blocks) return false;
-  double atomics = 0.0, bins = kBinsPerLaunch;
-  add_update_cost(sys, kind, k, j, atomics, bins);
-  return atomics > bins;
+  double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
+  add_update_cost(sys, kind, k, j, atomics, bins, fullest);
+  return atomics > bins + fullest;
 }
 
 // Whether the sweep of chain subset j of k sends its count updates through the bins.
@@ -2154,9 +2160,9 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   // bin tables at two blocks per compute unit
   bool binned = b->hist == soma::kHistBinned;
   if (!binned && b->hist_auto && b->bins_ok) {   // as bins_pay, for the whole batch
-    double atomics = 0.0, bins = kBinsPerLaunch;
-    for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins);
-    binned = atomics > bins;
+    double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
+    for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins, fullest);
+    binned = atomics > bins + 0.5 * fullest;   // blocks of twice the threads
   }
   binned = binned && kind != SOMA_MOVE_MIXED;
   if (b->c64) {

@@ -148,7 +148,7 @@ def test_default_mode_with_many_updates_equals_atomics(orc, kind, width, n, opti
     of its own, never reached, keeps them): the same bits, on a ragged grid."""
     from paper_1711_03828_amd import soma as C
     from paper_1711_03828_amd.melt import Melt
-    grid = (45, 37, 29)
+    grid = (141, 37, 29)
     chains = 900_000 // n
     sp = [Species(chains, n, n // 2)]
     k0 = np.float32(3.0 * 31 / 36.0)
