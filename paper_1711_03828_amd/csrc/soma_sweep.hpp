@@ -202,6 +202,13 @@ __device__ __forceinline__ LaneMap lane_map_tile(const SweepArgs &a, uint32_t ti
   return m;
 }
 
+// Lanes of the next and the previous bead pair of the chain; the lane itself where
+// there is none.  What comes from there has the weight 0, and the neighbouring lane
+// belongs to another chain (or loaded one, on an idle lane): 0 times a position of
+// its that is not finite would be NaN and stop this chain's end beads.
+__device__ __forceinline__ int lane_above(const LaneMap &m, bool exists) { return exists ? m.lane + 1 : m.lane; }
+__device__ __forceinline__ int lane_below(const LaneMap &m, bool exists) { return exists ? m.lane - 1 : m.lane; }
+
 __device__ __forceinline__ LaneMap lane_map(const SweepArgs &a) {
   const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x) * a.wpb + (threadIdx.x >> 6);
   return lane_map_tile(a, tile, true);
@@ -451,9 +458,9 @@ __device__ __forceinline__ uint32_t local_tile(const SweepArgs &a, const LaneMap
   const float dfa = trial_field(a, A), dfb = trial_field(a, B);
   // bonded neighbours of a: own b and b of the adjacent lane (lane k-1 if a is
   // even, lane k+1 if a is odd); of b: own a and a of the other adjacent lane
-  const int up = m.lane < 63 ? m.lane + 1 : m.lane, dn = m.lane > 0 ? m.lane - 1 : m.lane;
-  const int src_a = odd_first ? up : dn, src_b = odd_first ? dn : up;
   const bool lo_ok = m.k > 0, hi_ok = i0 + 2u < a.n;   // beads 2k-1 and 2k+2 exist
+  const int up = lane_above(m, hi_ok), dn = lane_below(m, lo_ok);
+  const int src_a = odd_first ? up : dn, src_b = odd_first ? dn : up;
   const float lo_w = lo_ok ? 1.0f : 0.0f, hi_w = hi_ok ? 1.0f : 0.0f;
   const float wadj_a = odd_first ? hi_w : lo_w, wadj_b = odd_first ? lo_w : hi_w;
 
@@ -619,7 +626,7 @@ __device__ __forceinline__ uint32_t smc_wave(const SweepArgs &a, const LaneMap &
   for (int pass = 0; pass < 2; ++pass) {
     const bool odd = (first ^ (uint32_t)pass) != 0u;
     const F3 send = sel(odd, r0, r1);
-    const int src = odd ? (m.lane < 63 ? m.lane + 1 : m.lane) : (m.lane > 0 ? m.lane - 1 : m.lane);
+    const int src = odd ? lane_above(m, i1 + 1u < N) : lane_below(m, m.k > 0);
     const F3 nb = {shfl_f(send.x, src), shfl_f(send.y, src), shfl_f(send.z, src)};
     const F3 left = sel(odd, r0, nb);
     const F3 right = sel(odd, nb, r1);
@@ -811,7 +818,7 @@ __device__ __forceinline__ void mixed_wave(const SweepArgs &a, const MixArgs &mx
   for (int pass = 0; pass < 2; ++pass) {
     const bool odd = (first ^ (uint32_t)pass) != 0u;
     const F3 send = sel(odd, r0, r1);
-    const int src = odd ? (m.lane < 63 ? m.lane + 1 : m.lane) : (m.lane > 0 ? m.lane - 1 : m.lane);
+    const int src = odd ? lane_above(m, i1 + 1u < N) : lane_below(m, m.k > 0);
     const F3 nb = {shfl_f(send.x, src), shfl_f(send.y, src), shfl_f(send.z, src)};
     const F3 left = sel(odd, r0, nb);     // bead i-1
     const F3 right = sel(odd, nb, r1);    // bead i+1

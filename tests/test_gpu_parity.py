@@ -346,3 +346,39 @@ def test_invalid_configs_rejected(C):
     cfg.species[0].n = 129
     with pytest.raises(C.SomaError):
         C.soma_buffer_sizes(cfg)
+
+
+@pytest.mark.parametrize("n", [100, 32, 17])
+@pytest.mark.parametrize("kind", ["local", "smc", "gibbs", "mixed"])
+def test_nonfinite_chain_leaves_other_chains_alone(C, kind, n):
+    """A chain with a non-finite bead takes no other chain with it: without interactions (all
+    fields zero) every other chain makes the moves it makes beside a finite chain, bit for bit.
+    N = 100 leaves idle lanes in every wave, N = 32 none, N = 17 ends on a half-filled lane; the
+    bead is the first or the last of its chain, next to a lane of another one."""
+    from paper_1711_03828_amd.melt import Melt
+    move = {"local": C.SOMA_MOVE_LOCAL, "smc": C.SOMA_MOVE_SMC, "gibbs": C.SOMA_MOVE_GIBBS,
+            "mixed": C.SOMA_MOVE_MIXED}[kind]
+    grid, chains, k0 = (20, 18, 16), 41, np.float32(3.0 * 31 / 36.0)
+    pos = synth.gaussian_walks(51, chains, n, grid, 1 / math.sqrt(float(k0)))
+    cfg = custom_config(grid, [Species(chains, n, n // 2)], k0=k0, n_ref=32, local_a=0.45, smc_a=0.05,
+                        seed=4, p_learn=0.5 if kind == "mixed" else 0.0)
+    params = torch.from_numpy(synth.mlp_params(3, out_gain=0.3)).cuda()
+
+    def run(p):
+        m = Melt(cfg, positions=torch.from_numpy(p))
+        if kind == "mixed":
+            m.set_proposal(params)
+        m.sweep(2, move)
+        torch.cuda.synchronize()
+        out = m.pos.cpu().numpy().reshape(chains, n, 3)
+        m.close()
+        return out
+
+    good = run(pos)
+    for chain, bead, value in ((0, 0, np.nan), (0, 1, np.inf), (7, 0, -np.inf), (7, n - 1, np.nan)):
+        bad = pos.copy()
+        bad[chain * n + bead, 1] = value
+        got = run(bad)
+        others = np.arange(chains) != chain
+        same = (got[others] == good[others]).all(axis=(1, 2))
+        assert same.all(), (chain, bead, value, "chains that moved otherwise:", np.flatnonzero(~same).tolist())
