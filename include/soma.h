@@ -85,10 +85,11 @@ typedef enum soma_status {
 
 /* How the SET sweeps keep the occupation histogram (Eq. (4), Sec. 3.1.1)
  * current; see soma_set_histogram. */
-#define SOMA_HIST_DIRECT 0u /* one memory-side atomic per +-1 count update; sweeps expected to
-                               make many updates go through the bins (default) */
+#define SOMA_HIST_DIRECT 0u /* one memory-side atomic per +-1 count update */
 #define SOMA_HIST_BINNED 1u /* updates binned by brick of 16x16x8 cells, then applied
                                brick by brick in LDS */
+#define SOMA_HIST_AUTO 2u   /* sweep by sweep the one of the two that is expected to be
+                               faster (default) */
 
 /* Device error word bits (returned by soma_check / soma_observables). */
 #define SOMA_FLAG_POSITION 1u /* soma_observables found a position non-finite or |x| >= 2^22 */
@@ -319,18 +320,19 @@ int32_t soma_set_sweep_threads(soma_system *sys, uint32_t threads);
 /* Count updates of the SET-order sweeps (local, smart-MC, bond-Gibbs and
  * mixed moves of linear chains; the histogram of Eq. (4), Sec. 3.1.1).
  * SOMA_HIST_DIRECT: a bead that changes cell adds -1 and +1 to the packed
- * counts with two device atomics, except in sweeps (local, smart-MC and
- * bond-Gibbs moves, one wave per tile) whose expected number of updates makes the
- * bins of the other mode the faster way.  SOMA_HIST_BINNED: the grid is cut into
+ * counts with two device atomics.  SOMA_HIST_BINNED: the grid is cut into
  * bricks of 16 x 16 x 8 cells (x fastest; partial bricks at the faces); each
  * block groups its updates by brick, reserves room in the brick's bin in the
  * workspace with one atomic per (block, brick) and stores them there; after
  * the sweep one workgroup per brick adds its bin to the counts in LDS (a bin
  * that is full takes further updates as direct atomics).  soma_mc_sweep,
  * soma_cycle and captured cycles run that step themselves, so the counts are
- * current whenever a call returns its stream to the caller.  Both modes give
- * the same counts bit for bit (integer additions in any order); molecule-order,
- * architecture and batched sweeps always use direct atomics.  Capture graphs
+ * current whenever a call returns its stream to the caller.  SOMA_HIST_AUTO
+ * (default): bins for local, smart-MC and bond-Gibbs sweeps with one wave per
+ * tile whose expected number of updates makes them the faster way, atomics
+ * otherwise.  All modes give the same counts bit for bit (integer additions in
+ * any order); molecule-order and architecture sweeps always use direct atomics,
+ * batched sweeps follow soma_batch_set_histogram.  Capture graphs
  * again after a change.  SOMA_E_INVAL for an unknown mode, SOMA_E_UNSUPPORTED
  * for SOMA_HIST_BINNED on a grid of 2^21 bricks or more. */
 int32_t soma_set_histogram(soma_system *sys, uint32_t mode);
@@ -437,7 +439,11 @@ int32_t soma_run_cycle(soma_system *sys, uint32_t n_launches, void *stream);
  * acceptance counters advance accordingly).  With a cache file (may be NULL)
  * a stored choice for the same sizes and move kind is applied without running
  * anything (out->from_cache = 1); a new choice is appended to the file (text,
- * one line per key; an unwritable file is ignored).  BLOCKING. */
+ * one line per key; an unwritable file is ignored).  The system keeps the
+ * chosen shape, as if set by soma_set_histogram, soma_set_sweep_threads and
+ * soma_set_sweep_blocks (soma_batch_set_histogram, soma_batch_set_launch) with
+ * the values in *out: another system that is given these runs the same kernels.
+ * BLOCKING. */
 typedef struct soma_tune {
   uint32_t mode;          /* batches: 0 XCD ranges, 1 round-robin items */
   uint32_t grid_blocks;   /* 0: one block per tile group; else persistent blocks */
@@ -445,7 +451,7 @@ typedef struct soma_tune {
   uint32_t candidates;    /* shapes timed */
   uint32_t cycles_run;    /* SCMF cycles run while tuning */
   uint32_t from_cache;
-  uint32_t hist_mode;     /* single systems: SOMA_HIST_DIRECT or SOMA_HIST_BINNED */
+  uint32_t hist_mode;     /* SOMA_HIST_DIRECT or SOMA_HIST_BINNED, as timed */
   uint32_t block_threads; /* single systems: threads per block of the sweep */
 } soma_tune;
 /* Single systems, SET order: the search space is the histogram mode
@@ -482,11 +488,12 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
  * grid_blocks 0 (one block per item, default) or a persistent grid. */
 int32_t soma_batch_set_launch(soma_batch *b, uint32_t mode, uint32_t grid_blocks);
 /* Count updates of batched sweeps (Eq. (4), Sec. 3.1.1), as soma_set_histogram
- * for one system: SOMA_HIST_DIRECT (default; device atomics, or the bins for
- * sweeps expected to make many updates) or SOMA_HIST_BINNED, where each
+ * for one system, and for the batch as a whole whatever its systems are set to:
+ * SOMA_HIST_DIRECT, SOMA_HIST_BINNED, where each
  * sweep appends to the bins of every system's own workspace and one more launch
  * applies all of them brick by brick (mixed sweeps of a batch keep direct
- * atomics).  Counts, fields and trajectories are the same bits either way.  SOMA_E_UNSUPPORTED for SOMA_HIST_BINNED unless every
+ * atomics), or SOMA_HIST_AUTO (default).  Counts, fields and trajectories are
+ * the same bits in every mode.  SOMA_E_UNSUPPORTED for SOMA_HIST_BINNED unless every
  * system has bins (see soma_set_histogram) and at most two bead types. */
 int32_t soma_batch_set_histogram(soma_batch *b, uint32_t mode);
 /* n_sweeps sweeps of every system with fields fixed (asynchronous). */

@@ -485,8 +485,7 @@ struct soma_system {
   uint32_t arch_max_type[SOMA_MAX_SPECIES] = {};  // largest type code of their monomers
   uint32_t substeps = 1;      // field refreshes per SCMF cycle (chain subsets)
   uint32_t scheme = SOMA_SCHEME_SET;  // iteration order of local moves
-  uint32_t hist_mode = soma::kHistDirect;  // count updates of the SET sweeps (soma_set_histogram)
-  bool hist_auto = true;      // direct mode: sweeps with many updates may go through the bins
+  uint32_t hist_mode = soma::kHistAuto;  // count updates of the SET sweeps (soma_set_histogram)
   uint32_t sweep_threads = 256;  // block size of the local, smart-MC and bond-Gibbs sweeps
   uint32_t self_term = 0;        // add the bead's own share to cell-changing moves (soma_set_self_term)
   float4 *grad = nullptr;     // optional gradient field (caller-owned), see soma_set_grad_field
@@ -732,8 +731,8 @@ void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t
 }
 constexpr double kBinsPerLaunch = 10e-6;
 
-// Whether a sweep in the default histogram mode sends its count updates through
-// the bins: where their atomics are expected to take longer than the bins do.
+// Whether a sweep in SOMA_HIST_AUTO sends its count updates through the bins:
+// where their atomics are expected to take longer than the bins do.
 // Measured: 23 ps per memory-side atomic (two per bead that changes cell); the
 // bins cost about 10 us a launch (their part of the kernel that applies them and
 // of the sweep's barriers), a pass over the counts, 0.1 ns per wave, and what the
@@ -755,7 +754,7 @@ bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
 // Whether the sweep of chain subset j of k sends its count updates through the bins.
 bool sweep_binned(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
   return sys->hist_mode == soma::kHistBinned ||
-         (sys->hist_auto && sys->scheme == SOMA_SCHEME_SET && bins_pay(sys, kind, k, j));
+         (sys->hist_mode == soma::kHistAuto && sys->scheme == SOMA_SCHEME_SET && bins_pay(sys, kind, k, j));
 }
 
 // Whether the fields between two sweeps of one call may live in the blocked copy alone:
@@ -1130,14 +1129,14 @@ int32_t soma_set_scheme(soma_system *sys, uint32_t scheme) {
   return SOMA_OK;
 }
 
+static_assert(soma::kHistDirect == SOMA_HIST_DIRECT && soma::kHistBinned == SOMA_HIST_BINNED &&
+              soma::kHistAuto == SOMA_HIST_AUTO, "one numbering of the histogram modes");
 int32_t soma_set_histogram(soma_system *sys, uint32_t mode) {
   if (!sys) return fail(SOMA_E_INVAL, "system is NULL");
-  if (mode != SOMA_HIST_DIRECT && mode != SOMA_HIST_BINNED)
-    return fail(SOMA_E_INVAL, "histogram mode %u", mode);
+  if (mode > SOMA_HIST_AUTO) return fail(SOMA_E_INVAL, "histogram mode %u", mode);
   if (mode == SOMA_HIST_BINNED && !sys->d.bins_ok)
     return fail(SOMA_E_UNSUPPORTED, "binned count updates need fewer than 2^21 bricks of 16x16x8 cells");
-  sys->hist_mode = mode == SOMA_HIST_BINNED ? soma::kHistBinned : soma::kHistDirect;
-  sys->hist_auto = mode == SOMA_HIST_DIRECT;
+  sys->hist_mode = mode;
   return SOMA_OK;
 }
 
@@ -2035,8 +2034,7 @@ struct soma_batch {
   uint32_t n_items = 0, c64 = 0, v2 = 1;
   uint32_t mode = 0, grid_blocks = 0;  // launch shape (results do not depend on it)
   // binned count updates: every system's own bins, one apply launch for all
-  uint32_t hist = 0;                    // soma::kHistDirect or soma::kHistBinned
-  bool hist_auto = true;                // direct mode: the bins where they pay
+  uint32_t hist = soma::kHistAuto;
   bool bins_ok = false;                 // every system has bins and two bead types
   std::vector<soma::BinApplySeg> apply;
   std::vector<uint32_t> brick_first, af_first;   // blocks of the apply and of the apply + field launch
@@ -2159,7 +2157,7 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   // mixed sweeps keep direct atomics: their LDS tiles leave no room for the
   // bin tables at two blocks per compute unit
   bool binned = b->hist == soma::kHistBinned;
-  if (!binned && b->hist_auto && b->bins_ok) {   // as bins_pay, for the whole batch
+  if (b->hist == soma::kHistAuto && b->bins_ok) {   // as bins_pay, for the whole batch
     double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
     for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins, fullest);
     binned = atomics > bins + 0.5 * fullest;   // blocks of twice the threads
@@ -2378,13 +2376,11 @@ int32_t soma_batch_create(soma_system *const *systems, uint32_t n, void *workspa
 
 int32_t soma_batch_set_histogram(soma_batch *b, uint32_t mode) {
   if (!b) return fail(SOMA_E_INVAL, "batch is NULL");
-  if (mode != SOMA_HIST_DIRECT && mode != SOMA_HIST_BINNED)
-    return fail(SOMA_E_INVAL, "histogram mode %u", mode);
+  if (mode > SOMA_HIST_AUTO) return fail(SOMA_E_INVAL, "histogram mode %u", mode);
   if (mode == SOMA_HIST_BINNED && !b->bins_ok)
     return fail(SOMA_E_UNSUPPORTED,
                 "binned count updates need bins in every system and two bead types");
-  b->hist = mode == SOMA_HIST_BINNED ? soma::kHistBinned : soma::kHistDirect;
-  b->hist_auto = mode == SOMA_HIST_DIRECT;
+  b->hist = mode;
   return SOMA_OK;
 }
 
@@ -2616,7 +2612,6 @@ int32_t soma_autotune(soma_system *sys, uint32_t cycles, uint32_t move_kind,
     sys->sweep_blocks = grid;
     if (!mol) {
       sys->hist_mode = (mode & 1u) ? soma::kHistBinned : soma::kHistDirect;
-      sys->hist_auto = false;   // the measured choice, not the expected one
       sys->sweep_threads = 64u * (((mode >> 1) & 7u) + 1u);
     }
   };
@@ -2625,7 +2620,7 @@ int32_t soma_autotune(soma_system *sys, uint32_t cycles, uint32_t move_kind,
                          [&]() -> int32_t { return soma_cycle(sys, 1, move_kind, stream); }, out);
   if (!r) {
     out->mode = 0;   // the item order exists for batches only
-    out->hist_mode = sys->hist_mode == soma::kHistBinned ? SOMA_HIST_BINNED : SOMA_HIST_DIRECT;
+    out->hist_mode = mol ? SOMA_HIST_DIRECT : sys->hist_mode;
     out->block_threads = mol ? 256u : sys->sweep_threads;
   }
   return r;
@@ -2682,14 +2677,13 @@ int32_t soma_batch_autotune(soma_batch *b, uint32_t cycles, uint32_t move_kind,
                          [&](uint32_t mode, uint32_t grid) {
                            b->mode = mode & 1u;
                            b->hist = (mode >> 1) ? soma::kHistBinned : soma::kHistDirect;
-                           b->hist_auto = false;
                            b->grid_blocks = grid;
                          },
                          [&]() -> int32_t { return soma_batch_cycle(b, 1, move_kind, stream); },
                          out);
   if (!r) {
     out->mode = b->mode;
-    out->hist_mode = b->hist == soma::kHistBinned ? SOMA_HIST_BINNED : SOMA_HIST_DIRECT;
+    out->hist_mode = b->hist;
     out->block_threads = 256u;
   }
   return r;

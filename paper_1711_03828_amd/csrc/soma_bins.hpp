@@ -27,6 +27,7 @@ namespace soma {
 constexpr uint32_t kBrickCells = 2048u;      // 16 x 16 x 8
 constexpr uint32_t kHistDirect = 0u;         // one atomic per update
 constexpr uint32_t kHistBinned = 1u;         // per-brick bins, applied by bin_apply_kernel
+constexpr uint32_t kHistAuto = 2u;           // sweep by sweep, whichever is expected to be faster
 constexpr uint32_t kUpdPresent = 0x8000u;
 constexpr uint32_t kUpdMinus = 0x4000u;
 

@@ -179,7 +179,8 @@ class Melt:
         C.soma_set_scheme(self.handle, scheme)
 
     def set_histogram(self, mode: int):
-        """Count updates of SET sweeps: C.SOMA_HIST_DIRECT or C.SOMA_HIST_BINNED."""
+        """Count updates of SET sweeps: C.SOMA_HIST_DIRECT, C.SOMA_HIST_BINNED or
+        C.SOMA_HIST_AUTO (the default)."""
         C.soma_set_histogram(self.handle, mode)
 
     def choose_scheme(self, cycles: int, stream=None):

@@ -29,6 +29,7 @@ SOMA_SCHEME_SET = 0
 SOMA_SCHEME_MOLECULE = 1
 SOMA_HIST_DIRECT = 0
 SOMA_HIST_BINNED = 1
+SOMA_HIST_AUTO = 2
 SOMA_NOALLOC_TRAIN_WAVES = 128
 SOMA_FLAG_POSITION = 1
 SOMA_FLAG_NETWORK = 2

@@ -259,3 +259,81 @@ def test_binned_fullsize_equals_direct():
     assert obs.counts_conserved == 1 and obs.error_flags == 0
     direct.close()
     binned.close()
+
+
+def _workspace_words(melts, run):
+    """Words of the melts' workspaces that `run` changes: the counters and partial sums of a sweep
+    and a refresh are some ten thousand, the bin entries of a sweep one or two per moved bead."""
+    torch.cuda.synchronize()
+    before = [m.workspace.clone() for m in melts]
+    run()
+    torch.cuda.synchronize()
+    return sum(int((a.view(torch.int32) != m.workspace.view(torch.int32)).sum())
+               for a, m in zip(before, melts))
+
+
+FEW, MANY = 1 << 15, 1 << 17   # words: atomics stay below, bins come out above
+
+
+def _busy_melt(seed=6, grid=(141, 37, 29), beads=900_000, n=32, local_a=0.45, **kw):
+    """A melt whose bond-Gibbs and local sweeps move some half of its beads to other cells."""
+    from paper_1711_03828_amd.melt import Melt
+    k0 = np.float32(3.0 * 31 / 36.0)
+    return Melt(custom_config(grid, [Species(beads // n, n, n // 2)], k0=k0, n_ref=32, chi_n=25.0,
+                              kappa_n=50.0, local_a=local_a, smc_a=0.05625, seed=seed, **kw))
+
+
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("kind", ["gibbs", "smc", "local"])
+def test_histogram_modes_do_what_they_name(kind, batched):
+    """DIRECT never goes through the bins, BINNED always does, AUTO and a mode never set do here
+    (estimated atomics of 1.5 times and more what the bins cost), in sweeps, cycles and graphs."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Batch
+    move = {"local": C.SOMA_MOVE_LOCAL, "smc": C.SOMA_MOVE_SMC, "gibbs": C.SOMA_MOVE_GIBBS}[kind]
+    for mode in (None, C.SOMA_HIST_DIRECT, C.SOMA_HIST_BINNED, C.SOMA_HIST_AUTO):
+        melts = [_busy_melt(seed=6 + i, beads=1_800_000 if kind != "gibbs" else 900_000)
+                 for i in range(2 if batched else 1)]
+        target = Batch(melts) if batched else melts[0]
+        if mode is not None:
+            target.set_histogram(mode)
+        target.capture_cycle(1, move)
+        for what, run in (("sweep", lambda: target.sweep(1, move)), ("cycle", lambda: target.cycle(1, move)),
+                          ("graph", lambda: target.run_cycle(1))):
+            words = _workspace_words(melts, run)
+            flush(kind, batched, mode, what, words)
+            if mode == C.SOMA_HIST_DIRECT:
+                assert words < FEW, (mode, what)
+            else:
+                assert words > MANY, (mode, what)
+        for m in [target] + (melts if batched else []):
+            m.close()
+
+
+@pytest.mark.parametrize("batched", [False, True])
+def test_tuned_shape_set_again_runs_the_same_kernels(batched):
+    """The histogram mode that the autotuner reports, given to another melt by the setter, takes
+    the way that the tuned melt takes, for the tuned move kind and for another one."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Batch
+    sets = [[_busy_melt(seed=6 + i) for i in range(2 if batched else 1)] for _ in range(2)]
+    tuned, again = [Batch(m) if batched else m[0] for m in sets]
+    t = tuned.autotune(1, C.SOMA_MOVE_GIBBS)
+    assert t.hist_mode in (C.SOMA_HIST_DIRECT, C.SOMA_HIST_BINNED)
+    # the other mode first, so that a setter that does nothing is seen
+    again.set_histogram(1 - t.hist_mode)
+    again.set_histogram(t.hist_mode)
+    if batched:
+        again.set_launch(t.mode, t.grid_blocks)
+    else:
+        C.soma_set_sweep_threads(again.handle, t.block_threads)
+        C.soma_set_sweep_blocks(again.handle, t.grid_blocks)
+    for kind in (C.SOMA_MOVE_GIBBS, C.SOMA_MOVE_LOCAL):
+        words = [_workspace_words(m, lambda: x.cycle(1, kind)) for m, x in zip(sets, (tuned, again))]
+        flush("tuned", t.hist_mode, "kind", kind, words)
+        for w in words:
+            assert w > MANY if t.hist_mode == C.SOMA_HIST_BINNED else w < FEW
+    for x in (tuned, again):
+        x.set_histogram(C.SOMA_HIST_DIRECT)   # and atomics can be had after tuning
+    for m, x in zip(sets, (tuned, again)):
+        assert _workspace_words(m, lambda: x.cycle(1, C.SOMA_MOVE_GIBBS)) < FEW
