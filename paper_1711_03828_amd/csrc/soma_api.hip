@@ -703,6 +703,17 @@ bool species_vec2(const soma_system *sys, uint32_t sp) {
 // Chains sub_j, sub_j + sub_k, ... of a species of n chains.
 uint32_t subset_size(uint32_t n, uint32_t k, uint32_t j) { return n > j ? (n - j + k - 1) / k : 0u; }
 
+// Blocks of species sp's SET sweep of n_sub chains with one wave per tile, and whether
+// the system's grid limit makes it a persistent grid of fewer.
+uint64_t tile_blocks(const soma_system *sys, uint32_t sp, uint32_t kind, uint32_t n_sub) {
+  const uint32_t waves = (kind == SOMA_MOVE_MIXED ? 256u : sys->sweep_threads) / 64u;
+  const uint32_t chains = waves * (64u / ((sys->cfg.species[sp].n + 1u) / 2u));
+  return ((uint64_t)n_sub + chains - 1u) / chains;
+}
+bool persistent_grid(const soma_system *sys, uint32_t sp, uint32_t kind, uint32_t n_sub) {
+  return sys->sweep_blocks && sys->sweep_blocks < tile_blocks(sys, sp, kind, n_sub);
+}
+
 // Expected seconds of the count updates of a sweep of chain subset j of k, as
 // memory-side atomics and through the bins (without the bins' cost per launch),
 // added to what is there; fullest: the longest that one block takes to apply a brick.
@@ -745,7 +756,10 @@ constexpr double kBinsPerLaunch = 10e-6;
 // blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
 // system, whose waves reserve room one by one.
 bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
-  if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED || sys->sweep_blocks) return false;
+  if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED) return false;
+  for (uint32_t sp = 0; sp < sys->cfg.n_species; ++sp)
+    if (!sys->d.arch[sp] && persistent_grid(sys, sp, kind, subset_size(sys->cfg.species[sp].n_chains, k, j)))
+      return false;
   double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
   add_update_cost(sys, kind, k, j, atomics, bins, fullest);
   return atomics > bins + fullest;
@@ -828,9 +842,8 @@ int32_t launch_sweep(soma_system *sys, uint32_t kind, hipStream_t s, uint32_t of
     }
     const uint32_t threads = kind == SOMA_MOVE_MIXED ? 256u : sys->sweep_threads;
     a.wpb = threads / 64u;
-    const uint64_t chains_per_block = (uint64_t)(threads / 64u) * a.chains_per_wave;
-    uint64_t blocks = (a.n_sub + chains_per_block - 1) / chains_per_block;
-    if (sys->sweep_blocks && sys->sweep_blocks < blocks) {
+    uint64_t blocks = tile_blocks(sys, sp, kind, a.n_sub);
+    if (persistent_grid(sys, sp, kind, a.n_sub)) {
       blocks = sys->sweep_blocks;   // persistent: tiles from counters, zero between launches
       a.queue = reinterpret_cast<uint32_t *>(sys->ws + sys->d.off_queue);
     }

@@ -337,3 +337,64 @@ def test_tuned_shape_set_again_runs_the_same_kernels(batched):
         x.set_histogram(C.SOMA_HIST_DIRECT)   # and atomics can be had after tuning
     for m, x in zip(sets, (tuned, again)):
         assert _workspace_words(m, lambda: x.cycle(1, C.SOMA_MOVE_GIBBS)) < FEW
+
+
+def test_auto_mode_decides_by_the_grid_that_runs():
+    """SOMA_HIST_AUTO keeps atomics for persistent grids; a grid limit above the number of blocks
+    of the launch makes none, and changes nothing."""
+    from paper_1711_03828_amd import soma as C
+    m = _busy_melt(beads=1_800_000)
+    tiles = -(-(1_800_000 // 32) // 16)   # blocks of four waves of four chains
+    for blocks, binned in ((0, True), (1 << 30, True), (tiles, True), (tiles - 1, False), (512, False)):
+        C.soma_set_sweep_blocks(m.handle, blocks)
+        words = _workspace_words([m], lambda: m.cycle(1, C.SOMA_MOVE_LOCAL))
+        flush("limit", blocks, "words", words)
+        assert words > MANY if binned else words < FEW, blocks
+    m.close()
+
+
+@pytest.mark.parametrize("kind,width,n,option", [
+    ("gibbs", 16, 32, "walls"), ("gibbs", 32, 31, "substeps"), ("smc", 32, 32, "grad"),
+    ("smc", 16, 17, "captured"), ("local", 16, 45, "ext"), ("local", 32, 32, "captured")])
+def test_auto_mode_equals_direct(orc, kind, width, n, option):
+    """Cycles that SOMA_HIST_AUTO sends through the bins (with the fields refreshed by the kernel
+    that applies them; asserted) against the same cycles with SOMA_HIST_DIRECT (asserted): the same
+    bits on a ragged grid."""
+    from paper_1711_03828_amd import soma as C
+    grid = (141, 37, 29)
+    beads = (1_800_000 if kind != "gibbs" or option == "substeps" else 900_000) // n * n
+    move = {"local": C.SOMA_MOVE_LOCAL, "smc": C.SOMA_MOVE_SMC, "gibbs": C.SOMA_MOVE_GIBBS}[kind]
+    melts = [_busy_melt(grid=grid, beads=beads, n=n, count_width=width) for _ in range(2)]
+    auto, direct = melts
+    direct.set_histogram(C.SOMA_HIST_DIRECT)
+    ext = torch.from_numpy(synth.uniform_field(7, auto.n_cells, -2.0, 2.0)).cuda()
+    mask = torch.from_numpy(synth.pack_mask(synth.wall_cells(grid, [0])).view(np.int32)).cuda()
+    for m in melts:
+        if option == "walls":   # keep the start out of the wall plane z = 0
+            z = m.pos[:, 2]
+            z.add_((torch.remainder(z, float(grid[2])) < 1.0).float())
+            m.rebuild_histogram()
+        if option in ("walls", "ext"):
+            m.set_external(ext, mask if option == "walls" else None)
+        if option == "grad":
+            m.keep_grad_field()
+        if option == "substeps":
+            m.set_substeps(2)
+        if option == "captured":
+            m.capture_cycle(3, move)
+    run = (lambda m: m.run_cycle(1)) if option == "captured" else (lambda m: m.cycle(3, move))
+    for rep in range(3):
+        words = [_workspace_words([m], lambda: run(m)) for m in melts]
+        flush(kind, width, n, option, words)
+        assert words[0] > MANY and words[1] < FEW
+        assert torch.equal(auto.pos, direct.pos) and torch.equal(auto.counts, direct.counts), rep
+        assert torch.equal(auto.omega, direct.omega), rep
+        oa, od = auto.observables(), direct.observables()
+        assert oa.h_nb == od.h_nb and list(oa.accepted) == list(od.accepted)
+        assert (oa.count_a, oa.count_b) == (od.count_a, od.count_b)
+        assert oa.counts_conserved == 1 and oa.error_flags == 0
+    for m in melts:
+        m.sweep(2, move)
+    _compare(orc, direct, auto, [Species(beads // n, n, n // 2)], grid, "two sweeps")
+    for m in melts:
+        m.close()
