@@ -398,3 +398,31 @@ def test_auto_mode_equals_direct(orc, kind, width, n, option):
     _compare(orc, direct, auto, [Species(beads // n, n, n // 2)], grid, "two sweeps")
     for m in melts:
         m.close()
+
+
+def test_fullsize_binned_equals_atomics():
+    """134,217,728 beads on 384x384x192 cells, 32-bit counts: one local and one smart-MC cycle with
+    SOMA_HIST_DIRECT (atomics, then the field kernel; asserted) and with SOMA_HIST_BINNED from the
+    same state: the same bits, and the counts of a device recount."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Melt
+    cfg = device_config(synth.C2_LARGE)
+    flush("full size: device init (Philox walks)")
+    melts = direct, binned = Melt(cfg), Melt(cfg)
+    direct.set_histogram(C.SOMA_HIST_DIRECT)
+    binned.set_histogram(C.SOMA_HIST_BINNED)
+    for kind in (C.SOMA_MOVE_LOCAL, C.SOMA_MOVE_SMC):
+        words = [_workspace_words([m], lambda: m.cycle(1, kind)) for m in melts]
+        flush("full size: kind", kind, "words", words)
+        assert words[0] < FEW and words[1] > MANY
+        assert torch.equal(direct.pos, binned.pos)
+        assert torch.equal(direct.counts, binned.counts)
+        assert torch.equal(direct.omega, binned.omega)
+    recount = torch.zeros_like(direct.counts)
+    C.soma_density_hist(cfg, direct.pos.data_ptr(), recount.data_ptr(), _stream())
+    torch.cuda.synchronize()
+    assert torch.equal(recount, direct.counts)
+    for m in melts:
+        obs = m.observables()
+        assert obs.counts_conserved == 1 and obs.error_flags == 0
+        m.close()
