@@ -426,3 +426,54 @@ def test_fullsize_binned_equals_atomics():
         obs = m.observables()
         assert obs.counts_conserved == 1 and obs.error_flags == 0
         m.close()
+
+
+@pytest.mark.parametrize("kind,width,option", [("local", 16, "ext"), ("gibbs", 16, "substeps"),
+                                               ("smc", 32, "walls"), ("gibbs", 32, "plain")])
+def test_auto_mode_batch_equals_direct_melts(kind, width, option):
+    """A batch of uneven melts whose sweeps SOMA_HIST_AUTO, the default, sends through the bins
+    (asserted), eager and captured, against the same melts one by one with SOMA_HIST_DIRECT."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Batch
+    move = {"local": C.SOMA_MOVE_LOCAL, "smc": C.SOMA_MOVE_SMC, "gibbs": C.SOMA_MOVE_GIBBS}[kind]
+    shapes = [((141, 37, 29), 1_200_000, 32), ((57, 64, 41), 620_000, 31), ((20, 17, 9), 30_000, 100),
+              ((90, 33, 50), 900_000, 17)]
+    sets = []
+    for _ in range(2):
+        sets.append([_busy_melt(seed=20 + i, grid=g, beads=b, n=n, count_width=width)
+                     for i, (g, b, n) in enumerate(shapes)])
+        for m, (g, b, n) in zip(sets[-1], shapes):
+            ext = mask = None
+            if option == "ext":
+                ext = torch.from_numpy(synth.uniform_field(7, m.n_cells, -2.0, 2.0)).cuda()
+            if option == "walls":
+                z = m.pos[:, 2]
+                z.add_((torch.remainder(z, float(g[2])) < 1.0).float())
+                m.rebuild_histogram()
+                mask = torch.from_numpy(synth.pack_mask(synth.wall_cells(g, [0])).view(np.int32)).cuda()
+            if ext is not None or mask is not None:
+                m.kept = (ext, mask)
+                m.set_external(ext, mask)
+    batched, single = sets
+    batch = Batch(batched)
+    if option == "substeps":
+        batch.set_substeps(2)
+    for m in single:
+        m.set_histogram(C.SOMA_HIST_DIRECT)
+        if option == "substeps":
+            m.set_substeps(2)
+    batch.capture_cycle(3, move)
+    for run in (lambda: batch.cycle(3, move), lambda: batch.run_cycle(1), lambda: batch.run_cycle(1)):
+        words = [_workspace_words(batched, run),
+                 _workspace_words(single, lambda: [m.cycle(3, move) for m in single])]
+        flush(kind, width, option, words)
+        assert words[0] > MANY and words[1] < FEW
+        for i, (a, b) in enumerate(zip(batched, single)):
+            assert torch.equal(a.pos, b.pos) and torch.equal(a.counts, b.counts), i
+            assert torch.equal(a.omega, b.omega), i
+            oa, ob = a.observables(), b.observables()
+            assert oa.h_nb == ob.h_nb and list(oa.accepted) == list(ob.accepted), i
+            assert oa.counts_conserved == 1 and oa.error_flags == 0, i
+    batch.close()
+    for m in batched + single:
+        m.close()
