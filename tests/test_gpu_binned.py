@@ -477,3 +477,54 @@ def test_auto_mode_batch_equals_direct_melts(kind, width, option):
     batch.close()
     for m in batched + single:
         m.close()
+
+
+@pytest.mark.parametrize("width,grid,ext,learned", [
+    (32, (261, 250, 133), True, False), (32, (261, 250, 133), False, True),
+    (16, (300, 293, 203), True, True)])
+def test_several_cycles_with_external_field_and_halo_copy(width, grid, ext, learned):
+    """The fields between the cycles of one call in their blocked copy (asserted), with an external
+    field and with the learned proposal's copy kept beside them: the bits of cycles called one by
+    one, and of the mixed cycle that follows and reads the copy of the last refresh."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Melt
+    k0 = np.float32(3.0 * 31 / 36.0)
+    cfg = custom_config(grid, [Species(720_000, 32, 16)], k0=k0, n_ref=32, chi_n=25.0, kappa_n=50.0,
+                        local_a=0.45, count_width=width, seed=8, p_learn=0.3 if learned else 0.0)
+    melts = [Melt(cfg) for _ in range(3)]
+    flush("case", width, grid, ext, learned)
+    field = torch.from_numpy(synth.uniform_field(7, melts[0].n_cells, -2.0, 2.0)).cuda()
+    for m in melts:
+        m.set_histogram(C.SOMA_HIST_BINNED)
+        if ext:
+            m.set_external(field, None)
+        if learned:
+            m.set_proposal(torch.from_numpy(synth.mlp_params(3, out_gain=0.3)).cuda())
+    single, several, graph = melts
+    graph.capture_cycle(3, C.SOMA_MOVE_LOCAL)
+
+    def copy_words(m, run):   # of the last plane of the blocked copy, which ends the workspace
+        tail = m.workspace.view(torch.int32)[-m.n_cells:]
+        torch.cuda.synchronize()
+        before = tail.clone()
+        run()
+        torch.cuda.synchronize()
+        return int((before != tail).sum())
+
+    for rep in range(2):
+        assert copy_words(single, lambda: [single.cycle(1, C.SOMA_MOVE_LOCAL) for _ in range(3)]) == 0
+        assert copy_words(several, lambda: several.cycle(3, C.SOMA_MOVE_LOCAL)) > MANY
+        assert copy_words(graph, lambda: graph.run_cycle(1)) > MANY
+        for step in ("local", "mixed"):
+            for m in (several, graph):
+                assert torch.equal(m.pos, single.pos) and torch.equal(m.counts, single.counts), (rep, step)
+                assert torch.equal(m.omega, single.omega), (rep, step)
+                o = m.observables()
+                assert o.counts_conserved == 1 and o.error_flags == 0
+            if not learned or step == "mixed":
+                break
+            for m in melts:
+                m.cycle(1, C.SOMA_MOVE_MIXED)
+            torch.cuda.synchronize()
+    for m in melts:
+        m.close()
