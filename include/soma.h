@@ -131,7 +131,7 @@ typedef struct soma_buffers {
   float *pos;          uint64_t pos_bytes;       /* >= 12 * n_beads */
   void *counts;        uint64_t counts_bytes;    /* >= (4 or 8) * n_cells */
   float *omega;        uint64_t omega_bytes;     /* >= 8 * n_cells */
-  void *workspace;     uint64_t workspace_bytes; /* >= soma_workspace_size() */
+  void *workspace;     uint64_t workspace_bytes; /* >= soma_workspace_size(), see there */
 } soma_buffers;
 
 typedef struct soma_obs {
@@ -159,7 +159,13 @@ int32_t soma_buffer_sizes(const soma_config *cfg, uint64_t *pos_bytes,
                           uint64_t *counts_bytes, uint64_t *omega_bytes,
                           uint64_t *workspace_bytes);
 
-/* Workspace bytes (acceptance slots, reduction partials, error word). */
+/* Workspace bytes (counters, reduction partials, the bins of the count updates and,
+ * for learned proposals, a copy of the fields).  For melts past the caches (counts
+ * of 64 MiB and more, positions above 256 MiB) they end with a second copy of the
+ * fields, 16384 bytes per brick of 16 x 16 x 8 cells (ceil(nx/16) ceil(ny/16)
+ * ceil(nz/8) bricks), which soma_cycle and captured cycles use between the local
+ * sweeps of one call.  A workspace shorter by these bytes is accepted: the fields
+ * then stay in buf->omega throughout, and the results are the same bits. */
 int32_t soma_workspace_size(const soma_config *cfg, uint64_t *bytes);
 
 /* Creates a handle for the configuration and the caller buffers.

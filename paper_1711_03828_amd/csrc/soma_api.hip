@@ -77,7 +77,7 @@ struct Derived {
   // per-brick bins of count updates (soma_set_histogram): bricks of 16 x 16 x 8 cells
   uint32_t nbx = 0, nby = 0, nbz = 0, bin_cap = 0, sub_shift = 0;
   uint64_t n_bricks = 0, off_bin_count = 0, off_bins = 0;
-  uint64_t off_blocked = 0, blocked_plane = 0;   // blocked copy of the fields (0: not kept)
+  uint64_t off_blocked = 0, blocked_plane = 0;   // blocked copy of the fields, last in the workspace (0: not kept)
   bool bins_ok = false;
   uint64_t off_queue = 0;   // tile counters of persistent local sweeps
 };
@@ -1019,8 +1019,9 @@ int32_t check_buffers(const Derived &d, const soma_buffers *b) {
                                                     (unsigned long long)b->counts_bytes, (unsigned long long)d.counts_bytes);
   if (b->omega_bytes < d.omega_bytes) return fail(SOMA_E_SIZE, "omega: %llu < %llu bytes",
                                                   (unsigned long long)b->omega_bytes, (unsigned long long)d.omega_bytes);
-  if (b->workspace_bytes < d.ws_bytes) return fail(SOMA_E_SIZE, "workspace: %llu < %llu bytes",
-                                                   (unsigned long long)b->workspace_bytes, (unsigned long long)d.ws_bytes);
+  const uint64_t ws_least = d.blocked_plane ? d.off_blocked : d.ws_bytes;   // the blocked copy is optional
+  if (b->workspace_bytes < ws_least) return fail(SOMA_E_SIZE, "workspace: %llu < %llu bytes",
+                                                 (unsigned long long)b->workspace_bytes, (unsigned long long)ws_least);
   if (!aligned(b->pos, 4) || !aligned(b->counts, 16) || !aligned(b->omega, 16) ||
       !aligned(b->workspace, 256))
     return fail(SOMA_E_INVAL, "alignment: pos 4, counts 16, omega 16, workspace 256 bytes");
@@ -1059,6 +1060,10 @@ int32_t soma_init_system(const soma_config *cfg, const soma_buffers *buf, uint32
   if (rc) return rc;
   rc = check_buffers(d, buf);
   if (rc) return rc;
+  if (buf->workspace_bytes < d.ws_bytes) {   // a workspace without the blocked copy of the fields
+    d.blocked_plane = 0;
+    d.ws_bytes = d.off_blocked;
+  }
   soma_system *sys = new (std::nothrow) soma_system();
   if (!sys) return fail(SOMA_E_INVAL, "out of host memory");
   sys->cfg = *cfg;

@@ -528,3 +528,32 @@ def test_several_cycles_with_external_field_and_halo_copy(width, grid, ext, lear
             torch.cuda.synchronize()
     for m in melts:
         m.close()
+
+
+def test_workspace_without_the_blocked_copy(monkeypatch):
+    """A workspace shorter by the blocked copy of the fields is accepted and gives the same bits;
+    one byte less is refused."""
+    from paper_1711_03828_amd import soma as C
+    from paper_1711_03828_amd.melt import Melt
+    grid = (261, 250, 133)
+    copy = 16384 * math.prod(-(-g // b) for g, b in zip(grid, (16, 16, 8)))
+    cfg = custom_config(grid, [Species(720_000, 32, 16)], k0=np.float32(3.0 * 31 / 36.0), n_ref=32,
+                        chi_n=25.0, kappa_n=50.0, local_a=0.45, count_width=32, seed=8)
+    full = Melt(cfg)
+    sizes = C.soma_buffer_sizes(cfg)
+    monkeypatch.setattr(C, "soma_buffer_sizes", lambda c: (*sizes[:3], sizes[3] - copy))
+    short = Melt(cfg)
+    monkeypatch.setattr(C, "soma_buffer_sizes", lambda c: (*sizes[:3], sizes[3] - copy - 1))
+    with pytest.raises(C.SomaError) as e:
+        Melt(cfg)
+    assert e.value.code == C.SOMA_E_SIZE
+    for m in (full, short):
+        m.set_histogram(C.SOMA_HIST_BINNED)
+        m.cycle(3, C.SOMA_MOVE_LOCAL)
+        m.cycle(2, C.SOMA_MOVE_LOCAL)
+    torch.cuda.synchronize()
+    assert torch.equal(full.pos, short.pos) and torch.equal(full.counts, short.counts)
+    assert torch.equal(full.omega, short.omega)
+    assert short.observables().counts_conserved == 1
+    full.close()
+    short.close()
