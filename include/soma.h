@@ -34,7 +34,9 @@
  * Memory ownership: the caller owns every device buffer (positions, counts,
  * omega, workspace) and keeps it alive for the life of the handle.  The
  * library never allocates or frees device memory.  The handle owns only host
- * memory.
+ * memory.  soma_observables also uses a few KiB of pinned host memory, shared by
+ * all handles of the process: the first call allocates it, and it is freed with
+ * the last handle.
  *
  * Streams: every call takes a HIP stream (hipStream_t passed as void*; NULL is
  * the default stream) and only enqueues work on it, except where a call is
@@ -398,7 +400,9 @@ int32_t soma_rebuild_histogram(soma_system *sys, void *stream);
 
 /* BLOCKING.  Chain observables in FP64 (Re^2, Rg^2, bond lengths, bond and
  * field energies), acceptance counters, the count sums and H_nb of the last
- * field update, and the device error word.  Synchronizes `stream`.
+ * field update, and the device error word.  Synchronizes `stream`.  The first
+ * call of the process's handles allocates pinned host memory (see above); without
+ * it (none to be had, or more than 32 calls at once) the totals are copied.
  * Returns SOMA_E_DEVICE_FLAG (with *out filled) if the error word is set. */
 int32_t soma_observables(soma_system *sys, soma_obs *out, void *stream);
 
@@ -662,7 +666,9 @@ int32_t soma_train_step_noalloc(const float *features, const float *targets, uin
                                 void *stream);
 
 /* Releases the handle (host memory and a captured graph).  Call it after the
- * work queued through the handle has completed. */
+ * work queued through the handle has completed.  For the last handle of the
+ * process the pinned host memory of soma_observables is freed too, which may wait
+ * for other work on the device; it leaves stream captures in progress alone. */
 void soma_destroy(soma_system *sys);
 
 /* Message of the last failed call on this thread ("" if none). */

@@ -422,6 +422,18 @@ struct CycleGraph {
 // wants one and freed with the last system; a call takes a free slot for its own
 // duration, so calls on several threads and streams never share one.
 namespace {
+// Allocating or freeing pinned memory while a stream is captured (by this thread, or
+// by another one in the global mode) is refused and spoils that capture, unless the
+// calling thread is in the relaxed mode.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool changed;
+  RelaxedCapture() : changed(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+  ~RelaxedCapture() {
+    if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
 constexpr uint32_t kHostSlots = 32u;
 struct HostPool {
   std::mutex mu;
@@ -435,6 +447,7 @@ struct HostSlot {
   HostSlot() {
     std::lock_guard<std::mutex> lock(g_host.mu);
     if (!g_host.base) {
+      RelaxedCapture relaxed;
       void *p = nullptr;
       if (hipHostMalloc(&p, kHostSlots * sizeof(soma::Totals), hipHostMallocPortable) != hipSuccess) {
         (void)hipGetLastError();
@@ -461,8 +474,9 @@ void host_pool_system(bool created) {
   if (created) {
     ++g_host.systems;
   } else if (--g_host.systems == 0 && g_host.base) {
-    (void)hipHostFree(g_host.base);
-    g_host.base = nullptr;
+    RelaxedCapture relaxed;
+    if (hipHostFree(g_host.base) == hipSuccess) g_host.base = nullptr;
+    else (void)hipGetLastError();   // kept for the next system
   }
 }
 }  // namespace

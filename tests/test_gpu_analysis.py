@@ -96,3 +96,37 @@ def test_slab_pattern_peak():
     _, mean, cnt, peak = C.soma_sq_shells(sq, w.grid, 12)
     flush("slab shells", np.round(mean[:6], 1), "peak", peak)
     assert peak == 2
+
+
+@pytest.mark.parametrize("where", ["same thread", "another thread"])
+def test_destroying_the_last_system_spares_a_capture(where):
+    """The pinned totals of the observables go with the last system; a stream capture of the
+    caller's in progress (in this or in another thread) goes on, and later systems find no error."""
+    import gc
+    import threading
+    from paper_1711_03828_amd.melt import Melt
+    cfg = device_config(synth.scaled(synth.C1_SMALL, 64, (12, 12, 12)))
+    gc.collect()
+    melt = Melt(cfg)
+    before = melt.observables()
+    x = torch.arange(16, device="cuda", dtype=torch.float32)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = x + 1
+        if where == "same thread":
+            melt.close()
+        else:
+            t = threading.Thread(target=melt.close)
+            t.start()
+            t.join()
+        z = y * 2
+    for rep in range(2):
+        x.fill_(float(rep))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert z.sum().item() == 32.0 * (rep + 1)
+    again = Melt(cfg)
+    after = again.observables()
+    assert (after.re2_sum, after.h_nb, after.count_a) == (before.re2_sum, before.h_nb, before.count_a)
+    again.close()
