@@ -460,6 +460,18 @@ struct HostSlot {
     g_host.used |= 1u << index;
     ptr = g_host.base + index;
   }
+  // Waits for the stream whose kernel writes the slot.  Where that is refused (a capture
+  // of another thread in the global mode) the kernel may still be running: the wait is
+  // repeated in the relaxed mode, so that the slot is not handed on before it is written;
+  // a slot whose writer cannot be waited for stays taken.
+  hipError_t wait(hipStream_t s) {
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess && ptr) {
+      RelaxedCapture relaxed;
+      if (hipStreamSynchronize(s) != hipSuccess) ptr = nullptr;
+    }
+    return e;
+  }
   ~HostSlot() {
     if (!ptr) return;
     std::lock_guard<std::mutex> lock(g_host.mu);
@@ -473,7 +485,7 @@ void host_pool_system(bool created) {
   std::lock_guard<std::mutex> lock(g_host.mu);
   if (created) {
     ++g_host.systems;
-  } else if (--g_host.systems == 0 && g_host.base) {
+  } else if (--g_host.systems == 0 && g_host.base && g_host.used == 0u) {
     RelaxedCapture relaxed;
     if (hipHostFree(g_host.base) == hipSuccess) g_host.base = nullptr;
     else (void)hipGetLastError();   // kept for the next system
@@ -1538,7 +1550,9 @@ int32_t soma_observables(soma_system *sys, soma_obs *out, void *stream) {
                      sys->att(), sys->err(), dst);
   LAUNCH_TRY();
   if (!slot.ptr) HIP_TRY(hipMemcpyAsync(&t, dst, sizeof t, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  const hipError_t waited = slot.wait(s);
+  if (waited != hipSuccess)
+    return fail(SOMA_E_HIP, "hipStreamSynchronize(s) failed: %s", hipGetErrorString(waited));
   if (slot.ptr) t = *slot.ptr;
   std::memset(out, 0, sizeof *out);
   out->sweeps = sys->sweep;
