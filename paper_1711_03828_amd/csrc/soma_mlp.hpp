@@ -42,6 +42,13 @@ struct NetDev {
   __bf16 w2[64 * 64];              // [out][in]
   __bf16 w3[16 * 64];              // rows >= 6 zero
 };
+// net_weights_to_lds copies the biases as one row of 144 floats and the weights as one
+// of 144 x 64 BF16 numbers.
+static_assert(offsetof(NetDev, b1f) == 0 && offsetof(NetDev, b2) == 64 * 4 &&
+              offsetof(NetDev, b3) == 128 * 4 && offsetof(NetDev, w1f) == 144 * 4 &&
+              offsetof(NetDev, w2) == offsetof(NetDev, w1f) + 64 * 64 * 2 &&
+              offsetof(NetDev, w3) == offsetof(NetDev, w1f) + 128 * 64 * 2 &&
+              sizeof(NetDev) == offsetof(NetDev, w1f) + 144 * 64 * 2, "biases and weights in a row");
 
 struct HeadArgs {
   float m_max, lo, hi;         // mu = m tanh(z/m); log sigma = lo + (hi-lo) sigmoid(z)
@@ -98,12 +105,13 @@ constexpr uint32_t kNetBlock = 256u;   // threads of the blocks that evaluate th
 
 __device__ __forceinline__ void net_weights_to_lds(const NetDev *__restrict__ net, __bf16 *sw) {
   constexpr uint32_t kWords = (uint32_t)kWRows * 8u, kN = (kWords + kNetBlock - 1u) / kNetBlock;
-  const uint4 *src = reinterpret_cast<const uint4 *>(net->w1f);
+  const char *base = reinterpret_cast<const char *>(net);
+  const uint4 *src = reinterpret_cast<const uint4 *>(base + offsetof(NetDev, w1f));
   float *sb = reinterpret_cast<float *>(sw + kWBias);
   uint4 v[kN];
 #pragma unroll
   for (uint32_t q = 0; q < kN; ++q) v[q] = src[min(threadIdx.x + q * kNetBlock, kWords - 1u)];
-  const float b = net->b1f[min(threadIdx.x, 143u)];
+  const float b = reinterpret_cast<const float *>(base)[min(threadIdx.x, 143u)];
 #pragma unroll
   for (uint32_t q = 0; q < kN; ++q) {
     const uint32_t i = threadIdx.x + q * kNetBlock;
