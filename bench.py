@@ -502,10 +502,8 @@ def batched_leg(cycles: int):
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / (cycles // 10 * 10)
-    # the same cycles melt by melt (one launch per melt and kernel), in the
-    # histogram mode the batch was tuned to
-    for m in melts:
-        m.set_histogram(tune.hist_mode)
+    # the same cycles melt by melt (one launch per melt and kernel), every melt in
+    # the library's default histogram mode: large ones through the bins, small ones not
     e0.record(stream)
     for m in melts:
         m.cycle(10)
@@ -1094,7 +1092,7 @@ def main():
                          "hist_mode": "binned" if tune_main.hist_mode else "direct",
                          "recount_ms": recount_ms,
                          "recount_beads_per_s": w.n_beads / (recount_ms * 1e-3),
-                         "recount": "binned: a reservation atomic per (wave, brick), the "
+                         "recount": "binned: a reservation atomic per (block, brick), the "
                                     "updates added brick by brick in LDS"}
     if args.move == "local":
         # the molecule-parallel order (Sec. 3.1.2, scheme 1) on the same melt
