@@ -175,11 +175,15 @@ int32_t derive(const soma_config *c, Derived *d) {
   d->bins_ok = d->n_bricks < (1ull << 21);
   if (d->bins_ok) {
     // per sub-bin: twice its share of about half a brick's beads, plus slack
-    // (a recount fills about half a brick's beads, a smart-MC sweep about 0.45)
+    // (a recount fills about half a brick's beads, a smart-MC sweep about 0.45).  The
+    // entries come block by block: of ten blocks that a brick of 10,000 beads takes most
+    // of them from, with 512 threads each, ten of 16 sub-bins get one, some 500 entries
+    // of a bond-Gibbs sweep, so that there half a block is left free (160x160x80 cells,
+    // 9.7M beads: 137 us a cycle, 180 with a slack of 64, the rest going to atomics).
     const double per_brick = (double)d->n_beads * soma::kBrickCells / (double)n_cells;
     d->sub_shift = d->n_bricks < soma::kFewBricks ? soma::kMaxSubShift : soma::kMaxSubShift - 1u;
     const uint32_t n_sub = 1u << d->sub_shift;
-    uint64_t cap = (uint64_t)std::ceil(1.1 * per_brick / n_sub) + 64u;
+    uint64_t cap = (uint64_t)std::ceil(1.1 * per_brick / n_sub) + (d->sub_shift == soma::kMaxSubShift ? 576u : 64u);
     cap = (cap + 15u) / 16u * 16u;
     if (cap > (1ull << 22)) cap = 1ull << 22;
     d->bin_cap = (uint32_t)cap;
