@@ -746,9 +746,10 @@ bool persistent_grid(const soma_system *sys, uint32_t sp, uint32_t kind, uint32_
 
 // Expected seconds of the count updates of a sweep of chain subset j of k, as
 // memory-side atomics and through the bins (without the bins' cost per launch),
-// added to what is there; fullest: the longest that one block takes to apply a brick.
+// added to what is there; brick: the longest that one block takes to apply a system's
+// mean brick (uneven melts have fuller ones).
 void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j, double &atomics,
-                     double &bins, double &fullest) {
+                     double &bins, double &brick) {
   const soma_config *c = &sys->cfg;
   double moved = 0.0, waves = 0.0;
   for (uint32_t sp = 0; sp < c->n_species; ++sp) {
@@ -763,36 +764,37 @@ void add_update_cost(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t
     moved += chains * S.n * (1.0 - stay * stay * stay);
     waves += chains / (64u / ((S.n + 1u) / 2u));
   }
-  atomics += 2.0 * 23e-12 * moved;
-  bins += (double)sys->d.counts_bytes / 2e12 + 1e-10 * waves;
+  atomics += 2.0 * 28e-12 * moved;
+  bins += (double)sys->d.counts_bytes / 2e12 + 3e-10 * waves;
   // a brick's entries are added by one block, 1 ns each; all bricks at once while
   // they fit the device
   if (sys->d.bins_ok)
-    fullest = std::max(fullest, 1e-9 * moved / (double)std::min<uint64_t>(sys->d.n_bricks, 512u));
+    brick = std::max(brick, 1e-9 * moved / (double)std::min<uint64_t>(sys->d.n_bricks, 512u));
 }
-constexpr double kBinsPerLaunch = 10e-6;
+constexpr double kBinsPerLaunch = 8e-6;
 
 // Whether a sweep in SOMA_HIST_AUTO sends its count updates through the bins:
-// where their atomics are expected to take longer than the bins do.
-// Measured: 23 ps per memory-side atomic (two per bead that changes cell); the
-// bins cost about 10 us a launch (their part of the kernel that applies them and
-// of the sweep's barriers), a pass over the counts, 0.1 ns per wave, and what the
-// fullest block takes (0.95M bond-Gibbs moves on 37x23x38 cells, 30 bricks: 54 us a
-// cycle with atomics, 64 with bins).  Per SCMF
-// cycle, atomics against bins, 256-thread blocks: 24^3 cells, 33k beads 8.1 / 12.5
-// us; 40^3, 640k beads 15.5 / 20.9; 96^3, 8.4M beads 103 / 71; film of 16M beads
-// 170 / 161; a batch of 24 melts, 3.3M beads 65 / 49; bond-Gibbs moves of 1M beads
-// 61 / 31; smart-MC moves of 7.4M beads 320 / 141.  Mixed sweeps keep atomics (their
-// blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
+// where their atomics are expected to take longer than the bins do.  The estimate: 28 ps
+// per memory-side atomic (two per bead that changes cell); for the bins 8 us a launch
+// (their part of the kernel that applies them and of the sweep's barriers), a pass over
+// the counts, 0.3 ns per wave, and what a block takes for a brick.  The constants are
+// a fit to 90 random melts near the line (20,000 to 40M beads, N = 8 to 128, 9 to 1,800
+// bricks, three move kinds, 1 to 8 sub-steps): the mode chosen takes 1.0% longer than the
+// better one on the mean and 19% at worst (20M beads of N = 128 in two sub-steps: atomics
+// 75 us, bins 89), always atomics 18% longer, always bins 3%; on 60 others over the
+// whole range 0.5% and 15% at worst.  Per SCMF cycle, atomics against bins, 256-thread
+// blocks: 24^3 cells, 33k beads 8.1 / 12.5 us; 96^3, 8.4M beads 103 / 71; film of 16M
+// beads 183 / 154; smart-MC moves of 7.4M beads 347 / 150.  Mixed sweeps keep atomics
+// (their blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
 // system, whose waves reserve room one by one.
 bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
   if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED) return false;
   for (uint32_t sp = 0; sp < sys->cfg.n_species; ++sp)
     if (!sys->d.arch[sp] && persistent_grid(sys, sp, kind, subset_size(sys->cfg.species[sp].n_chains, k, j)))
       return false;
-  double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
-  add_update_cost(sys, kind, k, j, atomics, bins, fullest);
-  return atomics > bins + fullest;
+  double atomics = 0.0, bins = kBinsPerLaunch, brick = 0.0;
+  add_update_cost(sys, kind, k, j, atomics, bins, brick);
+  return atomics > bins + brick;
 }
 
 // Whether the sweep of chain subset j of k sends its count updates through the bins.
@@ -2207,10 +2209,15 @@ int32_t launch_batch_sweep(soma_batch *b, uint32_t kind, hipStream_t s, uint32_t
   // mixed sweeps keep direct atomics: their LDS tiles leave no room for the
   // bin tables at two blocks per compute unit
   bool binned = b->hist == soma::kHistBinned;
-  if (b->hist == soma::kHistAuto && b->bins_ok) {   // as bins_pay, for the whole batch
-    double atomics = 0.0, bins = kBinsPerLaunch, fullest = 0.0;
-    for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins, fullest);
-    binned = atomics > bins + 0.5 * fullest;   // blocks of twice the threads
+  // As bins_pay, for the whole batch.  Its melts are small: their atomics fall on few
+  // cells and take longer, and a brick has a block of twice the threads or more.  On
+  // 60 random batches (2 to 40 melts, 0.3M to 9M beads, three move kinds) the mode
+  // chosen takes 4% longer than the better one on the mean; with the constants of
+  // single systems and half a brick it took 16%, mostly atomics where bins were faster.
+  if (b->hist == soma::kHistAuto && b->bins_ok) {
+    double atomics = 0.0, bins = kBinsPerLaunch, brick = 0.0;
+    for (const soma_system *x : b->sys) add_update_cost(x, kind, b->substeps, j, atomics, bins, brick);
+    binned = 1.4 * atomics > bins + 0.1 * brick;
   }
   binned = binned && kind != SOMA_MOVE_MIXED;
   if (b->c64) {
