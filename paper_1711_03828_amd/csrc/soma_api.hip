@@ -807,8 +807,10 @@ bool sweep_binned(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j)
 // plain local sweeps through the bins, whose updates are applied and fields written
 // by apply_field_kernel, of melts that keep the copy (their fields and positions
 // outgrow the caches, so that the sweep is bound by the lines it gathers, of which a
-// chain's cells share fewer when a line holds 4 x 4 x 2 of them: 134M beads, 1034 us
-// per sweep from the copy, 1199 from omega; the refresh takes 153 us into either).
+// chain's cells share fewer when a line holds 4 x 4 x 2 of them).  134M beads: 980 us
+// per sweep from the copy, 1112 from omega in cycles called one by one, and 1170 from
+// omega in the first cycle of a call, whose caches the copy has filled; the refresh
+// takes 150 to 156 us into either; per cycle 1171 us in calls of four, 1267 in calls of one.
 bool fields_blocked(const soma_system *sys, uint32_t kind, uint32_t k) {
   if (!sys->d.blocked_plane || kind != SOMA_MOVE_LOCAL || sys->scheme != SOMA_SCHEME_SET ||
       sys->arch_mask || sys->d.n_types > 2 || sys->d.forbid || sys->grad)
@@ -931,7 +933,10 @@ int32_t launch_grad(soma_system *sys, hipStream_t s) {
   return SOMA_OK;
 }
 
-// The bins applied and the fields refreshed in one launch (two bead types).
+// The bins applied and the fields refreshed in one launch (two bead types).  Cycles
+// against sweep, apply and refresh called apart, binned local moves: 134M beads on
+// 384x384x192 cells 1267 and 1325 us (the kernel takes 156 us for the 95 and 100 of the
+// two), 79M on 256^3 713 and 737, 41M on 261x250x133 (partial bricks) 409 and 404.
 // Without statistics one block per brick; with them at most as many as there are
 // partials, each over several bricks.
 // blocked: the fields go to the blocked copy instead of omega.

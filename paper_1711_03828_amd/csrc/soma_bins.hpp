@@ -37,8 +37,10 @@ constexpr uint32_t kUpdMinus = 0x4000u;
 // instead of queueing on one (a returning atomic on one address takes about 100
 // ns at the memory side).  16 sub-bins on grids of fewer than kFewBricks bricks,
 // whose counters are few; 8 on larger ones, where the entries of a brick then lie
-// in fewer lines (134M-bead melt, 13,824 bricks: 1107 us per sweep, 1147 with 16;
-// a batch of small melts: 323 against 292 us the other way round).
+// in fewer lines (134M-bead melt, 13,824 bricks: 40 us less per sweep than with 16;
+// a batch of small melts: 323 against 292 us the other way round).  Between 700 and
+// 3,000 bricks a cycle takes the same either way within 3%, and there the line is
+// that of the recount, which the blocks of bin_apply_kernel decide (kApplyOnlyWide).
 constexpr uint32_t kMaxSubShift = 4u, kFewBricks = 2048u;
 
 struct BinArgs {
@@ -262,7 +264,7 @@ __device__ __forceinline__ void bins_begin(BinLds<WAVES, WAVEWISE> &s) {
 // wave, and of the block unless WAVEWISE, calls this together, once per
 // bins_begin.  The 8 waves of a 512-thread block work on neighbouring chains and
 // share most of their bricks: with one reservation per (block, brick) instead of
-// one per (wave, brick) the binned local sweep of the 134M-bead melt takes 1102 us
+// one per (wave, brick) the binned local sweep of the 134M-bead melt takes 1112 us
 // (was 1237), of 8.4M beads on 96^3 cells 58 us (101), of a 16M-bead film, whose
 // few bricks make the counters few, 132 us (280).
 template <bool COUNT64, uint32_t WAVES, bool WAVEWISE>
@@ -386,7 +388,9 @@ __global__ __launch_bounds__(256) void density_hist_binned_kernel(const HistArgs
 // (a film of 450 bricks: 9.9 us, 9.8 with 1024; 131x97x88 cells, 693 bricks: 18.4 and
 // 28.5) and 1024 without them, mostly a recount, whose bins are full (420 bricks,
 // before the entries were taken pairwise: 15.8 us, 17.0 with 512; now 12.3); 256
-// where there are enough bricks to fill the device (13,824: 152 us, 157 with 512).
+// where there are enough bricks to fill the device (13,824: 152 us, 157 with 512;
+// whole recounts with 16 sub-bins and 1024 threads against 8 and 256: 432 bricks 35 /
+// 45 us, 1,000 60 / 63, 1,440 82 / 83, 2,028 114 / 111, 2,688 147 / 143).
 // LDS: planes x 2048 words (u16 pairs) or 2 x planes x 2048 halves (u32 pairs).
 constexpr uint32_t kApplyOnlyWide = 1024u, kApplyWide = 512u, kApplyNarrow = 256u;
 // Entries that a thread has in flight (narrow blocks have more to take: 134M beads 152
