@@ -431,8 +431,8 @@ int32_t soma_cycle(soma_system *sys, uint32_t n_cycles, uint32_t move_kind, void
 
 /* ---- Captured SCMF cycles ----------------------------------------------
  * soma_capture_cycle records `cycles` SCMF cycles of the system (as soma_cycle,
- * with the system's sub-steps), followed by the
- * advance of the device sweep counter, into a HIP graph; soma_run_cycle
+ * with the system's sub-steps; the last field refresh advances the device sweep
+ * counter) into a HIP graph; soma_run_cycle
  * replays it n_launches times on `stream` (asynchronous).  A replay gives the
  * same bits as the same cycles called one by one.  The graph holds the launch
  * shape and buffers of capture time: capture again after

@@ -405,8 +405,8 @@ bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p
 
 }  // namespace
 
-// An instantiated graph of SCMF cycles (sweep, field refresh) x cycles, then
-// the advance of the device sweep counters.
+// An instantiated graph of SCMF cycles (sweep, field refresh) x cycles, the last
+// refresh advancing the device sweep counters.
 struct CycleGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;

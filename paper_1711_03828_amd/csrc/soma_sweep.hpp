@@ -946,8 +946,9 @@ __device__ __forceinline__ void mixed_finish(const SweepArgs &a, const MixArgs &
 // Blocks of four waves: feature tiles of 9.2 KB a wave and one copy of the weights
 // (21.3 KB), two blocks per compute unit, so two waves per SIMD; told so, the compiler
 // keeps the matrix results in ordinary registers.  Six waves a block (three per SIMD)
-// spill: 95 us where four take 88 (1M beads).  Bound by vector instructions (60% of
-// the time; the matrix cores 18%) and the gathers.
+// spill: 95 us where four take 88 (1M beads).  Bound by what two waves a SIMD leave
+// idle: vector instructions take 51% of the time (at four cycles each), the matrix
+// cores 18%, and a wave waits 38% of its time.
 template <bool COUNT64, bool VEC2, bool BINNED, bool PERSIST = false>
 __global__ __launch_bounds__(256, 2)
 void mc_sweep_mixed_kernel(const SweepArgs a_in, const MixArgs mx) {
