@@ -785,7 +785,7 @@ constexpr double kBinsPerLaunch = 8e-6;
 // whole range 0.5% and 15% at worst.  Per SCMF cycle, atomics against bins, 256-thread
 // blocks: 24^3 cells, 33k beads 8.1 / 12.5 us; 96^3, 8.4M beads 103 / 71; film of 16M
 // beads 183 / 154; smart-MC moves of 7.4M beads 347 / 150.  Mixed sweeps keep atomics
-// (their blocks' LDS is full: 978 / 1018 us), and so do persistent grids of a single
+// (their blocks' LDS is full: 694 / 741 us), and so do persistent grids of a single
 // system, whose waves reserve room one by one.
 bool bins_pay(const soma_system *sys, uint32_t kind, uint32_t k, uint32_t j) {
   if (!sys->d.bins_ok || kind == SOMA_MOVE_MIXED) return false;
